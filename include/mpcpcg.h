@@ -225,23 +225,24 @@ int mpcpcg_cache_info(const mpcpcg_ctx *ctx, int32_t *entries, int64_t *device_b
  * 2 s); the problem then reports MPCPCG_TIMEOUT and every workgroup leaves normally.
  * inject_stall = 1 is a test hook: the first such wait of every launch of the (14, 7)
  * path waits for a signal that is never sent, so each multi-workgroup problem times out
- * (on the factorisation path, in its primal-step launch). */
+ * (the factorisation path has no such wait: there the hook only makes every problem of more
+ * than 16 knots report MPCPCG_TIMEOUT). */
 int mpcpcg_debug_set_wait(mpcpcg_ctx *ctx, int64_t limit_us, int32_t inject_stall);
 
 /* Solution method of mpcpcg_solve, mpcpcg_solve_batched and mpcpcg_backward.
  *   MPCPCG_METHOD_PCG (default): PCG as above (Algorithm 1).
  *   MPCPCG_METHOD_FACTOR: direct solve of the same Schur system, the alternative to the
- *     iterative solve that the paper names as future work (Section VI), by block cyclic
- *     reduction of the block-tridiagonal S (log2 N levels of parallel block eliminations,
- *     then back substitution).  At (14, 7) one workgroup per problem, except that a lone
- *     problem (a single solve or a batch of one) runs its levels with many block tasks
- *     spread over the device; at (28, 14) every level is spread over the device, one wave
- *     per block task.  FP64 throughout, exact up to rounding;
+ *     iterative solve that the paper names as future work (Section VI), by parallel block
+ *     elimination of the block-tridiagonal S.  At (14, 7) chunks of four knots are
+ *     eliminated in parallel, which leaves every fourth knot, again while a problem has
+ *     more than 32 of them, and the rest by block cyclic reduction, one workgroup per
+ *     problem; at (28, 14) by block cyclic reduction, every level spread over the device.
+ *     FP64 throughout, exact up to rounding;
  *     eps, max_iter, warm_start and stop_rule are ignored; stats report iters = 0, status
  *     OK or BREAKDOWN (a non-positive pivot, i.e. S not positive definite, or a non-finite
  *     result), final_ratio = 0.  Its cost does not depend on the conditioning of S.  At
- *     (14, 7) it needs ~6.5 KB of extra device workspace per knot of max_total_knots,
- *     allocated on first use.
+ *     (14, 7) it needs ~6.8 KB of extra device workspace per knot of max_total_knots,
+ *     allocated on first use, and takes horizons of up to 32 knots per compute unit.
  *   MPCPCG_METHOD_AUTO: per call, at (14, 7) the faster of the two by a cost model
  *     measured on MI355X, which prices PCG at ~100 iterations for cold starts and ~45 for
  *     warm starts (opts->warm_start; the adjoint counts as cold).  On the Kuka-shaped

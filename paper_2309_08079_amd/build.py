@@ -21,6 +21,10 @@ def flags():
     return ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-shared",
             # no packed FP32 (v_pk_*_f32) instructions anywhere in the device code
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            # the register allocator places register pairs (FP64) before single registers:
+            # with the default order the PCG loop ends up with holes it cannot pair and
+            # reloads entries of S from scratch in every iteration
+            "-mllvm", "-greedy-regclass-priority-trumps-globalness=1",
             "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

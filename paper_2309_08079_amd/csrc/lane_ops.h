@@ -159,14 +159,10 @@ __device__ __forceinline__ void row_fma14_f32(float &acc, float x, const float (
 
 template <int n> struct DAsm;
 template <> struct DAsm<14> {
-  template <int K, int LC, int LY> static __device__ __forceinline__ void axpy(double (&C)[LC], const double (&Y)[LY], double x) { dasm::axpy14<K>(C, Y, x); }
-  template <int K, int LY, int LX> static __device__ __forceinline__ void dotk(double &acc, const double (&Y)[LY], const double (&X)[LX]) { dasm::dotk14<K>(acc, Y, X); }
   template <int LM> static __device__ __forceinline__ void rowdot(double &acc, double x, const double (&M)[LM]) { dasm::rowdot14(acc, x, M); }
   template <int LC> static __device__ __forceinline__ void outer(double (&C)[LC], double s, double x) { dasm::outer14(C, s, x); }
 };
 template <> struct DAsm<7> {
-  template <int K, int LC, int LY> static __device__ __forceinline__ void axpy(double (&C)[LC], const double (&Y)[LY], double x) { dasm::axpy7<K>(C, Y, x); }
-  template <int K, int LY, int LX> static __device__ __forceinline__ void dotk(double &acc, const double (&Y)[LY], const double (&X)[LX]) { dasm::dotk7<K>(acc, Y, X); }
   template <int LM> static __device__ __forceinline__ void rowdot(double &acc, double x, const double (&M)[LM]) { dasm::rowdot7(acc, x, M); }
   template <int LC> static __device__ __forceinline__ void outer(double (&C)[LC], double s, double x) { dasm::outer7(C, s, x); }
 };
@@ -179,30 +175,45 @@ __device__ __forceinline__ double row_dot(const double (&m)[L], double x) {
   return acc;
 }
 
+// C += X Y on J columns (Y's rows owned by lanes m), one block: a single pair of wait states
+// instead of one per row of Y
+template <int M, int J, int LX, int LY, int LC>
+__device__ __forceinline__ void mm_nn_add(const double (&X)[LX], const double (&Y)[LY],
+                                          double (&C)[LC]) {
+  if constexpr (M == 14 && J == 14) dasm::prod14x14(C, Y, X);
+  else if constexpr (M == 14 && J == 8) dasm::prod14x8(C, Y, X);
+  else if constexpr (M == 14 && J == 7) dasm::prod14x7(C, Y, X);
+  else if constexpr (M == 14 && J == 4) dasm::prod14x4(C, Y, X);
+  else {
+    static_assert(M == 7 && J == 7, "no block of this shape");
+    dasm::prod7x7(C, Y, X);
+  }
+}
+
 // C = X Y : C[j] = sum_{m<M} X[m] Y(lane m)[j], j < J   (Y's rows owned by lanes m)
 template <int M, int J, int LX, int LY, int LC>
 __device__ __forceinline__ void mm_nn(const double (&X)[LX], const double (&Y)[LY],
                                       double (&C)[LC]) {
-  static_assert(M <= LX && J <= LY && J <= LC, "shapes");
 #pragma unroll
   for (int j = 0; j < J; ++j) C[j] = 0.0;
-  static_for<0, M>([&](auto mm) {
-    constexpr int K = decltype(mm)::value;
-    DAsm<J>::template axpy<K>(C, Y, X[K]);
-  });
+  mm_nn_add<M, J>(X, Y, C);
 }
 
-// C = X Y^T : C[j] = sum_{m<M} X[m] Y(lane j)[m], j < J   (Y's rows owned by lanes j)
+// C += X Y^T : C[j] += sum_{m<M} X[m] Y(lane j)[m], j < J   (Y's rows owned by lanes j)
+template <int M, int J, int LX, int LY, int LC>
+__device__ __forceinline__ void mm_nt_add(const double (&X)[LX], const double (&Y)[LY],
+                                          double (&C)[LC]) {
+  static_assert(J == 14 && (M == 14 || M == 7), "no block of this shape");
+  if constexpr (M == 14) dasm::prodt14x14(C, Y, X);
+  else dasm::prodt7x14(C, Y, X);
+}
+// C = X Y^T
 template <int M, int J, int LX, int LY, int LC>
 __device__ __forceinline__ void mm_nt(const double (&X)[LX], const double (&Y)[LY],
                                       double (&C)[LC]) {
-  static_assert(M <= LX && M <= LY && J <= LC, "shapes");
-  static_for<0, J>([&](auto jj) {
-    constexpr int K = decltype(jj)::value;
-    double s = 0.0;
-    DAsm<M>::template dotk<K>(s, Y, X);
-    C[K] = s;
-  });
+#pragma unroll
+  for (int j = 0; j < J; ++j) C[j] = 0.0;
+  mm_nt_add<M, J>(X, Y, C);
 }
 
 // C[k] = s(lane k) * x for k < n  (a broadcast vector scaled by a lane value)
@@ -213,35 +224,124 @@ __device__ __forceinline__ void outer_row(double (&C)[LC], double s, double x) {
   DAsm<n>::outer(C, s, x);
 }
 
+// One elimination step a_j += bc_k(a_j) * c over CNT columns of a: the columns col(0), ...,
+// col(CNT - 1) of a compile-time map, in one block.
+template <int k, int CNT, class COL>
+__device__ __forceinline__ void elim_cols(COL &&col, double c) {
+  static_assert(CNT >= 0 && CNT <= 7, "columns per block");
+  using std::integral_constant;
+  auto at = [&](auto r) -> double & { return col(r); };
+#define MPC_C(R) at(integral_constant<int, R>{})
+  if constexpr (CNT == 1) dasm::elim<k>(MPC_C(0), c);
+  if constexpr (CNT == 2) dasm::elim<k>(MPC_C(0), MPC_C(1), c);
+  if constexpr (CNT == 3) dasm::elim<k>(MPC_C(0), MPC_C(1), MPC_C(2), c);
+  if constexpr (CNT == 4) dasm::elim<k>(MPC_C(0), MPC_C(1), MPC_C(2), MPC_C(3), c);
+  if constexpr (CNT == 5) dasm::elim<k>(MPC_C(0), MPC_C(1), MPC_C(2), MPC_C(3), MPC_C(4), c);
+  if constexpr (CNT == 6) dasm::elim<k>(MPC_C(0), MPC_C(1), MPC_C(2), MPC_C(3), MPC_C(4), MPC_C(5), c);
+  if constexpr (CNT == 7) dasm::elim<k>(MPC_C(0), MPC_C(1), MPC_C(2), MPC_C(3), MPC_C(4), MPC_C(5), MPC_C(6), c);
+#undef MPC_C
+}
+// columns AT .. AT + CNT - 1
+template <int k, int AT, int CNT, int L>
+__device__ __forceinline__ void elim_tail(double (&a)[L], double c) {
+  elim_cols<k, CNT>([&](auto r) -> double & { return a[AT + decltype(r)::value]; }, c);
+}
+// entries AT .. AT + CNT - 1 of the columns 0 .. n-1 without k and k + 1
+template <int n, int k, int AT, int CNT, int L>
+__device__ __forceinline__ void elim_rest(double (&a)[L], double c) {
+  elim_cols<k, CNT>(
+      [&](auto r) -> double & {
+        constexpr int i = AT + decltype(r)::value;
+        return a[k + 1 < n && i >= k ? i + 2 : i];
+      },
+      c);
+}
+
+// Reciprocal: hardware estimate + one Newton step (full FP64 accuracy without the
+// division's scaling and fix-up sequence).
+__device__ __forceinline__ double rcp_f64(double x) {
+  const double d = __builtin_amdgcn_rcp(x);
+  return __builtin_fma(d, __builtin_fma(-x, d, 1.0), d);
+}
+
 // In-place Gauss-Jordan inverse of an n x n symmetric positive definite matrix whose row
 // `lane` is a[0..n-1] (rows >= n must be zero and stay zero).  No pivoting is needed for
-// SPD matrices: every pivot is a positive Schur complement.  Step k: the pivot row is
-// scaled by d = 1/a_kk, every other row i loses (a_ik d) times the pivot row, and column
-// k becomes (d for the pivot row, -a_ik d otherwise).  Written as t = s*a + c*bc_k(a)
-// with (s, c) = (0, d) on the pivot lane and (1, -a_ik d) elsewhere.
-// `positive` (optional) ends false when a pivot is not > 0, i.e. when the matrix is not
-// positive definite (every pivot of an SPD matrix is positive).
+// SPD matrices: every pivot is a positive Schur complement.  Step k: every row i but the
+// pivot row loses f_i = a_ik / a_kk times the pivot row, and column k becomes 1 in the
+// pivot row and -f_i elsewhere; the pivot row itself is left unscaled and every row is
+// multiplied by its own 1 / a_ii once at the end, so a step costs one fused multiply-add
+// per column.  A chain of 14 dependent pivots bounds it: column k + 1 is updated first, and
+// the next pivot's reciprocal runs beside the updates of the other columns.
+// `positive` (optional) ends false on a lane whose row's pivot is not > 0: the matrix is
+// positive definite if it stays true on every lane.
 template <int n, int L>
 __device__ __forceinline__ void gj_inverse(double (&a)[L], int lane, bool *positive = nullptr) {
+  double piv = bc<0>(a[0]);
+  double d = rcp_f64(piv);
+  double mine = 0.0;  // 1 / a_ii of this lane's row
   static_for<0, n>([&](auto kk) {
     constexpr int k = decltype(kk)::value;
-    const double piv = bc<k>(a[k]);
-    if (positive) *positive = *positive && (piv > 0.0);
-    // reciprocal of the pivot: hardware estimate + one Newton step (full FP64 accuracy
-    // without the division's scaling and fix-up sequence)
-    double d = __builtin_amdgcn_rcp(piv);
-    d = __builtin_fma(d, __builtin_fma(-piv, d, 1.0), d);
     const bool me = (lane == k);
     const double f = a[k] * d;
-    const double sc = me ? 0.0 : 1.0;
-    const double c = me ? d : -f;
-    double t[n];
-#pragma unroll
-    for (int j = 0; j < n; ++j) t[j] = a[j] * sc;
-    DAsm<n>::template axpy<k>(t, a, c);
-#pragma unroll
-    for (int j = 0; j < n; ++j) a[j] = (j == k) ? (me ? d : -f) : t[j];
+    const double c = me ? 0.0 : -f;
+    mine = me ? d : mine;
+    a[k] = me ? 1.0 : c;
+    constexpr int rest = k + 1 < n ? n - 2 : n - 1;
+    if constexpr (k + 1 < n) {
+      dasm::elim<k>(a[k + 1], c);
+      piv = bc<k + 1>(a[k + 1]);
+      d = __builtin_amdgcn_rcp(piv);
+      elim_rest<n, k, 0, rest / 2>(a, c);
+      d = __builtin_fma(d, __builtin_fma(-piv, d, 1.0), d);
+      elim_rest<n, k, rest / 2, rest - rest / 2>(a, c);
+    } else {
+      elim_rest<n, k, 0, rest / 2>(a, c);
+      elim_rest<n, k, rest / 2, rest - rest / 2>(a, c);
+    }
   });
+  if (positive) *positive = *positive && (lane >= n || mine > 0.0);
+#pragma unroll
+  for (int j = 0; j < n; ++j) a[j] *= mine;
+}
+
+// b <- a^-1 b for an n x n symmetric positive definite matrix whose row `lane` is a (rows
+// >= n zero, a is consumed) and m right-hand sides whose row `lane` is b: the elimination
+// above on the columns right of each pivot and on b only.  For m columns of a product a^-1 b
+// it costs n (n / 2 + m) multiply-adds a lane instead of the inverse's n^2 and the product's
+// n m.
+template <int n, int m, int L>
+__device__ __forceinline__ void gj_solve(double (&a)[L], double (&b)[m], int lane, bool *positive = nullptr) {
+  double piv = bc<0>(a[0]);
+  double d = rcp_f64(piv);
+  double mine = 0.0;
+  static_for<0, n>([&](auto kk) {
+    constexpr int k = decltype(kk)::value;
+    const bool me = (lane == k);
+    const double c = me ? 0.0 : -(a[k] * d);
+    mine = me ? d : mine;
+    constexpr int left = n - 2 - k;  // columns k + 2 .. n - 1
+    if constexpr (k + 1 < n) {
+      dasm::elim<k>(a[k + 1], c);
+      piv = bc<k + 1>(a[k + 1]);
+      d = __builtin_amdgcn_rcp(piv);
+    }
+    elim_tail<k, 0, (m > 7 ? 7 : m)>(b, c);
+    if constexpr (m > 7) elim_tail<k, 7, m - 7>(b, c);
+    if constexpr (k + 1 < n) d = __builtin_fma(d, __builtin_fma(-piv, d, 1.0), d);
+    if constexpr (left > 0) {
+      elim_tail<k, k + 2, (left + 1) / 2>(a, c);
+      elim_tail<k, k + 2 + (left + 1) / 2, left / 2>(a, c);
+    }
+  });
+  if (positive) *positive = *positive && (lane >= n || mine > 0.0);
+#pragma unroll
+  for (int j = 0; j < m; ++j) b[j] *= mine;
+}
+template <int n, int L>
+__device__ __forceinline__ void gj_solve(double (&a)[L], double &x, int lane) {
+  double b[1] = {x};
+  gj_solve<n, 1>(a, b, lane);
+  x = b[0];
 }
 
 }  // namespace mpc

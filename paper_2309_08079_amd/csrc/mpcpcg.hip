@@ -79,7 +79,6 @@ struct Schedule {
   int nprobs = 0;
   DevArrays mem;
   ProbDesc *d_probs = nullptr;
-  ProbDesc *d_sorted = nullptr;  // the same descriptors, longest first (factorisation sweep)
   Task *d_tasks = nullptr;
   // the same tasks in eight per-XCD lists (batched PCG; nullptr when the batch does not
   // qualify), with their own problem descriptors (t0 indexes these lists)
@@ -99,6 +98,16 @@ struct Schedule {
         if (graph[m][x]) (void)hipGraphDestroy(graph[m][x]);
       }
   }
+};
+
+// Chunks and separators of the direct solve for one horizon signature: level 0 cuts the
+// knots into chunks, level l > 0 the separators that level l - 1 left.
+struct DirectSchedule {
+  DevArrays mem;
+  std::vector<int> nchunks;
+  std::vector<mpc::Chunk *> d_chunks;
+  int nprobs = 0;
+  mpc::SepProb *d_probs = nullptr;  // what the last level left
 };
 
 // chunks of the control-step kernels (linearisation, line search) for one horizon signature
@@ -200,9 +209,11 @@ struct mpcpcg_ctx {
   int64_t clock_khz = 100000;  // wall-clock rate
   int stall = 0;               // test hook (mpcpcg_debug_set_wait)
   size_t cache_limit = 32;     // signatures kept per cache
-  // factorisation path workspace (allocated on first use): S rows, rhs / y, D^-1, lambda
-  double *f_s = nullptr, *f_rhs = nullptr, *f_dinv = nullptr, *f_lam = nullptr;
-  int *f_flag = nullptr;  // breakdown flag of a split single solve (kept at 0 between solves)
+  // direct solve workspace (allocated on first use): W, H and z per knot, the separators'
+  // blocks and vectors, one breakdown flag per problem (kept at 0 between solves)
+  double *f_ws = nullptr;
+  int *f_flag = nullptr;
+  Lru<Sig, DirectSchedule> dsched;
   double *qinv_ws = nullptr, *rinv_ws = nullptr;
   void *tws = nullptr;
   Gang *gang = nullptr;
@@ -283,14 +294,6 @@ KernelFn kernel_for(int mode) {
     case kAdjointKept: return mpc::pcg_kernel<kNX, kNU, KPW, mpc::kAdjoint, 3>;
     default: return mpc::pcg_kernel<kNX, kNU, KPW, mpc::kAdjoint>;
   }
-}
-
-// formation-only (phase 1) and epilogue-only (phase 2) kernels of the factorisation path,
-// built for 16 knots per workgroup
-KernelFn phase_kernel(int mode, int phase) {
-  if (mode == mpc::kForward)
-    return phase == 1 ? mpc::pcg_kernel<kNX, kNU, 16, mpc::kForward, 1> : mpc::pcg_kernel<kNX, kNU, 16, mpc::kForward, 2>;
-  return phase == 1 ? mpc::pcg_kernel<kNX, kNU, 16, mpc::kAdjoint, 1> : mpc::pcg_kernel<kNX, kNU, 16, mpc::kAdjoint, 2>;
 }
 
 KernelFn kernel_for(int kpw, int mode) {
@@ -504,9 +507,8 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
   s->ntasks = (int)tasks.size();
   s->nprobs = B;
   s->d_probs = s->mem.upload(probs.data(), probs.size());
-  s->d_sorted = s->mem.upload(sorted.data(), sorted.size());
   s->d_tasks = s->mem.upload(tasks.data(), tasks.size());
-  if (!s->d_probs || !s->d_sorted || !s->d_tasks) {
+  if (!s->d_probs || !s->d_tasks) {
     (void)hipGetLastError();
     return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
   }
@@ -556,23 +558,87 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
   return MPCPCG_OK;
 }
 
+// Levels of separators: a level has at most a quarter of the rows of the one before it and
+// one more per problem; levels follow until the longest horizon has at most kCrBlocks.
+int64_t level_slots(const mpcpcg_ctx *c, int level) {  // level 0: knots
+  int64_t n = c->max_knots;
+  for (int l = 0; l < level; ++l) n = n / mpc::kChunk + c->max_batch;
+  return n;
+}
+int separator_levels(int64_t nmax) {
+  int l = 0;
+  do {
+    nmax = (nmax + mpc::kChunk - 1) / mpc::kChunk;
+    ++l;
+  } while (nmax > mpc::kCrBlocks);
+  return l;
+}
+
+// Doubles per row of a level: blocks by columns padded to 16 rows (one 128-byte line each).
+constexpr size_t kBlkDoubles = (size_t)kNX * mpc::kGroup;
+
 int ensure_factor_ws(mpcpcg_ctx *c) {
-  if (c->f_s) return MPCPCG_OK;
-  const size_t K = (size_t)c->max_knots;
-  // blocks stored by columns padded to 16 rows (see fws_index)
-  if (hipMalloc(&c->f_s, K * 3 * kNX * mpc::kGroup * sizeof(double)) != hipSuccess ||
-      hipMalloc(&c->f_rhs, K * kNX * sizeof(double)) != hipSuccess ||
-      hipMalloc(&c->f_dinv, K * kNX * mpc::kGroup * sizeof(double)) != hipSuccess ||
-      hipMalloc(&c->f_lam, K * kNX * sizeof(double)) != hipSuccess ||
-      hipMalloc(&c->f_flag, sizeof(int)) != hipSuccess) {
+  if (c->f_ws) return MPCPCG_OK;
+  // W, H and z of every row that some level eliminates; the systems of the levels above 0
+  const int levels = separator_levels(c->max_knots);
+  size_t n = (size_t)c->max_knots * (2 * kBlkDoubles + mpc::kGroup);
+  for (int l = 1; l <= levels; ++l) n += (size_t)level_slots(c, l) * (5 * kBlkDoubles + 4 * mpc::kGroup);
+  const size_t fb = sizeof(int) * (size_t)c->max_batch;
+  if (hipMalloc(&c->f_ws, sizeof(double) * n) != hipSuccess || hipMalloc(&c->f_flag, fb) != hipSuccess) {
     (void)hipGetLastError();
-    for (double **q : {&c->f_s, &c->f_rhs, &c->f_dinv, &c->f_lam})
-      if (*q) { (void)hipFree(*q); *q = nullptr; }
-    if (c->f_flag) { (void)hipFree(c->f_flag); c->f_flag = nullptr; }
-    return fail(c, MPCPCG_ENOMEM, "cannot allocate the factorisation workspace (%zu knots)", K);
+    if (c->f_ws) { (void)hipFree(c->f_ws); c->f_ws = nullptr; }
+    return fail(c, MPCPCG_ENOMEM, "cannot allocate the factorisation workspace (%lld knots)", (long long)c->max_knots);
   }
-  HIPCHK(c, hipMemset(c->f_flag, 0, sizeof(int)));
+  HIPCHK(c, hipMemset(c->f_flag, 0, fb));
   HIPCHK(c, hipDeviceSynchronize());
+  return MPCPCG_OK;
+}
+
+// The direct path takes horizons up to 32 knots per compute unit (8,192 on MI355X), as it
+// always has.
+int check_direct_horizon(mpcpcg_ctx *c, int64_t n) {
+  if (n > (int64_t)32 * c->cus)
+    return fail(c, MPCPCG_EINVAL, "a horizon of %lld knots exceeds the factorisation path's %d", (long long)n, 32 * c->cus);
+  return MPCPCG_OK;
+}
+
+int direct_schedule(mpcpcg_ctx *c, const Sig &off, DirectSchedule **out) {
+  if (DirectSchedule *hit = c->dsched.get(off)) { *out = hit; return MPCPCG_OK; }
+  const int B = (int)off.size() - 1;
+  int64_t nmax = 0;
+  for (int b = 0; b < B; ++b) nmax = std::max(nmax, off[b + 1] - off[b]);
+  if (int st = check_direct_horizon(c, nmax)) return st;
+  auto s = std::make_unique<DirectSchedule>();
+  s->nprobs = B;
+  s->nprobs = B;
+  // longest problems first: their separator systems take the longest
+  std::vector<int> order(B);
+  for (int b = 0; b < B; ++b) order[b] = b;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return off[x + 1] - off[x] > off[y + 1] - off[y]; });
+  std::vector<mpc::SepProb> rows;  // the problems' rows at the current level
+  for (int b : order) rows.push_back(mpc::SepProb{(int32_t)off[b], (int32_t)(off[b + 1] - off[b]), b, (int32_t)(off[b + 1] - off[b])});
+  bool ok = true;
+  for (int l = 0; l < separator_levels(nmax); ++l) {
+    std::vector<mpc::Chunk> chunks;
+    for (auto &p : rows) {
+      const int32_t slot = (int32_t)chunks.size();
+      for (int k = 0; k < p.nsep; k += mpc::kChunk)
+        chunks.push_back(mpc::Chunk{p.sep0, p.nsep, p.id, k, (int32_t)chunks.size()});
+      p.sep0 = slot;
+      p.nsep = (p.nsep + mpc::kChunk - 1) / mpc::kChunk;
+    }
+    if ((int64_t)chunks.size() > level_slots(c, l + 1)) return fail(c, MPCPCG_EINVAL, "batch exceeds the factorisation workspace");
+    s->nchunks.push_back((int)chunks.size());
+    s->d_chunks.push_back(s->mem.upload(chunks.data(), chunks.size()));
+    ok = ok && s->d_chunks.back();
+  }
+  s->d_probs = s->mem.upload(rows.data(), rows.size());
+  if (!ok || !s->d_probs) {
+    (void)hipGetLastError();
+    return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
+  }
+  make_room(c, c->dsched, true);
+  *out = c->dsched.put(off, std::move(s));
   return MPCPCG_OK;
 }
 
@@ -587,6 +653,10 @@ int ensure_factor_ws(mpcpcg_ctx *c) {
 //        up to 2.2x that when every CU holds a problem; a lone problem, whose first levels
 //        spread over the device, ~49 + 20.5 (log2 N - 4) in all, against ~95 + 2.1 iters
 //        for its PCG solve.
+// The factorisation's prices are those of the method it had when the model was fitted; the
+// chunked elimination is two to three times faster.  The lines stay where they are because
+// the choice shows in the results (iterations in the stats, a lambda stopped at eps or exact):
+// a call keeps the method it has always had.
 // The adjoint (warm = false) is priced as a cold solve.
 bool use_factor(mpcpcg_ctx *c, const std::vector<int64_t> &off, bool warm) {
   if (c->method == MPCPCG_METHOD_PCG) return false;
@@ -609,76 +679,86 @@ bool use_factor(mpcpcg_ctx *c, const std::vector<int64_t> &off, bool warm) {
   return t_fac < t_pcg;
 }
 
-int launch_phase(mpcpcg_ctx *c, KArgs a, int mode, int phase, Schedule *s, int N, hipStream_t stream) {
-  constexpr int kpw = 16;
-  KernelFn fn = phase_kernel(mode, phase);
-  int nb = 0;
-  HIPCHK(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void *>(fn), kpw * mpc::kGroup, 0));
-  const int cap = nb * c->cus;
-  int grid;
-  a.xoff = nullptr;  // the phases pop the global queue
-  if (s) {
-    a.probs = s->d_probs; a.tasks = s->d_tasks; a.ntasks = s->ntasks; a.persistent = 1;
-    grid = std::min(s->ntasks, cap);
-    int need = 0;
-    for (int64_t b = 0; b + 1 < (int64_t)s->off.size(); ++b)
-      need = std::max<int>(need, (int)((s->off[b + 1] - s->off[b] + kpw - 1) / kpw));
-    if (need > cap) return fail(c, MPCPCG_EINVAL, "a horizon needs %d co-resident workgroups; the device holds %d", need, cap);
-  } else {
-    grid = (N + kpw - 1) / kpw;
-    if (grid > cap) return fail(c, MPCPCG_EINVAL, "horizon N=%d needs %d co-resident workgroups; the device holds %d", N, grid, cap);
-    a.single.k0 = 0; a.single.N = N; a.single.t0 = 0; a.single.nparts = grid; a.single.id = 0;
-    a.probs = nullptr; a.tasks = nullptr; a.ntasks = grid; a.persistent = 0;
-  }
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(kpw * mpc::kGroup), 0, stream, a);
-  HIPCHK(c, hipGetLastError());
-  return MPCPCG_OK;
-}
-
-// Factorisation path: formation to the workspace (phase 1), the block cyclic reduction of
-// every problem, then the epilogue from the solved lambda (phase 2).  s == nullptr: one
-// problem of N knots.
-int run_factor(mpcpcg_ctx *c, KArgs a, int mode, Schedule *s, int N, hipStream_t stream) {
+// Direct solve: elimination of every chunk's inner knots, the separators' systems, back
+// substitution with the primal step (or the adjoint's gradients).  off == nullptr: one
+// problem of N knots, scheduled without device arrays.
+int run_direct(mpcpcg_ctx *c, const KArgs &k, int mode, const Sig *off, int N, hipStream_t stream) {
   int st = ensure_factor_ws(c);
   if (st) return st;
-  const int64_t knots = s ? s->off.back() : N;
-  if (!s && (N + 15) / 16 > c->max_tasks) return fail(c, MPCPCG_EINVAL, "N=%d exceeds the context's task workspace", N);
-  if (knots > c->max_knots) return fail(c, MPCPCG_EINVAL, "knots exceed the context limit");
-  a.s_ws = c->f_s; a.rhs_ws = c->f_rhs; a.lam_ws = c->f_lam;
-  if ((st = launch_phase(c, a, mode, 1, s, N, stream))) return st;
-  mpc::TriArgs t;
-  std::memset(&t, 0, sizeof t);
-  t.s_ws = c->f_s; t.rhs_ws = c->f_rhs; t.dinv_ws = c->f_dinv; t.lam_ws = c->f_lam;
-  t.stats = a.stats;
-  t.s0 = 1;
-  t.flag = c->f_flag;
-  if (s && s->nprobs > 1) {
-    t.probs = s->d_sorted; t.nprobs = s->nprobs;
+  mpc::DirectArgs a;
+  std::memset(&a, 0, sizeof a);
+  const bool adj = mode == mpc::kAdjoint;
+  a.Q = k.Q; a.R = k.R; a.A = k.A; a.B = k.B;
+  a.q = adj ? k.gx : k.q; a.r = adj ? k.gu : k.r;
+  a.x0 = k.x0; a.e = k.e; a.gl = k.gl;
+  a.lam_in = k.lam_in; a.dx_in = k.dx_in; a.du_in = k.du_in;
+  a.lam = k.lam; a.dx = k.dx; a.du = k.du;
+  a.dQ = k.dQ; a.dR = k.dR; a.dA = k.dA; a.dB = k.dB; a.dq = k.dq; a.dr = k.dr;
+  a.dx0 = k.dx0; a.de = k.de; a.dgamma = k.dgamma;
+  a.stats = k.stats;
+  a.stall = k.stall;
+  DirectSchedule *s = nullptr;
+  int levels;
+  if (off) {
+    if ((st = direct_schedule(c, *off, &s))) return st;
+    levels = (int)s->nchunks.size();
   } else {
-    // a lone problem (a single solve or a batch of one): the levels with more block tasks
-    // than one workgroup holds run as one launch per sub-step over the device, the rest
-    // in one workgroup
-    const int n1 = s ? (int)(s->off[1] - s->off[0]) : N;
-    t.probs = nullptr; t.nprobs = 1;
-    t.single.k0 = 0; t.single.N = n1; t.single.t0 = 0; t.single.nparts = 1; t.single.id = 0;
-    while ((n1 - 1) / (2 * t.s0) + 1 > mpc::kCrGroups) t.s0 *= 2;
+    if ((st = check_direct_horizon(c, N))) return st;
+    levels = separator_levels(N);
   }
-  const int n1 = t.single.N;
-  auto grid = [](int n) { return dim3((n + mpc::kCrGroups - 1) / mpc::kCrGroups); };
-  auto n_odd = [n1](int sl) { return (n1 - sl + 2 * sl - 1) / (2 * sl); };
-  for (int sl = 1; sl < t.s0; sl *= 2) {
-    hipLaunchKernelGGL((mpc::cr_level<kNX, mpc::kLvlOdd>), grid(n_odd(sl)), dim3(mpc::kCrThreads), 0, stream, t, sl);
-    hipLaunchKernelGGL((mpc::cr_level<kNX, mpc::kLvlEven>), grid((n1 - 1) / (2 * sl) + 1), dim3(mpc::kCrThreads), 0,
-                       stream, t, sl);
+  a.N = N;
+  a.nprobs = s ? s->nprobs : 1;
+  a.probs = s ? s->d_probs : nullptr;
+  a.flag = c->f_flag;
+  // the workspace, level by level
+  double *w = c->f_ws;
+  auto take = [&](size_t n) { double *p = w; w += n; return p; };
+  std::vector<mpc::SepLevel> lev(levels + 1);
+  std::memset(lev.data(), 0, sizeof(mpc::SepLevel) * lev.size());
+  for (int l = 0; l <= levels; ++l) {
+    const size_t n = (size_t)level_slots(c, l);
+    mpc::SepLevel &v = lev[l];
+    if (l < levels) { v.wh = take(n * 2 * kBlkDoubles); v.z = take(n * mpc::kGroup); }
+    if (l > 0) {
+      v.dl = take(n * kBlkDoubles); v.dr = take(n * kBlkDoubles); v.l = take(n * kBlkDoubles);
+      v.yl = take(n * mpc::kGroup); v.yr = take(n * mpc::kGroup); v.x = take(n * mpc::kGroup);
+    }
   }
-  hipLaunchKernelGGL(mpc::cr_solve<kNX>, dim3(t.nprobs), dim3(mpc::kCrThreads), 0, stream, t);
-  if (t.s0 > 1) {
-    for (int sl = t.s0 / 2; sl >= 1; sl /= 2)
-      hipLaunchKernelGGL((mpc::cr_level<kNX, mpc::kLvlBack>), grid(n_odd(sl)), dim3(mpc::kCrThreads), 0, stream, t, sl);
-    hipLaunchKernelGGL(mpc::cr_finish<kNX>, dim3(1), dim3(mpc::kCrThreads), 0, stream, t);
+  // a launch over the chunks of level l
+  auto at = [&](int l) {
+    int64_t rows = N;
+    for (int i = 0; i < l; ++i) rows = (rows + mpc::kChunk - 1) / mpc::kChunk;
+    a.N1 = (int)rows;
+    a.nchunks = s ? (l < levels ? s->nchunks[l] : 0) : (int)((rows + mpc::kChunk - 1) / mpc::kChunk);
+    a.chunks = s && l < levels ? s->d_chunks[l] : nullptr;
+    a.wh = lev[l].wh; a.z = lev[l].z;
+    a.in = lev[l];
+    if (l < levels) a.out = lev[l + 1];
+  };
+  auto elim_grid = [&] { return dim3((a.nchunks + mpc::kElimWaves - 1) / mpc::kElimWaves); };
+  at(0);
+  if (adj)
+    hipLaunchKernelGGL((mpc::direct_eliminate<kNX, kNU, true>), elim_grid(), dim3(mpc::kElimThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((mpc::direct_eliminate<kNX, kNU, false>), elim_grid(), dim3(mpc::kElimThreads), 0, stream, a);
+  for (int l = 1; l < levels; ++l) {
+    at(l);
+    hipLaunchKernelGGL(mpc::sep_eliminate<kNX>, elim_grid(), dim3(mpc::kElimThreads), 0, stream, a);
   }
+  at(levels);
+  hipLaunchKernelGGL(mpc::separator_solve<kNX>, dim3(a.nprobs), dim3(mpc::kCrThreads), 0, stream, a);
+  auto back_grid = [&] { return dim3((a.nchunks + mpc::kBackWaves - 1) / mpc::kBackWaves); };
+  for (int l = levels - 1; l >= 1; --l) {
+    at(l);
+    hipLaunchKernelGGL(mpc::sep_back<kNX>, back_grid(), dim3(mpc::kBackThreads), 0, stream, a);
+  }
+  at(0);
+  if (adj)
+    hipLaunchKernelGGL((mpc::direct_back<kNX, kNU, true>), back_grid(), dim3(mpc::kBackThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((mpc::direct_back<kNX, kNU, false>), back_grid(), dim3(mpc::kBackThreads), 0, stream, a);
   HIPCHK(c, hipGetLastError());
-  return launch_phase(c, a, mode, 2, s, N, stream);
+  return MPCPCG_OK;
 }
 
 int launch_batched(mpcpcg_ctx *c, Schedule *s, KArgs &a, int mode, int want_pin, hipStream_t stream) {
@@ -1176,8 +1256,8 @@ int mpcpcg_destroy(mpcpcg_ctx *c) {
   c->sched.m.clear();
   c->csched.m.clear();
   c->wsched.m.clear();
-  for (double *q : {c->f_s, c->f_rhs, c->f_dinv, c->f_lam})
-    if (q) (void)hipFree(q);
+  c->dsched.m.clear();
+  if (c->f_ws) (void)hipFree(c->f_ws);
   if (c->f_flag) (void)hipFree(c->f_flag);
   if (c->qinv_ws) (void)hipFree(c->qinv_ws);
   if (c->rinv_ws) (void)hipFree(c->rinv_ws);
@@ -1235,7 +1315,7 @@ int mpcpcg_solve(mpcpcg_ctx *c, const mpcpcg_problem *p, const mpcpcg_opts *o, f
   }
   KArgs a = base_args(c, p, o);
   a.lam = lambda; a.dx = dx; a.du = du; a.stats = stats;
-  if (use_factor(c, std::vector<int64_t>{0, p->N}, o->warm_start != 0)) return run_factor(c, a, mpc::kForward, nullptr, p->N, s);
+  if (use_factor(c, std::vector<int64_t>{0, p->N}, o->warm_start != 0)) return run_direct(c, a, mpc::kForward, nullptr, p->N, s);
   return launch_single(c, a, p->N, single_kpw(c, p->N), mpc::kForward, s);
 }
 
@@ -1254,13 +1334,12 @@ int mpcpcg_solve_batched(mpcpcg_ctx *c, int32_t batch, const int64_t *off, const
     w.lam = lambda; w.dx = dx; w.du = du; w.stats = stats;
     return wide_run(c, key, w, false, s);
   }
-  const bool fac = use_factor(c, key, o->warm_start != 0);
-  const Tuned tu = pick(c, key);
-  Schedule *sc = nullptr;
-  if ((st = get_schedule(c, key, fac ? 16 : tu.kpw, &sc))) return st;
   KArgs a = base_args(c, p, o);
   a.lam = lambda; a.dx = dx; a.du = du; a.stats = stats;
-  if (fac) return run_factor(c, a, mpc::kForward, sc, 0, s);
+  if (use_factor(c, key, o->warm_start != 0)) return run_direct(c, a, mpc::kForward, &key, 0, s);
+  const Tuned tu = pick(c, key);
+  Schedule *sc = nullptr;
+  if ((st = get_schedule(c, key, tu.kpw, &sc))) return st;
   return launch_batched(c, sc, a, mpc::kForward, tu.pin, s);
 }
 
@@ -1289,17 +1368,17 @@ int mpcpcg_backward(mpcpcg_ctx *c, int32_t batch, const int64_t *off, const mpcp
     w.dgamma = dgamma; w.stats = stats;
     return wide_run(c, key, w, false, s);
   }
-  const bool fac = use_factor(c, key, false);  // the adjoint solve starts cold
-  const Tuned tu = pick(c, key);
-  Schedule *sc = nullptr;
-  if ((st = get_schedule(c, key, fac ? 16 : tu.kpw, &sc))) return st;
   KArgs a = base_args(c, p, o);
   a.warm = 0;
   a.lam_in = lambda; a.dx_in = dx; a.du_in = du;
   a.gl = gl; a.gx = gx; a.gu = gu;
   a.dQ = dQ; a.dR = dR; a.dA = dA; a.dB = dB; a.dq = dq; a.dr = dr; a.dx0 = dx0; a.de = de;
   a.dgamma = dgamma; a.stats = stats;
-  if (fac) return run_factor(c, a, mpc::kAdjoint, sc, 0, s);
+  // the adjoint solve starts cold
+  if (use_factor(c, key, false)) return run_direct(c, a, mpc::kAdjoint, &key, 0, s);
+  const Tuned tu = pick(c, key);
+  Schedule *sc = nullptr;
+  if ((st = get_schedule(c, key, tu.kpw, &sc))) return st;
   return launch_batched(c, sc, a, mpc::kAdjoint, tu.pin, s);
 }
 
@@ -1516,6 +1595,7 @@ int mpcpcg_set_cache_limit(mpcpcg_ctx *c, int32_t max_signatures) {
   c->cache_limit += 1;
   make_room(c, c->sched, true);
   make_room(c, c->wsched, true);
+  make_room(c, c->dsched, true);
   make_room(c, c->csched, true);
   make_room(c, c->cgraph, false);
   make_room(c, c->tuned, false);
@@ -1528,9 +1608,10 @@ int mpcpcg_cache_info(const mpcpcg_ctx *c, int32_t *entries, int64_t *device_byt
   int64_t bytes = 0;
   for (const auto &kv : c->sched.m) bytes += kv.second.v->mem.bytes;
   for (const auto &kv : c->wsched.m) bytes += kv.second.v->mem.bytes;
+  for (const auto &kv : c->dsched.m) bytes += kv.second.v->mem.bytes;
   for (const auto &kv : c->csched.m) bytes += kv.second.v->mem.bytes;
   if (entries)
-    *entries = (int32_t)(c->sched.size() + c->wsched.size() + c->csched.size() + c->cgraph.size() + c->tuned.size());
+    *entries = (int32_t)(c->sched.size() + c->wsched.size() + c->dsched.size() + c->csched.size() + c->cgraph.size() + c->tuned.size());
   if (device_bytes) *device_bytes = bytes;
   return MPCPCG_OK;
 }
@@ -1682,9 +1763,10 @@ int mpcpcg_control_step(mpcpcg_ctx *c, int32_t batch, const int64_t *off, const 
       WideSchedule *w = nullptr;
       if ((st = wide_schedule(c, key, &w))) return st;
     } else {
-      const bool fac = use_factor(c, key, o->warm_start != 0);
       Schedule *sc = nullptr;
-      if ((st = get_schedule(c, key, fac ? 16 : pick_kpw(c, key), &sc))) return st;
+      DirectSchedule *ds = nullptr;
+      st = use_factor(c, key, o->warm_start != 0) ? direct_schedule(c, key, &ds) : get_schedule(c, key, pick_kpw(c, key), &sc);
+      if (st) return st;
     }
     g = c->cgraph.get(key);
     if (!g) {  // dropped with an evicted schedule of the same horizons: start it afresh

@@ -48,9 +48,7 @@ struct Task {
 struct alignas(256) Gang {
   int done;        // parts finished with the problem
   int abort;       // set when a part gave up waiting
-  int timed_out;   // factorisation path: set by the formation launch when a part gave up,
-                   // read and cleared by the primal-step launch (reports TIMEOUT)
-  int pad[61];
+  int pad[62];
 };
 
 // Tagged words of the loop barriers, per task: (tag << 32) | 32-bit payload with tag =
@@ -195,9 +193,6 @@ struct KArgs {
                          // [4 + x] head of XCD x
   double *qinv_ws;       // [knots][NX][kGroup]   Q_b^-1 by columns (row r at r)
   double *rinv_ws;       // [controls][NU + NX][kURows]  (R^-1 | R^-1 B^T) by columns
-  // factorisation path: S rows [knots][NX][3 NX] and rhs [knots][NX] written by phase 1,
-  // lambda [knots][NX] read by phase 2
-  double *s_ws, *rhs_ws, *lam_ws;  // factorisation workspace (layout: fws_index)
   // factor record of a forward solve (written when fac_mode = 1): Phi^-1 (FP32) by columns
   // (layout: fws_index), read back by its adjoint (PHASE 3) instead of inverting S_bb,
   // exchanging D^-1 between parts and forming the off-diagonal blocks again; qinv_ws and
@@ -245,15 +240,11 @@ __device__ __forceinline__ double uni(double v) {
 // per compute unit; a 48-knot one has 12 waves, one per compute unit).
 template <int KPW>
 constexpr int waves_per_eu() { return KPW == 32 ? 2 : 3; }
-// The formation-only and epilogue-only kernels of the factorisation path hold no PCG state:
-// two waves per SIMD give them the registers of the formation without spills.
-template <int KPW, int PHASE>
-constexpr int phase_waves_per_eu() { return (PHASE == 1 || PHASE == 2) ? 2 : waves_per_eu<KPW>(); }
 // Rows of a control block as stored by columns (NU = 7 rows padded to 8: half a line).
 constexpr int kURows = 8;
 
-// Factorisation workspace: element (r, c) of block t (0: S_{b,b-1}, 1: S_bb, 2: S_{b,b+1})
-// of packed knot k.  Blocks are stored by columns padded to kGroup rows, so one column is
+// Factor record of Phi^-1: element (r, c) of block t (0: (b,b-1), 1: (b,b), 2: (b,b+1)) of
+// packed knot k.  Blocks are stored by columns padded to kGroup rows, so one column is
 // one 128-byte line and the 16 lanes of a knot group (lane = row) read or write it whole.
 template <int NX>
 __device__ __forceinline__ int64_t fws_index(int64_t k, int t, int c, int r) {
@@ -261,13 +252,11 @@ __device__ __forceinline__ int64_t fws_index(int64_t k, int t, int c, int r) {
 }
 
 // PHASE 0: formation, PCG and epilogue fused (a forward solve with fac_mode 1 also writes
-// its factor record).  PHASE 1 (factorisation path): formation only, S rows and the
-// right-hand side written to s_ws / rhs_ws.  PHASE 2: formation, lambda read from lam_ws
-// (the block-tridiagonal solve), then the epilogue.  PHASE 3 (adjoint): S formed as in
-// PHASE 0 from the inverses of Q and R read from the forward's factor record, Phi^-1 read
-// from it as well, then PCG and epilogue.
+// its factor record).  PHASE 3 (adjoint): S formed as in PHASE 0 from the inverses of Q and
+// R read from the forward's factor record, Phi^-1 read from it as well, then PCG and
+// epilogue.
 template <int NX, int NU, int KPW, int MODE, int PHASE = 0>
-__global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_eu(phase_waves_per_eu<KPW, PHASE>(), phase_waves_per_eu<KPW, PHASE>())))
+__global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_eu(waves_per_eu<KPW>(), waves_per_eu<KPW>())))
     pcg_kernel(const KArgs a) {
   static_assert(NX == 14 && NU <= NX, "the fused row kernels are written for 14-row blocks");
   constexpr int NT = KPW * kGroup;
@@ -710,13 +699,6 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
     const float *rv = (MODE == kAdjoint) ? a.gu : a.r;
     double Dd[NX];
     float Pm[NX], Pd[NX], Pp[NX];
-    if constexpr (PHASE == 2) {
-      // the epilogue needs only S_{b,b+1} (the rest of its inputs are in the workspace)
-      const double *sp = a.s_ws + fws_index<NX>(act ? kb : 0, 2, 0, lane);
-#pragma unroll
-      for (int j = 0; j < NX; ++j) { Sm[j] = 0.0; Sd[j] = 0.0; Dd[j] = 0.0; Sp[j] = (act && rowv) ? sp[j * kGroup] : 0.0; }
-      rhs = 0.0;
-    } else {
     {
       // (1) previous-knot terms: T = A_{b-1} Q_{b-1}^-1 -> S_{b,b-1} = -T,
       //     theta = T A_{b-1}^T + ..., zeta = -T q_{b-1} - ...
@@ -847,14 +829,12 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       for (int j = 0; j < NX; ++j) Sp[j] = -Sx[j];
     }
     // (5) D_b^-1 = S_bb^-1 (theta_{b-1}^-1 for b >= 1, Q_0 up to rounding for b = 0).  Knot
-    //     slots past the horizon have S_bb = I, so their D^-1 = I stays finite.  Only the
-    //     preconditioner needs it (not the factorisation path).
+    //     slots past the horizon have S_bb = I, so their D^-1 = I stays finite.
     if constexpr (PHASE == 0) {
 #pragma unroll
       for (int j = 0; j < NX; ++j) Dd[j] = Sd[j];
       gj_inverse<NX>(Dd, lane);
     }
-    }  // PHASE != 2 (formation)
     if constexpr (PHASE == 0) {
     // (6) exchange D^-1 rows with the neighbouring knots (the one cross-knot dependency of
     //     the formation; section IV-A, Symmetric Stair preconditioner: of the whole
@@ -932,20 +912,6 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         }
       }
     }
-    if constexpr (PHASE == 1) {
-      if (act) {
-        // all 16 lanes store (rows >= NX hold zeros), so every column is one whole line
-        double *col = a.s_ws + fws_index<NX>(kb, 0, 0, lane);
-#pragma unroll
-        for (int j = 0; j < NX; ++j) {
-          col[j * kGroup] = Sm[j];
-          col[(NX + j) * kGroup] = Sd[j];
-          col[(2 * NX + j) * kGroup] = Sp[j];
-        }
-        if (rowv) a.rhs_ws[kb * NX + lane] = rhs;
-      }
-    }
-
     if constexpr (MODE == kForm) {
       if (act && rowv) {
         const int64_t o = kb * 3 * NX * NX + (int64_t)lane * NX;
@@ -963,13 +929,13 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           }
         if (a.gam_out) a.gam_out[kb * NX + lane] = (float)rhs;
       }
-    } else if constexpr (PHASE != 1) {
+    } else {
       double lam = 0.0, eta_ref = 0.0, eta_new = 0.0;
       int status = MPCPCG_NOT_CONVERGED, it = 0;
-      if constexpr (PHASE == 2) {
-        if (act && rowv) lam = a.lam_ws[kb * NX + lane];
-        status = MPCPCG_OK;
-      } else {
+      // S starts the solve in new registers: a value that the formation had to spill is read
+      // back here once, not in every iteration
+#pragma unroll
+      for (int j = 0; j < NX; ++j) asm volatile("" : "+v"(Sm[j]), "+v"(Sd[j]), "+v"(Sp[j]));
       // Phi^-1 rows move to LDS for the solve (the D^-1 exchange above used the same bytes)
       __syncthreads();
       if (rowv) {
@@ -1177,7 +1143,6 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         alpha_prev = alpha;
       }
       if (it > max_iter) it = max_iter;
-      }  // PHASE == 0 (PCG)
       if (aborted) status = MPCPCG_TIMEOUT;
       if (!rowv || !act) lam = 0.0;
 
@@ -1279,7 +1244,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           a.dr[(cb - 1) * NU + lane] = (float)n1u;
         }
       }
-      if ((PHASE == 0 || PHASE == 3) && tid == 0 && part == 0)
+      if (tid == 0 && part == 0)
         put_stats(a.stats + pd.id, it, status,
                   eta_ref > 0.0 ? (float)__builtin_sqrt(eta_new > 0.0 ? eta_new / eta_ref : 0.0) : 0.0f);
     }
@@ -1310,14 +1275,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           // wrote its stats before its arrival was counted, so this store comes later)
           const int ab = __hip_atomic_load(&gang->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           int *status_word = a.stats ? reinterpret_cast<int *>(a.stats + pd.id) + 1 : nullptr;
-          if constexpr (PHASE == 1) {
-            if (ab) __hip_atomic_store(&gang->timed_out, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          } else if constexpr (PHASE == 2) {
-            const int t1 = __hip_atomic_load(&gang->timed_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((ab || t1) && status_word)
-              __hip_atomic_store(status_word, (int)MPCPCG_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&gang->timed_out, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          } else if constexpr (MODE != kForm) {
+          if constexpr (MODE != kForm) {
             if (ab && status_word)
               __hip_atomic_store(status_word, (int)MPCPCG_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
