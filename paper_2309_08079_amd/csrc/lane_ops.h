@@ -216,6 +216,11 @@ __device__ __forceinline__ void mm_nt(const double (&X)[LX], const double (&Y)[L
   mm_nt_add<M, J>(X, Y, C);
 }
 
+// C[k] += s(lane k) * x for k < n
+template <int n, int LC>
+__device__ __forceinline__ void outer_row_add(double (&C)[LC], double s, double x) {
+  DAsm<n>::outer(C, s, x);
+}
 // C[k] = s(lane k) * x for k < n  (a broadcast vector scaled by a lane value)
 template <int n, int LC>
 __device__ __forceinline__ void outer_row(double (&C)[LC], double s, double x) {

@@ -135,12 +135,9 @@ struct WideSchedule {
   mpc::wide::KnotDesc *d_knots = nullptr;
   mpc::wide::ProbDescW *d_probs = nullptr;
   int nknots = 0, nprobs = 0, maxN = 0;
-  // block tasks of the cyclic reduction: per level (stride 1, 2, 4, ...) the eliminated
-  // blocks (also the back-substitution's) and the absorbing blocks; one root per problem
-  std::vector<int> stride, n_odd, n_even;
-  std::vector<int64_t> at_odd, at_even;  // offsets into d_tasks
-  int64_t at_root = 0;
-  mpc::wide::CrTask *d_tasks = nullptr;
+  // chunks of the direct solve, level by level until one row per problem is left
+  std::vector<int> nchunks;
+  std::vector<mpc::wide::WChunk *> d_chunks;
   // tasks of the gang PCG: (problem, part) longest problem first, KW knots per part
   ProbDesc *d_gprobs = nullptr;
   Task *d_gtasks = nullptr;
@@ -222,7 +219,8 @@ struct mpcpcg_ctx {
   Lru<Sig, Tuned> tuned;  // horizon signature -> batched PCG schedule choice
   // generic path (nx = 28)
   bool wide = false;
-  double *w_S = nullptr, *w_Dinv = nullptr, *w_rhs = nullptr, *w_Qinv = nullptr, *w_RW = nullptr;
+  double *w_S = nullptr, *w_Dinv = nullptr, *w_rhs = nullptr, *w_rhs_prev = nullptr, *w_Qinv = nullptr;
+  double *w_dir = nullptr;  // direct solve (on first use)
   double *w_lam = nullptr;  // lambda of the factorisation path
   int *w_flag = nullptr;    // per-problem breakdown flags of the factorisation path
   float *w_P = nullptr;
@@ -884,25 +882,28 @@ int wide_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, WideSchedule *
       }
     }
   }
-  std::vector<mpc::wide::CrTask> tasks;
-  for (int s = 1; s < maxN; s *= 2) {
-    w->stride.push_back(s);
-    w->at_odd.push_back((int64_t)tasks.size());
-    for (int b = 0; b < B; ++b)
-      for (int j = s; j < pd[b].N; j += 2 * s) tasks.push_back(mpc::wide::CrTask{b, j});
-    w->n_odd.push_back((int)((int64_t)tasks.size() - w->at_odd.back()));
-    w->at_even.push_back((int64_t)tasks.size());
-    for (int b = 0; b < B; ++b)
-      if (pd[b].N > s)
-        for (int i = 0; i < pd[b].N; i += 2 * s) tasks.push_back(mpc::wide::CrTask{b, i});
-    w->n_even.push_back((int)((int64_t)tasks.size() - w->at_even.back()));
+  {
+    std::vector<mpc::wide::WChunk> rows(B);  // the problems' rows at the current level
+    for (int b = 0; b < B; ++b) rows[b] = mpc::wide::WChunk{off[b], pd[b].N, b, 0, 0};
+    for (int n = maxN; n > 1; n = (n + 3) / 4) {
+      std::vector<mpc::wide::WChunk> ch;
+      for (auto &p : rows) {
+        const int first = (int)ch.size();
+        for (int k = 0; k < p.N; k += 4) ch.push_back(mpc::wide::WChunk{p.k0, p.N, p.id, k, (int32_t)ch.size()});
+        p.k0 = first;
+        p.N = (p.N + 3) / 4;
+      }
+      w->nchunks.push_back((int)ch.size());
+      w->d_chunks.push_back(w->mem.upload(ch.data(), ch.size()));
+      if (!w->d_chunks.back()) {
+        (void)hipGetLastError();
+        return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
+      }
+    }
   }
-  w->at_root = (int64_t)tasks.size();
-  for (int b = 0; b < B; ++b) tasks.push_back(mpc::wide::CrTask{b, 0});
-  w->d_tasks = w->mem.upload(tasks.data(), tasks.size());
   w->d_knots = w->mem.upload(kd.data(), kd.size());
   w->d_probs = w->mem.upload(pd.data(), pd.size());
-  if (!w->d_tasks || !w->d_knots || !w->d_probs) {
+  if (!w->d_knots || !w->d_probs) {
     (void)hipGetLastError();
     return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
   }
@@ -916,10 +917,92 @@ mpc::wide::WArgs wide_args(mpcpcg_ctx *c, const mpcpcg_problem *p, const mpcpcg_
   std::memset(&a, 0, sizeof a);
   a.Q = p->Q; a.R = p->R; a.A = p->A; a.B = p->B;
   a.q = p->q; a.r = p->r; a.x0 = p->x0; a.e = p->e;
-  a.S = c->w_S; a.Dinv = c->w_Dinv; a.P = c->w_P; a.rhs = c->w_rhs; a.Qinv = c->w_Qinv; a.RW = c->w_RW;
+  a.S = c->w_S; a.Dinv = c->w_Dinv; a.P = c->w_P; a.rhs = c->w_rhs; a.rhs_prev = c->w_rhs_prev; a.Qinv = c->w_Qinv;
   a.lamw = c->w_lam;
   if (o) { a.eps = o->eps; a.max_iter = o->max_iter; a.warm = o->warm_start; a.stop_abs = o->stop_rule; }
   return a;
+}
+
+// Rows of level l of the 28-state direct solve: a quarter of the level before and one more per
+// problem at most (level 0: knots).
+int64_t wide_level_rows(const mpcpcg_ctx *c, int l) {
+  int64_t n = c->max_knots;
+  for (int i = 0; i < l; ++i) n = n / 4 + c->max_batch;
+  return n;
+}
+int wide_levels(int64_t nmax) {
+  int l = 0;
+  for (; nmax > 1; nmax = (nmax + 3) / 4) ++l;
+  return l;
+}
+
+// workspace of the direct solve: -W^T | H^T and z of every row that a level eliminates, the
+// systems of the levels above 0, one flag per problem (kept at 0 between solves)
+int ensure_wide_direct(mpcpcg_ctx *c) {
+  if (c->w_dir) return MPCPCG_OK;
+  const size_t MM = (size_t)kWNX * kWNX;
+  size_t n = 2;  // (a context of one knot has no levels)
+  const int levels = wide_levels(c->max_knots);
+  for (int l = 0; l <= levels; ++l) {
+    const size_t rows = (size_t)wide_level_rows(c, l);
+    if (l < levels) n += rows * (2 * MM + kWNX);
+    if (l > 0) n += rows * (3 * MM + 3 * kWNX);
+  }
+  const size_t fb = sizeof(int) * (size_t)c->max_batch;
+  if (hipMalloc(&c->w_dir, sizeof(double) * n) != hipSuccess) {
+    (void)hipGetLastError();
+    c->w_dir = nullptr;
+    return fail(c, MPCPCG_ENOMEM, "cannot allocate the factorisation workspace (%lld knots)", (long long)c->max_knots);
+  }
+  HIPCHK(c, hipMemset(c->w_flag, 0, fb));
+  HIPCHK(c, hipDeviceSynchronize());
+  return MPCPCG_OK;
+}
+
+int wide_direct(mpcpcg_ctx *c, WideSchedule *w, const mpc::wide::WArgs &a, hipStream_t s) {
+  namespace mw = mpc::wide;
+  if (int st = ensure_wide_direct(c)) return st;
+  const int64_t MM = (int64_t)kWNX * kWNX;
+  const int levels = (int)w->nchunks.size();
+  double *p = c->w_dir;
+  auto take = [&](int64_t n) { double *q = p; p += n; return q; };
+  std::vector<mw::WLevel> lev(levels + 1);
+  for (int l = 0; l <= levels; ++l) {
+    mw::WLevel &v = lev[l];
+    std::memset(&v, 0, sizeof v);
+    const int64_t rows = wide_level_rows(c, l);
+    if (l == 0) {
+      v.d0 = a.Qinv; v.s0 = MM;
+      v.d1 = a.S + MM; v.s1 = 3 * MM;
+      v.l = a.S; v.sl = 3 * MM;
+      v.y0 = a.rhs; v.y1 = a.rhs_prev; v.x = a.lamw;
+    } else {
+      v.d0 = take(rows * MM); v.d1 = take(rows * MM); v.l = take(rows * MM);
+      v.s0 = v.s1 = v.sl = MM;
+      v.y0 = take(rows * kWNX); v.y1 = take(rows * kWNX); v.x = take(rows * kWNX);
+    }
+    if (l < levels) { v.ph = take(rows * 2 * MM); v.z = take(rows * kWNX); }
+  }
+  mw::WDirect d;
+  d.flag = c->w_flag;
+  for (int l = 0; l < levels; ++l) {
+    d.chunks = w->d_chunks[l]; d.in = lev[l]; d.out = lev[l + 1];
+    if (l == 0)
+      hipLaunchKernelGGL((mw::wide_eliminate<kWNX, 2>), dim3(w->nchunks[l]), dim3(2 * 64), 0, s, d);
+    else
+      hipLaunchKernelGGL((mw::wide_eliminate<kWNX, 4>), dim3(w->nchunks[l]), dim3(4 * 64), 0, s, d);
+  }
+  const dim3 root_grid((w->nprobs + 1) / 2);
+  if (levels == 0)
+    hipLaunchKernelGGL((mw::wide_root<kWNX, true>), root_grid, dim3(64), 0, s, a, lev[0], w->d_probs, w->nprobs, c->w_flag);
+  else
+    hipLaunchKernelGGL((mw::wide_root<kWNX, false>), root_grid, dim3(64), 0, s, a, lev[levels], w->d_probs, w->nprobs, c->w_flag);
+  for (int l = levels - 1; l >= 0; --l) {
+    d.chunks = w->d_chunks[l]; d.in = lev[l]; d.out = lev[l + 1];
+    hipLaunchKernelGGL(mw::wide_back<kWNX>, dim3(w->nchunks[l]), dim3(128), 0, s, d);
+  }
+  HIPCHK(c, hipGetLastError());
+  return MPCPCG_OK;
 }
 
 // formation, preconditioner, then (unless form_only) PCG + epilogue
@@ -933,52 +1016,26 @@ int wide_run(mpcpcg_ctx *c, const std::vector<int64_t> &off, mpc::wide::WArgs &a
   a.nknots = w->nknots;
   a.nprobs = w->nprobs;
   const bool fac = !form_only && use_factor(c, off, a.warm != 0);
-  a.no_dinv = fac ? 1 : 0;
-  {
-    namespace mw = mpc::wide;
-    const dim3 blk(mw::kFormWaves * 64);
-    hipLaunchKernelGGL((mw::wide_form_inv<kWNX, kWNU>), dim3((2 * w->nknots + mw::kFormWaves - 1) / mw::kFormWaves),
-                       blk, 0, s, a);
-    hipLaunchKernelGGL((mw::wide_form_theta<kWNX, kWNU>), dim3((w->nknots + mw::kFormWaves - 1) / mw::kFormWaves),
-                       blk, 0, s, a);
-  }
-  HIPCHK(c, hipGetLastError());
+  a.direct = fac ? 1 : 0;
+  a.need_up = fac ? 0 : 1;
+  namespace mw = mpc::wide;
+  const dim3 pair_grid((w->nknots + 2 * mw::kPairWaves - 1) / (2 * mw::kPairWaves)), pair_blk(mw::kPairWaves * 64);
+  hipLaunchKernelGGL((mw::wide_form<kWNX, kWNU>), pair_grid, pair_blk, 0, s, a);
   if (!fac) {
-    hipLaunchKernelGGL((mpc::wide::wide_precond<kWNX, kWNU>), dim3(w->nknots), dim3(256), 0, s, a);
-    HIPCHK(c, hipGetLastError());
+    hipLaunchKernelGGL(mw::wide_theta<kWNX>, pair_grid, pair_blk, 0, s, a);
+    hipLaunchKernelGGL(mw::wide_precond<kWNX>, pair_grid, pair_blk, 0, s, a);
   }
+  if (form_only) hipLaunchKernelGGL(mw::wide_export<kWNX>, dim3(w->nknots), dim3(256), 0, s, a);
+  HIPCHK(c, hipGetLastError());
   if (form_only) return MPCPCG_OK;
   if (fac) {
-    // factorisation path: cyclic reduction, one launch per sub-step of a level over the
-    // tasks of every problem, then the primal step (or adjoint gradients) per knot
-    namespace mw = mpc::wide;
-    const dim3 blk(mw::kCrWaves * 64);
-    auto grid = [](int n) { return dim3((n + mw::kCrWaves - 1) / mw::kCrWaves); };
-    hipLaunchKernelGGL(mw::wide_cr_init, dim3((w->nprobs + 255) / 256), dim3(256), 0, s, c->w_flag, w->nprobs);
-    for (size_t l = 0; l < w->stride.size(); ++l) {
-      if (w->n_odd[l])
-        hipLaunchKernelGGL((mw::wide_cr_step<kWNX, mw::kCrOdd>), grid(w->n_odd[l]), blk, 0, s, a,
-                           w->d_tasks + w->at_odd[l], w->n_odd[l], w->stride[l], c->w_flag);
-      if (w->n_even[l])
-        hipLaunchKernelGGL((mw::wide_cr_step<kWNX, mw::kCrEven>), grid(w->n_even[l]), blk, 0, s, a,
-                           w->d_tasks + w->at_even[l], w->n_even[l], w->stride[l], c->w_flag);
-    }
-    hipLaunchKernelGGL((mw::wide_cr_step<kWNX, mw::kCrRoot>), grid(w->nprobs), blk, 0, s, a,
-                       w->d_tasks + w->at_root, w->nprobs, 0, c->w_flag);
-    for (size_t l = w->stride.size(); l-- > 0;)
-      if (w->n_odd[l])
-        hipLaunchKernelGGL((mw::wide_cr_step<kWNX, mw::kCrBack>), grid(w->n_odd[l]), blk, 0, s, a,
-                           w->d_tasks + w->at_odd[l], w->n_odd[l], w->stride[l], c->w_flag);
-    hipLaunchKernelGGL(mw::wide_cr_finish<kWNX>, dim3(w->nprobs), dim3(256), 0, s, a, (const int *)c->w_flag);
-    HIPCHK(c, hipGetLastError());
-    hipLaunchKernelGGL((mw::wide_epilogue<kWNX, kWNU>), dim3((w->nknots + mw::kFormWaves - 1) / mw::kFormWaves),
-                       dim3(mw::kFormWaves * 64), 0, s, a);
+    if ((st = wide_direct(c, w, a, s))) return st;
+    hipLaunchKernelGGL((mw::wide_epilogue<kWNX, kWNU>), pair_grid, pair_blk, 0, s, a);
     HIPCHK(c, hipGetLastError());
     return MPCPCG_OK;
   }
   // PCG on gangs of workgroups (every gang co-resident), then the primal step or gradients
   {
-    namespace mw = mpc::wide;
     auto fn = mw::wide_pcg_gang<kWNX, kWKnots>;
     int nb = 0;
     HIPCHK(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void *>(fn), kWKnots * 64, 0));
@@ -999,8 +1056,7 @@ int wide_run(mpcpcg_ctx *c, const std::vector<int64_t> &off, mpc::wide::WArgs &a
     }
     hipLaunchKernelGGL(fn, dim3(grid), dim3(kWKnots * 64), 0, s, a, ga);
     HIPCHK(c, hipGetLastError());
-    hipLaunchKernelGGL((mw::wide_epilogue<kWNX, kWNU>), dim3((w->nknots + mw::kFormWaves - 1) / mw::kFormWaves),
-                       dim3(mw::kFormWaves * 64), 0, s, a);
+    hipLaunchKernelGGL((mw::wide_epilogue<kWNX, kWNU>), pair_grid, pair_blk, 0, s, a);
     HIPCHK(c, hipGetLastError());
   }
   return MPCPCG_OK;
@@ -1211,10 +1267,10 @@ int mpcpcg_create(mpcpcg_ctx **out, int32_t nx, int32_t nu, int64_t max_total_kn
         hipMalloc(&c->w_Dinv, sizeof(double) * K * MM) != hipSuccess ||
         hipMalloc(&c->w_P, sizeof(float) * K * 3 * MM) != hipSuccess ||
         hipMalloc(&c->w_rhs, sizeof(double) * K * nx) != hipSuccess ||
+        hipMalloc(&c->w_rhs_prev, sizeof(double) * K * nx) != hipSuccess ||
         hipMalloc(&c->w_lam, sizeof(double) * K * nx) != hipSuccess ||
         hipMalloc(&c->w_flag, sizeof(int) * (size_t)max_batch) != hipSuccess ||
         hipMalloc(&c->w_Qinv, sizeof(double) * K * MM) != hipSuccess ||
-        hipMalloc(&c->w_RW, sizeof(double) * K * nu * (nu + nx)) != hipSuccess ||
         hipMalloc(&c->w_tws, sizeof(mpc::wide::WTag) * (size_t)wide_max_tasks(c.get())) != hipSuccess ||
         hipMalloc(&c->w_gang, sizeof(Gang) * (size_t)max_batch) != hipSuccess ||
         hipMalloc(&c->w_queue, 16 * sizeof(int)) != hipSuccess) {
@@ -1267,8 +1323,8 @@ int mpcpcg_destroy(mpcpcg_ctx *c) {
   if (c->ls_part) (void)hipFree(c->ls_part);
   if (c->cs_ws) (void)hipFree(c->cs_ws);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  for (void *p : {(void *)c->w_S, (void *)c->w_Dinv, (void *)c->w_P, (void *)c->w_rhs, (void *)c->w_lam, (void *)c->w_Qinv,
-                  (void *)c->w_RW, (void *)c->w_flag, c->w_tws, (void *)c->w_gang, (void *)c->w_queue})
+  for (void *p : {(void *)c->w_S, (void *)c->w_Dinv, (void *)c->w_P, (void *)c->w_rhs, (void *)c->w_rhs_prev, (void *)c->w_dir, (void *)c->w_lam, (void *)c->w_Qinv,
+                  (void *)c->w_flag, c->w_tws, (void *)c->w_gang, (void *)c->w_queue})
     if (p) (void)hipFree(p);
   delete c;
   return MPCPCG_OK;

@@ -1,16 +1,15 @@
-// Generic-size path (any nx <= 32, nu <= nx; built for the 28-state / 14-control shape).
+// The 28-state / 14-control path.
 //
 // The 14-state kernel keeps each knot's rows of S and Phi^-1 in registers, one 16-lane
 // DPP row per knot.  A 28-row block does not fit that mapping (a row of S is 84 FP64
-// values), so this path stages the blocks in a device workspace instead:
-//   wide_form_inv, wide_form_theta   one wave per knot (and per control): Q^-1, R^-1, the
-//                S row blocks, gamma (or the adjoint right-hand side) and D^-1, in FP64,
-//                rows in registers;
-//   wide_precond one workgroup per knot: Phi^-1 row blocks -D_b^-1 S_{b,b+-1} D_{b+-1}^-1
-//                (FP32) once every D^-1 exists (the one cross-knot dependency);
-//   wide_pcg_gang (wide_pcg.h) PCG (Algorithm 1) on gangs of workgroups, rows of S and
-//                Phi^-1 in registers; then wide_epilogue: the primal step, or in adjoint
-//                mode nu_1 and the block-sparse gradients.
+// values), so this path stages the blocks in a device workspace instead.  Every kernel but
+// the PCG gives a knot (a row of the block system) to a pair of 16-lane rows (pair_ops.h):
+//   wide_form    Q^-1, S_{b+1,b}, the shares of S's diagonal blocks and right-hand sides;
+//   for the PCG: wide_theta completes S_bb and forms D_b^-1; wide_precond forms Phi^-1 (FP32)
+//                once every D^-1 exists; wide_pcg_gang (wide_pcg.h) is PCG (Algorithm 1) on
+//                gangs of workgroups, rows of S and Phi^-1 in registers;
+//   for the direct solve: wide_eliminate per level, wide_root, wide_back per level;
+//   wide_epilogue  the primal step, or in adjoint mode nu_1 and the block-sparse gradients.
 // Precision matches the 14-state kernel: FP64 formation, S, vectors and reductions; FP32
 // Phi^-1.  Method references: S, gamma (Section III-B, sign-flipped so S is positive
 // definite), Phi^-1 (Section IV-A), PCG (Algorithm 1), dZ = -G^-1 (g - C^T lambda).
@@ -19,6 +18,7 @@
 #include <stdint.h>
 
 #include "mpcpcg.h"
+#include "pair_ops.h"
 
 namespace mpc {
 namespace wide {
@@ -47,651 +47,600 @@ struct WArgs {
   const KnotDesc *knots;
   const ProbDescW *probs;
   int32_t nknots, nprobs;
-  // workspace (FP64 unless noted)
+  // workspace (FP64 unless noted; blocks by columns, so that the lanes that own a block's rows
+  // move whole lines)
   double *S;      // [K][3][NX][NX]
   double *Dinv;   // [K][NX][NX]
   float *P;       // [K][3][NX][NX]
-  double *rhs;    // [K][NX]
+  double *rhs;    // [K][NX]; complete once wide_theta ran, before that without rhs_prev
+  double *rhs_prev;  // [K][NX] the previous knot's share of the right-hand side
   double *Qinv;   // [K][NX][NX]
-  double *RW;     // [controls][NU][NU + NX]: R^-1 rows then (R^-1 B^T) rows
   float eps;
   int32_t max_iter;
   int32_t warm;
   int32_t adjoint;
   int32_t stop_abs;   // 1: eta < eps; 0: sqrt(eta / eta_ref) < eps
-  int32_t no_dinv;    // 1: wide_form_theta skips D^-1 (only the preconditioner needs it)
-  double *lamw;       // [K][NX] lambda of the factorisation path
+  int32_t need_up;    // 1: wide_form also writes S_{b,b+1} (the PCG and the export read it)
+  int32_t direct;     // 1: wide_epilogue checks the multipliers (the PCG does it as it goes)
+  double *lamw;       // [K][NX] lambda
 };
 
-// ---------------------------------------------------------------- LDS dense helpers
-// C (m x n, ld n) = op(X) (m x k) * op(Y) (k x n); tx/ty transpose the stored operands.
-template <int NT>
-__device__ void lds_gemm(double *C, const double *X, bool tx, int ldx, const double *Y, bool ty,
-                         int ldy, int m, int k, int n, double alpha, bool accumulate) {
-  __syncthreads();
-  for (int t = threadIdx.x; t < m * n; t += NT) {
-    const int i = t / n, j = t % n;
-    double s = 0.0;
-    for (int p = 0; p < k; ++p) {
-      const double xv = tx ? X[p * ldx + i] : X[i * ldx + p];
-      const double yv = ty ? Y[j * ldy + p] : Y[p * ldy + j];
-      s = __builtin_fma(xv, yv, s);
-    }
-    C[i * n + j] = accumulate ? __builtin_fma(alpha, s, C[i * n + j]) : alpha * s;
-  }
-  __syncthreads();
-}
-
 // ---------------------------------------------------------------- formation
-// Two launches, one wave per task, lane r < n owning row r of an n x n block in registers.
-//   wide_form_inv    task t < K: knot t inverts Q_t (Gauss-Jordan in registers), writes
-//                    Q_t^-1 and S_{t,t+1} = -Q_t^-1 A_t^T, and its transpose as
-//                    S_{t+1,t} (S is symmetric, Section III-B); task K + t: control t of
-//                    knot t inverts R_t and writes (R_t^-1 | R_t^-1 B_t^T);
-//   wide_form_theta  knot b: theta_b = A_{b-1} Q_{b-1}^-1 A_{b-1}^T + B_{b-1} R_{b-1}^-1
-//                    B_{b-1}^T + Q_b^-1 = S_{b,b}, the right-hand side gamma_b (or the
-//                    adjoint's) and, for the preconditioner, D_b^-1 = theta_b^-1.
-// Each Q and R is inverted once (not once per neighbouring knot), and no step needs a
-// workgroup barrier.  Products take the left operand's row from the lane's registers and
-// the right operand's row from the wave's own LDS block, the same address for every lane
-// (a broadcast read).
-constexpr int kFormWaves = 4;
-
-__device__ __forceinline__ double lane_value(double v, int m) {  // v of lane m (m uniform)
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), m);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), m);
-  return __hiloint2double(hi, lo);
-}
-
+// wide_form: one pair of 16-lane rows per knot b (pair_ops.h; two knots per wave), each Q and
+// R inverted once and nothing exchanged between knots:
+//   Q_b^-1;  T = A_b Q_b^-1, written as S_{b+1,b} = -T and, transposed, as S_{b,b+1};
+//   theta's share A_b Q_b^-1 A_b^T + B_b R_b^-1 B_b^T of knot b + 1 (to the place of S_{b+1,b+1});
+//   gamma's (or the adjoint right-hand side's) share of b in rhs, of b + 1 in rhs_prev.
+// wide_theta completes S_bb = share + Q_b^-1 and the right-hand side and forms D_b^-1 = S_bb^-1
+// for the preconditioner; the direct solve adds the shares itself as it reads them.
+// What bounds them is FP64 issue in one chain per wave and, before the blocks were laid out by
+// columns, memory: a lane that walks its own row of 28 doubles touches one line per lane and
+// entry.  Hence whole lines everywhere, and for the row-major inputs a detour through LDS.
+// Measured on MI355X, 5,436 knots (the 32-problem two-arm batch), in us, forward:
+//   wide_form   57 (one wave per knot, pivot rows by readlane, products from LDS: 79, and 52 more
+//               for theta; one pair per knot with row-wise access at 2 waves per SIMD: 105);
+//   wide_theta  36 (with the products of theta and S before: 85); wide_precond 46 (130: one
+//               workgroup per knot, operands in LDS);
+//   wide_eliminate 109 for the knots, 25 for each of three levels above (four levels of odd-even
+//               reduction, blocks re-read on each: ~ 430); its blocks read when needed and
+//               barriers that drained the stores: 164 and 55;
+//   wide_epilogue  43 forward and 34 adjoint (56 and 69 by one wave per knot).
 // order this wave's LDS accesses: its earlier writes complete before its later reads
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
-// In-place Gauss-Jordan inverse of an SPD N x N matrix (no pivoting), rows in the lanes'
-// registers: the pivot row k is read from lane k with readlane.  `row` is the row a lane
-// holds (lane k must hold row k; other lanes may hold copies of rows, or zeros under a row
-// id >= N, and keep them consistent).  `pd` ends false if a pivot is not > 0.
-template <int N>
-__device__ __forceinline__ void reg_gj_inverse(double (&a)[N], int row, bool &pd) {
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    double pk[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) pk[j] = lane_value(a[j], k);
-    const double piv = pk[k];
-    pd = pd && (piv > 0.0);
-    const double d = 1.0 / piv;
-    // pivot row: a_kj d; other rows: a_ij - f a_kj (f = a_ik d); column k: d / -f,
-    // as c a_kj + s a_ij with (s, c) = (0, d) on the pivot lane and (1, -f) elsewhere
-    const bool me = row == k;
-    const double f = a[k] * d;
-    const double sc = me ? 0.0 : 1.0, c = me ? d : -f;
-#pragma unroll
-    for (int j = 0; j < N; ++j) a[j] = (j == k) ? c : __builtin_fma(c, pk[j], sc * a[j]);
-  }
+// a workgroup barrier for data in LDS: stores to global memory stay in flight across it
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// acc_j += sum_{m < M} x_m Y[m][j] for j < NX (Y in LDS, rows of NX)
-template <int NX, int M>
-__device__ __forceinline__ void row_times(const double (&x)[M], const double *Y, double (&acc)[NX]) {
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const double *y = Y + m * NX;
-#pragma unroll
-    for (int j = 0; j < NX; ++j) acc[j] = __builtin_fma(x[m], y[j], acc[j]);
-  }
-}
+constexpr int kPairWaves = 2;  // waves per workgroup of the pair kernels
+
+// indices of this thread's pair
+struct PairLane {
+  int lane, half, r, pr;  // lane of the 16-lane row, half, block row (clamped), pair of the wave
+  bool rowv;
+  __device__ __forceinline__ explicit PairLane(int tid)
+      : lane(tid & 15), half((tid >> 4) & 1), r(14 * ((tid >> 4) & 1) + min(tid & 15, 13)), pr((tid >> 5) & 1),
+        rowv((tid & 15) < 14) {}
+};
 
 template <int NX, int NU>
-__global__ void __launch_bounds__(kFormWaves * 64) wide_form_inv(const WArgs a) {
+__global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_form(const WArgs a) {
+  static_assert(NX == pair::kN && NU == pair::kH, "blocks of 28 and 14 rows");
   constexpr int MM = NX * NX;
-  __shared__ __attribute__((aligned(16))) double stage[kFormWaves][MM];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = blockIdx.x * kFormWaves + w;
-  if (t >= 2 * a.nknots) return;  // whole waves leave; no workgroup barrier follows
-  const bool ctrl = t >= a.nknots;
-  const KnotDesc kd = a.knots[ctrl ? t - a.nknots : t];
-  const int b = kd.b;
+  const PairLane L(threadIdx.x);
+  const int w = threadIdx.x >> 6;
+  const int t = (blockIdx.x * kPairWaves + w) * 2 + L.pr;
+  const bool live = t < a.nknots;
+  const KnotDesc kd = a.knots[live ? t : a.nknots - 1];  // (a spare pair repeats the last knot)
+  const int b = kd.b, r = L.r, lane = L.lane;
   const int64_t kb = kd.k0 + b;
   const int64_t cb = kd.k0 - kd.id + b;  // packed control row of control b
-  const bool hasNext = b + 1 < kd.N;
-  double *buf = stage[w];
-  bool pd = true;
-  if (!ctrl) {
-    const bool rowv = lane < NX;
-    const int r = rowv ? lane : 0;
-    double q[NX];
-#pragma unroll
-    for (int j = 0; j < NX; ++j) {
-      const double v = (double)a.Q[kb * MM + r * NX + j];
-      q[j] = rowv ? v : 0.0;
-    }
-    reg_gj_inverse<NX>(q, lane, pd);
-    if (rowv)
-#pragma unroll
-      for (int j = 0; j < NX; ++j) a.Qinv[kb * MM + r * NX + j] = q[j];
-    double *S = a.S + kb * 3 * MM;
-    if (b == 0 && rowv)
-#pragma unroll
-      for (int j = 0; j < NX; ++j) S[r * NX + j] = 0.0;  // no S_{0,-1}
-    double acc[NX];
-#pragma unroll
-    for (int j = 0; j < NX; ++j) acc[j] = 0.0;
-    if (hasNext) {
-      // stage A_b^T: lane j writes row j of A_b as column j
-      if (rowv)
-#pragma unroll
-        for (int m = 0; m < NX; ++m) buf[m * NX + r] = (double)a.A[cb * MM + r * NX + m];
-      wave_lds_order();
-      row_times<NX, NX>(q, buf, acc);  // (Q_b^-1 A_b^T)_r
-    }
-    if (rowv) {
-#pragma unroll
-      for (int j = 0; j < NX; ++j) S[2 * MM + r * NX + j] = -acc[j];
-      if (hasNext)
-#pragma unroll
-        for (int j = 0; j < NX; ++j) S[3 * MM + j * NX + r] = -acc[j];  // S_{b+1,b}, column r
-    }
-  } else {
-    if (!hasNext) return;
-    const bool rowv = lane < NU;
-    const int r = rowv ? lane : 0;
-    double ri[NU];
-#pragma unroll
-    for (int j = 0; j < NU; ++j) {
-      const double v = (double)a.R[cb * NU * NU + r * NU + j];
-      ri[j] = rowv ? v : 0.0;
-    }
-    reg_gj_inverse<NU>(ri, lane, pd);
-    // stage B_b^T (NU rows of NX): lane j writes row j of B_b as column j
-    if (lane < NX)
-#pragma unroll
-      for (int m = 0; m < NU; ++m) buf[m * NX + lane] = (double)a.B[cb * NX * NU + lane * NU + m];
-    wave_lds_order();
-    double wr[NX];
-#pragma unroll
-    for (int j = 0; j < NX; ++j) wr[j] = 0.0;
-    row_times<NX, NU>(ri, buf, wr);  // (R_b^-1 B_b^T)_r
-    if (rowv) {
-      double *rw = a.RW + cb * NU * (NU + NX) + r * (NU + NX);
-#pragma unroll
-      for (int j = 0; j < NU; ++j) rw[j] = ri[j];
-#pragma unroll
-      for (int j = 0; j < NX; ++j) rw[NU + j] = wr[j];
-    }
-  }
-}
-
-template <int NX, int NU>
-__global__ void __launch_bounds__(kFormWaves * 64) wide_form_theta(const WArgs a) {
-  constexpr int MM = NX * NX;
-  __shared__ __attribute__((aligned(16))) double stage[kFormWaves][2][MM];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = blockIdx.x * kFormWaves + w;
-  if (t >= a.nknots) return;
-  const KnotDesc kd = a.knots[t];
-  const int b = kd.b;
-  const int64_t kb = kd.k0 + b;
-  const int64_t cb = kd.k0 - kd.id + b;
-  const bool hasPrev = b >= 1;
+  const bool next = b + 1 < kd.N, out = live && L.rowv, outn = out && next;
   const bool adj = a.adjoint != 0;
   const float *qv = adj ? a.gx : a.q;
   const float *rv = adj ? a.gu : a.r;
-  const bool rowv = lane < NX;
-  const int r = rowv ? lane : 0;
-  double *P = stage[w][0], *W = stage[w][1];
-  double th[NX];
-  double g = 0.0;  // gamma_b, row r
-  {
-    double qi[NX];
-#pragma unroll
-    for (int j = 0; j < NX; ++j) {
-      const double v = a.Qinv[kb * MM + r * NX + j];
-      qi[j] = rowv ? v : 0.0;
-      th[j] = qi[j];
-    }
-    if (qv)
-#pragma unroll
-      for (int m = 0; m < NX; ++m) g = __builtin_fma(qi[m], (double)qv[kb * NX + m], g);
-  }
-  if (hasPrev) {
-    // P = -S_{b-1,b} = Q_{b-1}^-1 A_{b-1}^T; W = R_{b-1}^-1 B_{b-1}^T
-    const double *Sp = a.S + ((kb - 1) * 3 + 2) * MM;
-    const double *rw = a.RW + (cb - 1) * NU * (NU + NX);
-    if (rowv) {
-#pragma unroll
-      for (int m = 0; m < NX; ++m) P[m * NX + r] = -Sp[m * NX + r];
-#pragma unroll
-      for (int m = 0; m < NU; ++m) W[m * NX + r] = rw[m * (NU + NX) + NU + r];
-    }
-    double x[NX], y[NU];
-#pragma unroll
-    for (int j = 0; j < NX; ++j) {
-      const double v = (double)a.A[(cb - 1) * MM + r * NX + j];
-      x[j] = rowv ? v : 0.0;
-    }
-#pragma unroll
-    for (int j = 0; j < NU; ++j) {
-      const double v = (double)a.B[(cb - 1) * NX * NU + r * NU + j];
-      y[j] = rowv ? v : 0.0;
-    }
-    wave_lds_order();
-    // gamma_b -= (A Q^-1)_r q_{b-1} + (B R^-1)_r r_{b-1}; (A Q^-1)_{rm} = P_{mr},
-    // (B R^-1)_{rm} = W_{mr}
-    if (qv)
-#pragma unroll
-      for (int m = 0; m < NX; ++m) g = __builtin_fma(-P[m * NX + r], (double)qv[(kb - 1) * NX + m], g);
-    if (rv)
-#pragma unroll
-      for (int m = 0; m < NU; ++m) g = __builtin_fma(-W[m * NX + r], (double)rv[(cb - 1) * NU + m], g);
-    row_times<NX, NX>(x, P, th);  // + (A Q^-1 A^T)_r
-    row_times<NX, NU>(y, W, th);  // + (B R^-1 B^T)_r
-  }
-  if (rowv) {
-    double add;
-    if (adj) add = (double)a.gl[kb * NX + r];
-    else if (b == 0) add = (double)a.x0[(int64_t)kd.id * NX + r];
-    else add = a.e ? -(double)a.e[(cb - 1) * NX + r] : 0.0;
-    a.rhs[kb * NX + r] = g + add;
-    double *S1 = a.S + (kb * 3 + 1) * MM + r * NX;
-#pragma unroll
-    for (int j = 0; j < NX; ++j) S1[j] = th[j];
-  }
-  // D_b^-1 = theta_b^-1 (only the preconditioner needs it); D_0^-1 = Q_0
-  if (a.no_dinv) return;
-  double *D = a.Dinv + kb * MM + r * NX;
-  if (b == 0) {
-    if (rowv)
-#pragma unroll
-      for (int j = 0; j < NX; ++j) D[j] = (double)a.Q[kb * MM + r * NX + j];
-    return;
-  }
   bool pd = true;
-  reg_gj_inverse<NX>(th, lane, pd);
-  if (rowv)
-#pragma unroll
-    for (int j = 0; j < NX; ++j) D[j] = th[j];
-}
-
-// Phi^-1 blocks of knot b (needs D^-1 of b-1, b, b+1) and optional FP32 export of S/gamma.
-template <int NX, int NU>
-__global__ void __launch_bounds__(256) wide_precond(const WArgs a) {
-  constexpr int NT = 256;
-  constexpr int MM = NX * NX;
-  __shared__ double Db[MM], Dn[MM], Sx[MM], X[MM], Y[MM];
-  const KnotDesc kd = a.knots[blockIdx.x];
-  const int b = kd.b, N = kd.N;
-  const int64_t kb = kd.k0 + b;
-  const int tid = threadIdx.x;
-  for (int t = tid; t < MM; t += NT) Db[t] = a.Dinv[kb * MM + t];
-  float *Pb = a.P + kb * 3 * MM;
-  for (int t = tid; t < MM; t += NT) Pb[MM + t] = (float)Db[t];
-  for (int side = 0; side < 2; ++side) {
-    const bool has = side == 0 ? b >= 1 : b + 1 < N;
-    const int slot = side == 0 ? 0 : 2;
-    if (!has) {
-      for (int t = tid; t < MM; t += NT) Pb[slot * MM + t] = 0.0f;
-      continue;
-    }
-    const int64_t kn = side == 0 ? kb - 1 : kb + 1;
-    __syncthreads();
-    for (int t = tid; t < MM; t += NT) {
-      Dn[t] = a.Dinv[kn * MM + t];
-      Sx[t] = a.S[kb * 3 * MM + slot * MM + t];
-    }
-    lds_gemm<NT>(X, Db, false, NX, Sx, false, NX, NX, NX, NX, 1.0, false);
-    lds_gemm<NT>(Y, X, false, NX, Dn, false, NX, NX, NX, NX, -1.0, false);
-    for (int t = tid; t < MM; t += NT) Pb[slot * MM + t] = (float)Y[t];
-  }
-  if (a.S_out) {
-    for (int t = tid; t < 3 * MM; t += NT) {
-      a.S_out[kb * 3 * MM + t] = (float)a.S[kb * 3 * MM + t];
-      a.P_out[kb * 3 * MM + t] = Pb[t];
-    }
-    for (int t = tid; t < NX; t += NT) a.gam_out[kb * NX + t] = (float)a.rhs[kb * NX + t];
-  }
-}
-
-// ---------------------------------------------------------------- cyclic reduction
-// Block cyclic reduction of the block-tridiagonal S of every problem of a batch, the same
-// recurrences as the 14-state kernel (tri_kernel.h): with stride s the odd multiples j are
-// eliminated (V_j = D_j^-1 L_j, U_j = D_j^-1 L_{j+s}^T, z_j = D_j^-1 y_j), the even
-// multiples i absorb them (D_i -= L_i U_{i-s} + L_{i+s}^T V_{i+s}, y_i -= L_i z_{i-s} +
-// L_{i+s}^T z_{i+s}, L_i <- -L_i V_{i-s}), then x_0 = D_0^-1 y_0 and the levels are undone,
-// x_j = z_j - V_j x_{j-s} - U_j x_{j+s}.  The reduced systems are Schur complements of S,
-// so a pivot <= 0 means S is not positive definite (BREAKDOWN).
-// Work mapping: one launch per sub-step of a level, over the block tasks of all problems
-// (so a level spreads over the whole device), one wave per task, lanes r and r + 32 own
-// row r < NX in registers (each computing half of the row's product columns); the
-// launches on one stream order the levels.  The Gauss-Jordan inverse
-// takes the pivot row from its lane with readlane; a matrix product takes the left
-// operand's row from registers and the right operand's rows from the wave's own LDS
-// staging block (the same address for every lane: a broadcast read); matrix-vector
-// products broadcast the vector from its owner lanes.  A wave only ever reads LDS it
-// wrote itself, in program order.
-// Storage: S blocks (b,b-1), (b,b) hold L and D (V once the knot is eliminated), block
-// (b,b+1) is kept for the primal step; Dinv holds U, rhs holds y then z, lamw the solution.
-constexpr int kCrWaves = 8;
-
-
-// Two lanes per row: lane l holds row l & 31 (valid below NX) and computes the output
-// columns [h H, h H + H) of it, h = l >> 5; both lanes of a row hold the whole left-operand
-// row, so inverses and matrix-vector products run on full rows in both halves.
-template <int NX>
-struct WaveBlocks {
-  static_assert(NX % 2 == 0 && NX <= 32, "two lanes per row of an even NX <= 32");
-  static constexpr int H = NX / 2;  // output columns per lane
-  int lane, h, row;  // row: this lane's row (>= NX for a lane without one)
-  bool rowv;
-  int r;             // row clamped to 0 for loads (results of such lanes are never stored)
-  __device__ __forceinline__ WaveBlocks(int l)
-      : lane(l), h(l >> 5), row(l & 31), rowv((l & 31) < NX), r((l & 31) < NX ? (l & 31) : 0) {}
-  // a global block into the staging block by rows (lane (h, c) copies column c of its
-  // half of the rows: coalesced)
-  __device__ __forceinline__ void stage_rows(double *buf, const double *B) const {
-    if (rowv)
-#pragma unroll 2
-      for (int mm = 0; mm < H; ++mm) buf[(h * H + mm) * NX + r] = B[(h * H + mm) * NX + r];
-  }
-  // the transpose of a global block into the staging block (lane (h, c) writes its half
-  // of row c as its half of column c)
-  __device__ __forceinline__ void stage_cols(double *buf, const double *B) const {
-    if (rowv)
-#pragma unroll 2
-      for (int mm = 0; mm < H; ++mm) buf[(h * H + mm) * NX + r] = B[r * NX + h * H + mm];
-  }
-  // unconditional loads from the clamped row, then masked: straight-line code
-  __device__ __forceinline__ void load(const double *B, double (&o)[NX]) const {
-#pragma unroll
-    for (int j = 0; j < NX; ++j) {
-      const double v = B[r * NX + j];
-      o[j] = rowv ? v : 0.0;
-    }
-  }
-  // row r of the transpose of a global block (column r of the block)
-  __device__ __forceinline__ void load_t(const double *B, double (&o)[NX]) const {
-#pragma unroll
-    for (int j = 0; j < NX; ++j) {
-      const double v = B[j * NX + r];
-      o[j] = rowv ? v : 0.0;
-    }
-  }
-  // this lane's half of row r
-  __device__ __forceinline__ void load_half(const double *B, double (&o)[H]) const {
-#pragma unroll
-    for (int j = 0; j < H; ++j) {
-      const double v = B[r * NX + h * H + j];
-      o[j] = rowv ? v : 0.0;
-    }
-  }
-  __device__ __forceinline__ void store_half(double *B, const double (&v)[H]) const {
-    if (rowv)
-#pragma unroll
-      for (int j = 0; j < H; ++j) B[r * NX + h * H + j] = v[j];
-  }
-  // this lane's half of row r of C = X Y (rows of X in registers, Y staged)
-  __device__ __forceinline__ void mm(const double (&X)[NX], const double *Y, double (&C)[H]) const {
-#pragma unroll
-    for (int j = 0; j < H; ++j) C[j] = 0.0;
-    mm_sub_signed<1>(X, Y, C);
-  }
-  // C -= X Y on this lane's half
-  __device__ __forceinline__ void mm_sub(const double (&X)[NX], const double *Y, double (&C)[H]) const {
-    mm_sub_signed<-1>(X, Y, C);
-  }
-  template <int SIGN>
-  __device__ __forceinline__ void mm_sub_signed(const double (&X)[NX], const double *Y, double (&C)[H]) const {
-#pragma unroll
-    for (int m = 0; m < NX; ++m) {
-      const double x = SIGN > 0 ? X[m] : -X[m];
-      const double *y = Y + m * NX + h * H;
-#pragma unroll
-      for (int j = 0; j < H; ++j) C[j] = __builtin_fma(x, y[j], C[j]);
-    }
-  }
-  // (X v)_r with v distributed over the lanes (lane m < NX holds v_m)
-  __device__ __forceinline__ double mv(const double (&X)[NX], double v) const {
-    double acc = 0.0;
-#pragma unroll
-    for (int m = 0; m < NX; ++m) acc = __builtin_fma(X[m], lane_value(v, m), acc);
-    return acc;
-  }
-};
-
-// One block task of the reduction (see the recurrences above).  The stride s is the same
-// for every problem of a launch; a problem whose horizon is <= s has no task at that level.
-struct CrTask {
-  int32_t prob;  // index into WArgs::probs
-  int32_t j;     // block of the task
-};
-
-enum CrStep { kCrOdd = 0, kCrEven = 1, kCrRoot = 2, kCrBack = 3 };
-
-// One sub-step of one level for every problem of the batch: wave w of workgroup g runs
-// task g * kCrWaves + w.  `flag` is set for a problem whose reduced blocks lose positive
-// definiteness.
-template <int NX, int STEP>
-__global__ void __launch_bounds__(kCrWaves * 64) wide_cr_step(const WArgs a, const CrTask *tasks, int ntasks,
-                                                                int s, int *flag) {
-  constexpr int MM = NX * NX;
-  // staged right operands: the elimination loads both of its own before the inverse so
-  // that their global round trips overlap it (at its register count one workgroup fills a
-  // CU, so the LDS is there); the other sub-steps stage one block at a time
-  constexpr int kBufs = STEP == kCrOdd ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) double stage[kCrWaves][kBufs][MM];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int t = blockIdx.x * kCrWaves + w;
-  if (t >= ntasks) return;  // whole waves leave; no workgroup barrier follows
-  const CrTask tk = tasks[t];
-  const ProbDescW pd = a.probs[tk.prob];
-  const int N = pd.N, j = tk.j;
-  const int64_t k0 = pd.k0;
-  const WaveBlocks<NX> W(lane);
-  double *b0 = stage[w][0], *b1 = stage[w][kBufs - 1];
-  auto blk = [&](int k, int t2) { return a.S + ((k0 + k) * 3 + t2) * MM; };
-  auto ublk = [&](int k) { return a.Dinv + (k0 + k) * MM; };
-  auto vld = [&](const double *v, int k) {
-    const double x = v[(k0 + k) * NX + W.r];
-    return W.rowv ? x : 0.0;
-  };
-  bool ok = true;
-  constexpr int H = WaveBlocks<NX>::H;
-  const bool out = W.rowv && W.h == 0;  // one writer per row of a vector
-  if constexpr (STEP == kCrOdd) {  // eliminate j = s(2m+1)
-    const bool up = j + s < N;
-    W.stage_rows(b0, blk(j, 0));             // L_j
-    if (up) W.stage_cols(b1, blk(j + s, 0)); // L_{j+s}^T
-    double D[NX], C[H];
-    W.load(blk(j, 1), D);
-    const double y = vld(a.rhs, j);
-    reg_gj_inverse<NX>(D, W.row, ok);        // D_j^-1, rows in D
-    const double z = W.mv(D, y);
-    wave_lds_order();
-    W.mm(D, b0, C);                          // V_j
-    W.store_half(blk(j, 1), C);              // over D_j (read above)
-    if (up) {
-      W.mm(D, b1, C);                        // U_j
-      W.store_half(ublk(j), C);
-    }
-    if (out) a.rhs[(k0 + j) * NX + W.r] = z;
-  } else if constexpr (STEP == kCrEven) {  // i = 2sm absorbs i - s and i + s
-    const int i = j;
-    double D[H], X[NX];
-    double y = vld(a.rhs, i);
-    if (i >= s) {
-      double C[H];
-      W.load(blk(i, 0), X);                  // L_i
-      y -= W.mv(X, vld(a.rhs, i - s));
-      W.stage_rows(b0, blk(i - s, 1));       // V_{i-s}
-      wave_lds_order();
-      W.mm(X, b0, C);
-#pragma unroll
-      for (int c = 0; c < H; ++c) C[c] = -C[c];
-      W.store_half(blk(i, 0), C);            // coupling to i - 2s (L_i is in X)
-      wave_lds_order();
-      W.stage_rows(b0, ublk(i - s));         // U_{i-s}
-      W.load_half(blk(i, 1), D);
-      wave_lds_order();
-      W.mm_sub(X, b0, D);                    // D_i -= L_i U_{i-s}
-    } else {
-      W.load_half(blk(i, 1), D);
-    }
-    if (i + s < N) {
-      W.load_t(blk(i + s, 0), X);            // L_{i+s}^T
-      y -= W.mv(X, vld(a.rhs, i + s));
-      wave_lds_order();
-      W.stage_rows(b0, blk(i + s, 1));       // V_{i+s}
-      wave_lds_order();
-      W.mm_sub(X, b0, D);                    // D_i -= L_{i+s}^T V_{i+s}
-    }
-    W.store_half(blk(i, 1), D);
-    if (out) a.rhs[(k0 + i) * NX + W.r] = y;
-  } else if constexpr (STEP == kCrRoot) {  // x_0 = D_0^-1 y_0
-    double D[NX];
-    W.load(blk(0, 1), D);
-    reg_gj_inverse<NX>(D, W.row, ok);
-    const double x = W.mv(D, vld(a.rhs, 0));
-    if (out) a.lamw[k0 * NX + W.r] = x;
-  } else {  // x_j = z_j - V_j x_{j-s} - U_j x_{j+s}
-    double T[NX];
-    W.load(blk(j, 1), T);
-    double x = vld(a.rhs, j) - W.mv(T, vld(a.lamw, j - s));
-    if (j + s < N) {
-      W.load(ublk(j), T);
-      x -= W.mv(T, vld(a.lamw, j + s));
-    }
-    if (out) a.lamw[(k0 + j) * NX + W.r] = x;
-  }
-  if (!ok && lane == 0) flag[tk.prob] = 1;  // every writer stores the same value
-}
-
-// Clears the breakdown flags before the first level (a kernel, so the sequence can be
-// captured in a graph).
-__global__ void wide_cr_init(int *flag, int nprobs) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < nprobs) flag[p] = 0;
-}
-
-// Stats of every problem: BREAKDOWN on a non-positive pivot or a non-finite solution.
-template <int NX>
-__global__ void __launch_bounds__(256) wide_cr_finish(const WArgs a, const int *flag) {
-  const ProbDescW pd = a.probs[blockIdx.x];
-  bool fin = true;
-  for (int t = threadIdx.x; t < pd.N * NX; t += 256) {
-    const double v = a.lamw[pd.k0 * NX + t];
-    fin = fin && (v == v) && !__builtin_isinf(v);
-  }
-  const bool bad = __syncthreads_or(!fin) || flag[blockIdx.x] != 0;
-  if (threadIdx.x == 0) {
-    mpcpcg_stats st;
-    st.iters = 0;
-    st.status = bad ? MPCPCG_BREAKDOWN : MPCPCG_OK;
-    st.final_ratio = 0.0f;
-    st.reserved = 0;
-    a.stats[pd.id] = st;
-  }
-}
-
-
-// ---------------------------------------------------------------- factorisation epilogue
-// The primal step of every knot from the multipliers lamw (dZ = -G^-1 (g - C^T lambda)),
-// or in adjoint mode nu_1 and the block-sparse gradients (the same expressions as the
-// PCG kernel's epilogue).  One wave per knot b; lane r < NX owns row r of the knot's
-// state block and lane r < NU row r of control b, which couples to lambda_{b+1}:
-//   x_b = -Q_b^-1 (q_b - lambda_b) + S_{b,b+1} lambda_{b+1}
-//   u_b = -R_b^-1 r_b - (R_b^-1 B_b^T) lambda_{b+1}
-template <int NX, int NU>
-__global__ void __launch_bounds__(kFormWaves * 64) wide_epilogue(const WArgs a) {
-  constexpr int MM = NX * NX;
-  __shared__ double vx[kFormWaves][NX], vu[kFormWaves][NU];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = blockIdx.x * kFormWaves + w;
-  if (t >= a.nknots) return;  // whole waves leave; no workgroup barrier follows
-  const KnotDesc kd = a.knots[t];
-  const int b = kd.b;
-  const int64_t kb = kd.k0 + b;
-  const int64_t cb = kd.k0 - kd.id + b;  // control b
-  const bool hasNext = b + 1 < kd.N;
-  const bool adj = a.adjoint != 0;
-  const float *qv = adj ? a.gx : a.q;
-  const float *rv = adj ? a.gu : a.r;
-  const double *lam = a.lamw;  // lambda, or mu in adjoint mode
-  const bool rowv = lane < NX, urow = lane < NU && hasNext;
-  const int r = rowv ? lane : 0, ru = lane < NU ? lane : 0;
-  double x = 0.0, u = 0.0;
+  double Qi[NX], v;
+  // the input blocks arrive as they lie in memory, whole lines, and turn into rows through LDS
+  constexpr int EM = (MM + 31) / 32, ER = (NU * NU + 31) / 32, EB = (NX * NU + 31) / 32;
+  __shared__ __attribute__((aligned(16))) float stage[kPairWaves * 2][2][MM];
+  float *s0 = stage[w * 2 + L.pr][0], *s1 = stage[w * 2 + L.pr][1];
+  const int me = threadIdx.x & 31;
+  float rv_[ER], bv_[EB];
   {
-    const double *Qi = a.Qinv + kb * MM + r * NX;
-    const double *Sp = a.S + (kb * 3 + 2) * MM + r * NX;
-#pragma unroll 4
-    for (int j = 0; j < NX; ++j) {
-      const double qj = qv ? (double)qv[kb * NX + j] : 0.0;
-      const double ln = hasNext ? lam[(kb + 1) * NX + j] : 0.0;
-      x = __builtin_fma(-Qi[j], qj - lam[kb * NX + j], x);
-      x = __builtin_fma(Sp[j], ln, x);
-    }
-  }
-  if (hasNext) {
-    const double *rw = a.RW + cb * NU * (NU + NX) + ru * (NU + NX);
+    float q[EM], f[EM];
 #pragma unroll
-    for (int m = 0; m < NU; ++m) u -= rw[m] * (rv ? (double)rv[cb * NU + m] : 0.0);
-#pragma unroll 4
-    for (int j = 0; j < NX; ++j) u -= rw[NU + j] * lam[(kb + 1) * NX + j];
-  }
-  const double mu = rowv ? lam[kb * NX + r] : 0.0;
-  if (!adj) {
-    if (rowv) {
-      a.lam[kb * NX + r] = (float)mu;
-      a.dx[kb * NX + r] = (float)x;
+    for (int j = 0; j < EM; ++j) {
+      const int e = j * 32 + me;
+      q[j] = e < MM ? a.Q[kb * MM + e] : 0.0f;
+      f[j] = next && e < MM ? a.A[cb * MM + e] : 0.0f;
     }
-    if (urow) a.du[cb * NU + lane] = (float)u;
-    return;
-  }
-  // adjoint: lam holds mu, x = nu_1 of the state rows, u = nu_1 of the control rows
-  if (rowv) {
-    if (a.dgamma) a.dgamma[kb * NX + r] = (float)mu;
-    a.dq[kb * NX + r] = (float)x;
-    if (b == 0) a.dx0[(int64_t)kd.id * NX + r] = (float)mu;
-    if (b >= 1 && a.de) a.de[(cb - 1) * NX + r] = (float)(-mu);
-    vx[w][r] = x;
-  }
-  if (urow) {
-    a.dr[cb * NU + lane] = (float)u;
-    vu[w][lane] = u;
+#pragma unroll
+    for (int j = 0; j < ER; ++j) rv_[j] = next && j * 32 + me < NU * NU ? a.R[cb * NU * NU + j * 32 + me] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < EB; ++j) bv_[j] = next && j * 32 + me < NX * NU ? a.B[cb * NX * NU + j * 32 + me] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < EM; ++j)
+      if (j * 32 + me < MM) {
+        s0[j * 32 + me] = q[j];
+        s1[j * 32 + me] = f[j];
+      }
   }
   wave_lds_order();
+  {
+    double Q[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      Q[j] = (double)s0[r * NX + j];
+      Qi[j] = j == r ? 1.0 : 0.0;
+    }
+    wave_lds_order();  // every row of Q has been read: R and B take its place
+#pragma unroll
+    for (int j = 0; j < ER; ++j)
+      if (j * 32 + me < NU * NU) s0[j * 32 + me] = rv_[j];
+#pragma unroll
+    for (int j = 0; j < EB; ++j)
+      if (j * 32 + me < NX * NU) s0[NU * NU + j * 32 + me] = bv_[j];
+    pair::gj_solve<NX>(Q, Qi, lane, L.half, pd);
+  }
+  if (out)
+#pragma unroll
+    for (int j = 0; j < NX; ++j) a.Qinv[kb * MM + j * NX + r] = Qi[j];
+  v = pair::row_dot(Qi, qv ? (double)qv[kb * NX + r] : 0.0);
+  double add;
+  if (adj) add = (double)a.gl[kb * NX + r];
+  else if (b == 0) add = (double)a.x0[(int64_t)kd.id * NX + r];
+  else add = a.e ? -(double)a.e[(cb - 1) * NX + r] : 0.0;
+  if (out) {
+    a.rhs[kb * NX + r] = v + add;
+    double *S = a.S + kb * 3 * MM;
+    if (b == 0) {  // no S_{0,-1} and no share of a previous knot
+#pragma unroll
+      for (int j = 0; j < NX; ++j) { S[j * NX + r] = 0.0; S[MM + j * NX + r] = 0.0; }
+      a.rhs_prev[kb * NX + r] = 0.0;
+    }
+    if (!next)
+#pragma unroll
+      for (int j = 0; j < NX; ++j) S[2 * MM + j * NX + r] = 0.0;
+  }
+  if (!__any(next)) return;
+  double (&T)[NX] = Qi, G[NX], p1;  // T replaces Q^-1 column by column
+  wave_lds_order();
+  {
+    double A[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) A[j] = (double)s1[r * NX + j];
+    p1 = -pair::row_dot(A, v);
+    pair::mm_inplace<NX>(A, T);
+  }
+#pragma unroll
+  for (int j = 0; j < NX; ++j) G[j] = 0.0;
+  pair::mm_nt_lds<NX>(T, s1, G);
+  if (outn) {
+    double *S0 = a.S + (kb + 1) * 3 * MM + r, *S2 = a.S + (kb * 3 + 2) * MM + r * NX;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      S0[j * NX] = -T[j];
+      if (a.need_up) S2[j] = -T[j];
+    }
+  }
+  {
+    // the control: both halves hold R^-1, each its rows of B
+    double R[NU], B[NU], U[NU];
+    const int ru = min(lane, NU - 1);
+#pragma unroll
+    for (int j = 0; j < NU; ++j) {
+      R[j] = next ? (double)s0[ru * NU + j] : (j == ru ? 1.0 : 0.0);
+      B[j] = (double)s0[NU * NU + r * NU + j];
+    }
+    gj_inverse<NU>(R, lane, &pd);
+    mm_nn<NU, NU>(B, R, U);
+    pair::mm_nt_add<NU>(U, B, G);
+    p1 -= mpc::row_dot<NU>(U, next && rv ? (double)rv[cb * NU + ru] : 0.0);
+  }
+  if (outn) {
+    double *S1 = a.S + ((kb + 1) * 3 + 1) * MM + r;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) S1[j * NX] = G[j];
+    a.rhs_prev[(kb + 1) * NX + r] = p1;
+  }
+}
+
+// S_bb, the right-hand side and D_b^-1 of knot b from the shares (D_0^-1 = S_00^-1 = Q_0 up to
+// rounding, like every other knot).
+template <int NX>
+__global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_theta(const WArgs a) {
+  constexpr int MM = NX * NX;
+  const PairLane L(threadIdx.x);
+  const int t = (blockIdx.x * kPairWaves + (threadIdx.x >> 6)) * 2 + L.pr;
+  const bool live = t < a.nknots;
+  const KnotDesc kd = a.knots[live ? t : a.nknots - 1];
+  const int64_t kb = kd.k0 + kd.b;
+  const int r = L.r;
+  double *S1 = a.S + (kb * 3 + 1) * MM + r;
+  double D[NX], I[NX];
+  bool pd = true;
+#pragma unroll
+  for (int j = 0; j < NX; ++j) {
+    D[j] = S1[j * NX] + a.Qinv[kb * MM + j * NX + r];
+    I[j] = j == r ? 1.0 : 0.0;
+  }
+  const double y = a.rhs[kb * NX + r] + a.rhs_prev[kb * NX + r];
+  if (live && L.rowv) {
+    a.rhs[kb * NX + r] = y;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) S1[j * NX] = D[j];
+  }
+  pair::gj_solve<NX>(D, I, L.lane, L.half, pd);
+  if (live && L.rowv)
+#pragma unroll
+    for (int j = 0; j < NX; ++j) a.Dinv[kb * MM + j * NX + r] = I[j];
+}
+
+// Phi^-1 blocks, one pair per knot b (needs D^-1 of b and b + 1): D_b^-1 itself, and
+// -D_{b+1}^-1 S_{b+1,b} D_b^-1, which is Phi^-1_{b+1,b} and, transposed, Phi^-1_{b,b+1}.
+template <int NX>
+__global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_precond(const WArgs a) {
+  constexpr int MM = NX * NX;
+  const PairLane L(threadIdx.x);
+  const int t = (blockIdx.x * kPairWaves + (threadIdx.x >> 6)) * 2 + L.pr;
+  const bool live = t < a.nknots;
+  const KnotDesc kd = a.knots[live ? t : a.nknots - 1];
+  const int64_t kb = kd.k0 + kd.b;
+  const int r = L.r;
+  const bool out = live && L.rowv, next = kd.b + 1 < kd.N;
+  float *P = a.P + kb * 3 * MM + r;
+  double D[NX], Y[NX];
+#pragma unroll
+  for (int j = 0; j < NX; ++j) D[j] = a.Dinv[kb * MM + j * NX + r];
+  if (out) {
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      P[MM + j * NX] = (float)D[j];
+      if (kd.b == 0) P[j * NX] = 0.0f;
+      if (!next) P[2 * MM + j * NX] = 0.0f;
+    }
+  }
+  if (!__any(next)) return;
+  const int64_t kn = next ? kb + 1 : kb;
+#pragma unroll
+  for (int j = 0; j < NX; ++j) Y[j] = a.S[kn * 3 * MM + j * NX + r];  // S_{b+1,b}
+  pair::mm_inplace<NX>(Y, D);
+#pragma unroll
+  for (int j = 0; j < NX; ++j) Y[j] = -a.Dinv[kn * MM + j * NX + r];
+  pair::mm_inplace<NX>(Y, D);
+  if (out && next) {
+    float *Pn = a.P + kn * 3 * MM + r, *Pu = a.P + (kb * 3 + 2) * MM + r * NX;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      Pn[j * NX] = (float)D[j];
+      Pu[j] = (float)D[j];
+    }
+  }
+}
+
+// S, Phi^-1 and gamma of one problem as the caller's row-major FP32 arrays.
+template <int NX>
+__global__ void __launch_bounds__(256) wide_export(const WArgs a) {
+  constexpr int MM = NX * NX;
+  const int64_t kb = a.knots[blockIdx.x].k0 + a.knots[blockIdx.x].b;
+  for (int t = threadIdx.x; t < 3 * MM; t += 256) {
+    const int64_t in = (kb * 3 + t / MM) * MM + (t % NX) * NX + t % MM / NX;
+    a.S_out[kb * 3 * MM + t] = (float)a.S[in];
+    a.P_out[kb * 3 * MM + t] = a.P[in];
+  }
+  if (threadIdx.x < NX) a.gam_out[kb * NX + threadIdx.x] = (float)a.rhs[kb * NX + threadIdx.x];
+}
+
+// ---------------------------------------------------------------- direct solve
+// The 14-state path's chunked elimination (tri_kernel.h has the recurrences) on 28-row blocks,
+// four rows of a level to one until one is left per problem: level 0 are the knots, level
+// l > 0 the separators of level l - 1.
+//   wide_eliminate  one workgroup per chunk: it eliminates rows 1 .. 3 one after the other.  A
+//       pair of 16-lane rows solves with D_k for W columns of T'_k^T or of F_k (and y_k), so
+//       every pair repeats the elimination of D_k itself and the columns are spread over the
+//       workgroup's 4 kWaves 16-lane rows;
+//   wide_root       the last separator of every problem, x_0 = D_0^-1 y_0, and its stats;
+//   wide_back       the inner rows of a level from the next level's solution.
+struct WChunk {
+  int64_t k0;    // first row of the problem at this level
+  int32_t N;     // rows of the problem
+  int32_t id;    // problem
+  int32_t b0;    // first row of the chunk, its separator
+  int32_t sep;   // the separator's row at the next level
+};
+
+// The system at one level: diagonal block (two shares), coupling to the previous row,
+// right-hand side (two shares), solution; blocks by columns.
+struct WLevel {
+  double *d0, *d1, *l, *y0, *y1, *x;
+  int64_t s0, s1, sl;  // doubles from one row's block to the next
+  double *ph, *z;      // what this level's elimination leaves: -W^T | H^T by columns, z
+};
+
+struct WDirect {
+  const WChunk *chunks;
+  WLevel in, out;
+  int32_t *flag;
+};
+
+template <int NX, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) wide_eliminate(const WDirect a) {
+  constexpr int MM = NX * NX, W = NX / WAVES, LD = NX + 2;
+  static_assert(NX == pair::kN && W % 7 == 0, "columns in blocks of seven");
+  // by columns: D_1 .. D_3 (each takes the previous step's correction), and the couplings of
+  // rows 1 .. 4 to their previous rows; the first of these becomes F_2, F_3
+  __shared__ double Dk[3][NX][LD], Lk[4][NX][LD];
+  double (&F)[NX][LD] = Lk[0];
+  const PairLane L(threadIdx.x);
+  const int slot = (threadIdx.x >> 6) * 2 + L.pr;
+  const bool isF = slot >= WAVES;
+  const int c0 = (isF ? slot - WAVES : slot) * W;
+  const int lane = L.lane, half = L.half, r = L.r;
+  const bool rowv = L.rowv;
+  const WChunk C = a.chunks[blockIdx.x];
+  const int N = C.N;
+  bool pd = true;
+  double Ds[W], yk[4], yc = 0.0;  // the F slots' columns of the separator's diagonal block; y_0 .. y_3
+  {
+    const int64_t k0 = C.k0 + C.b0;
+    constexpr int per = (MM / 2 + WAVES * 64 - 1) / (WAVES * 64);
+    double2 d0[3][per], d1[3][per], l[4][per];
+    const int left = N - C.b0;
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+      const int e = q * WAVES * 64 + threadIdx.x;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const bool on = e < MM / 2 && m + 1 < left;
+        if (m < 3) {
+          d0[m][q] = on ? reinterpret_cast<const double2 *>(a.in.d0 + (k0 + 1 + m) * a.in.s0)[e] : double2{0.0, 0.0};
+          d1[m][q] = on ? reinterpret_cast<const double2 *>(a.in.d1 + (k0 + 1 + m) * a.in.s1)[e] : double2{0.0, 0.0};
+        }
+        l[m][q] = on ? reinterpret_cast<const double2 *>(a.in.l + (k0 + 1 + m) * a.in.sl)[e] : double2{0.0, 0.0};
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) yk[m] = m < left ? a.in.y0[(k0 + m) * NX + r] + a.in.y1[(k0 + m) * NX + r] : 0.0;
+#pragma unroll
+    for (int c = 0; c < W; ++c)
+      Ds[c] = a.in.d0[k0 * a.in.s0 + r + (c0 + c) * NX] + a.in.d1[k0 * a.in.s1 + r + (c0 + c) * NX];
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+      const int e = q * WAVES * 64 + threadIdx.x, at = e / (NX / 2) * LD + e % (NX / 2) * 2;
+      if (e < MM / 2)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          if (m < 3)
+            *reinterpret_cast<double2 *>(&Dk[m][0][0] + at) = double2{d0[m][q].x + d1[m][q].x, d0[m][q].y + d1[m][q].y};
+          *reinterpret_cast<double2 *>(&Lk[m][0][0] + at) = l[m][q];
+        }
+    }
+  }
+  double ys = yk[0], O[W];
+  lds_barrier();
+#pragma unroll 1
+  for (int k = 1; k < 4; ++k) {
+    const int i = C.b0 + k;
+    if (i >= N) break;  // (the same for the whole workgroup)
+    double b[W + 1];
+    {
+      double D[NX];
+#pragma unroll
+      for (int j = 0; j < NX; ++j) D[j] = Dk[k - 1][j][r];
+#pragma unroll
+      for (int c = 0; c < W; ++c) b[c] = isF ? F[c0 + c][r] : Lk[k][r][c0 + c];
+      b[W] = yk[1] + yc;
+      yk[1] = yk[2];
+      yk[2] = yk[3];
+      pair::gj_solve<W + 1>(D, b, lane, half, pd);       // -W^T or H^T columns, and z
+    }
+    const double z = b[W];
+    if (rowv) {
+      double *o = a.in.ph + (C.k0 + i) * 2 * MM + (isF ? MM : 0) + c0 * NX + r;
+#pragma unroll
+      for (int c = 0; c < W; ++c) o[c * NX] = b[c];
+      if (slot == 0) a.in.z[(C.k0 + i) * NX + r] = z;
+    }
+    double X[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) X[j] = -F[r][j];        // -(F_k^T)
+    if (isF) pair::mm_add<W>(X, b, Ds);
+    ys += pair::row_dot(X, z);
+#pragma unroll
+    for (int j = 0; j < NX; ++j) X[j] = -Lk[k][j][r];
+#pragma unroll
+    for (int c = 0; c < W; ++c) O[c] = 0.0;
+    pair::mm_add<W>(X, b, O);                            // D_{k+1}'s correction, or F_{k+1}
+    yc = pair::row_dot(X, z);
+    if (k == 3) break;
+    lds_barrier();
+    if (rowv)
+#pragma unroll
+      for (int c = 0; c < W; ++c) {
+        if (isF)
+          F[c0 + c][r] = O[c];
+        else
+          Dk[k][c0 + c][r] += O[c];
+      }
+    lds_barrier();
+  }
+  const int64_t s = C.sep;
+  if (rowv) {
+    if (isF)
+#pragma unroll
+      for (int c = 0; c < W; ++c) a.out.d0[s * MM + (c0 + c) * NX + r] = Ds[c];
+    if (slot == 0) a.out.y0[s * NX + r] = ys;
+    if (C.b0 == 0) {  // a problem's first separator has no share from a previous chunk
+      if (!isF)
+#pragma unroll
+        for (int c = 0; c < W; ++c) a.out.d1[s * MM + (c0 + c) * NX + r] = 0.0;
+      if (slot == 0) a.out.y1[s * NX + r] = 0.0;
+    }
+    if (C.b0 + 4 < N) {
+#pragma unroll
+      for (int c = 0; c < W; ++c) {
+        if (isF)
+          a.out.l[(s + 1) * MM + (c0 + c) * NX + r] = O[c];
+        else
+          a.out.d1[(s + 1) * MM + (c0 + c) * NX + r] = O[c];
+      }
+      if (slot == 0) a.out.y1[(s + 1) * NX + r] = yc;
+    }
+  }
+  if (!pd) a.flag[C.id] = 1;  // every writer stores the same value
+}
+
+// The last row of problem p: x = D^-1 y, the stats, and the breakdown flag cleared for the next
+// solve (wide_epilogue turns a non-finite multiplier into BREAKDOWN as well).
+template <int NX, bool KNOTS>
+__global__ void __launch_bounds__(64) wide_root(const WArgs a, const WLevel v, const ProbDescW *probs, int nprobs, int32_t *flag) {
+  const PairLane L(threadIdx.x);
+  const int p = blockIdx.x * 2 + L.pr;
+  const bool live = p < nprobs;
+  const int q = live ? p : nprobs - 1;
+  const ProbDescW P = probs[q];
+  const int64_t k = KNOTS ? P.k0 : q;  // level 0: the problem's only knot; above, separator p
+  double D[NX], y[1];
+  bool pd = true;
+#pragma unroll
+  for (int j = 0; j < NX; ++j) D[j] = v.d0[k * v.s0 + L.r + j * NX] + v.d1[k * v.s1 + L.r + j * NX];
+  y[0] = v.y0[k * NX + L.r] + v.y1[k * NX + L.r];
+  pair::gj_solve<1>(D, y, L.lane, L.half, pd);
+  if (live && L.rowv) v.x[k * NX + L.r] = y[0];
+  const unsigned long long bad = __ballot(!pd) >> (32 * L.pr) & 0xffffffffull;
+  if (live && (threadIdx.x & 31) == 0) {
+    mpcpcg_stats st;
+    st.iters = 0;
+    st.status = bad || flag[P.id] ? MPCPCG_BREAKDOWN : MPCPCG_OK;
+    st.final_ratio = 0.0f;
+    st.reserved = 0;
+    a.stats[P.id] = st;
+    flag[P.id] = 0;
+  }
+}
+
+// One workgroup per chunk, one pair per row: z - H^T x_sep at once, then the chain
+// x_i = z_i - H_i^T x_sep + W_i^T x_{i+1} down the rows through LDS.
+template <int NX>
+__global__ void __launch_bounds__(128) wide_back(const WDirect a) {
+  constexpr int MM = NX * NX;
+  __shared__ double xs[5][32];
+  const PairLane L(threadIdx.x);
+  const int t = (threadIdx.x >> 6) * 2 + L.pr, r = L.r, me = threadIdx.x & 31;
+  const WChunk C = a.chunks[blockIdx.x];
+  const int i = C.b0 + t;
+  const int64_t s = C.sep;
+  const double xl = a.out.x[s * NX + r];
+  double P[NX], u = t == 0 ? xl : 0.0;
+  const bool inner = t > 0 && i < C.N;
+  const double *ph = a.in.ph + (C.k0 + (inner ? i : 0)) * 2 * MM + r;
+#pragma unroll
+  for (int j = 0; j < NX; ++j) P[j] = inner ? ph[MM + j * NX] : 0.0;
+  if (inner) u = a.in.z[(C.k0 + i) * NX + r];
+  u -= pair::row_dot(P, xl);
+#pragma unroll
+  for (int j = 0; j < NX; ++j) P[j] = inner ? ph[j * NX] : 0.0;
+  if (t == 0) xs[4][me] = C.b0 + 4 < C.N ? a.out.x[(s + 1) * NX + r] : 0.0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 3; q >= 0; --q) {
+    const double x = u - pair::row_dot(P, xs[t + 1][me]);
+    if (t == q) xs[t][me] = x;
+    __syncthreads();
+  }
+  if (i < C.N && L.rowv) a.in.x[(C.k0 + i) * NX + r] = xs[t][me];
+}
+
+// ---------------------------------------------------------------- primal step, gradients
+// One pair per knot b, from the multipliers lamw (lambda, or mu in adjoint mode):
+//   x_b = Q_b^-1 (lambda_b - q_b - A_b^T lambda_{b+1}),  u_b = -R_b^-1 (r_b + B_b^T lambda_{b+1})
+// and in adjoint mode, with (x, u) = nu_1, the block-sparse gradients.  Matrices are read and
+// written by columns of row-major arrays: lane r takes column r, consecutive addresses.
+template <int NX, int NU>
+__global__ void __launch_bounds__(kPairWaves * 64) wide_epilogue(const WArgs a) {
+  constexpr int MM = NX * NX;
+  const PairLane L(threadIdx.x);
+  const int t = (blockIdx.x * kPairWaves + (threadIdx.x >> 6)) * 2 + L.pr;
+  const bool live = t < a.nknots;
+  const KnotDesc kd = a.knots[live ? t : a.nknots - 1];
+  const int b = kd.b, r = L.r, lane = L.lane;
+  const int64_t kb = kd.k0 + b;
+  const int64_t cb = kd.k0 - kd.id + b;  // control b
+  const bool next = b + 1 < kd.N, out = live && L.rowv, outn = out && next;
+  const bool adj = a.adjoint != 0;
+  const float *qv = adj ? a.gx : a.q;
+  const float *rv = adj ? a.gu : a.r;
+  const double lam = a.lamw[kb * NX + r], ln = next ? a.lamw[(kb + 1) * NX + r] : 0.0;
+  if (a.direct && out && !(lam - lam == 0.0))  // infinite or not a number
+    reinterpret_cast<int *>(a.stats + kd.id)[1] = MPCPCG_BREAKDOWN;
+  double x, u;
+  {
+    double M[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) M[j] = next ? (double)a.A[cb * MM + j * NX + r] : 0.0;
+    const double w = lam - (qv ? (double)qv[kb * NX + r] : 0.0) - pair::row_dot(M, ln);
+#pragma unroll
+    for (int j = 0; j < NX; ++j) M[j] = a.Qinv[kb * MM + j * NX + r];
+    x = pair::row_dot(M, w);
+  }
+  const int c = min(lane, NU - 1);  // control row / column of this lane, the same in both halves
+  {
+    double M[NX], R[NU];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) M[j] = next ? (double)a.B[cb * NX * NU + j * NU + c] : 0.0;
+#pragma unroll
+    for (int j = 0; j < NU; ++j) R[j] = next ? (double)a.R[cb * NU * NU + c * NU + j] : (j == c ? 1.0 : 0.0);
+    u = -((next && rv ? (double)rv[cb * NU + c] : 0.0) + pair::row_dot(M, ln));
+    gj_solve<NU>(R, u, lane);
+  }
+  const bool outu = live && next && lane < NU && L.half == 0;
+  if (!adj) {
+    if (out) {
+      a.lam[kb * NX + r] = (float)lam;
+      a.dx[kb * NX + r] = (float)x;
+    }
+    if (outu) a.du[cb * NU + lane] = (float)u;
+    return;
+  }
+  if (out) {
+    if (a.dgamma) a.dgamma[kb * NX + r] = (float)lam;
+    a.dq[kb * NX + r] = (float)x;
+    if (b == 0) a.dx0[(int64_t)kd.id * NX + r] = (float)lam;
+  }
+  if (outu) a.dr[cb * NU + lane] = (float)u;
+  if (outn && a.de) a.de[cb * NX + r] = (float)(-ln);
+  const double dx = (double)a.dx_in[kb * NX + r];
+  // rows 14 h .. 14 h + 13 of column r, the row vector's halves on every lane of the pair
+  auto half_rows = [&](double s0, double v0, double s1, double v1, double (&C)[NU], int h) {
+    double lo, hi;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) C[k] = 0.0;
+    pair::dup(s0, lo, hi);
+    outer_row_add<NU>(C, h ? hi : lo, v0);
+    pair::dup(s1, lo, hi);
+    outer_row_add<NU>(C, h ? hi : lo, v1);
+  };
+  double C[NU];
   // dQ_b = sym(nu1x_b dx_b^T)
-  const float *dxb = a.dx_in + kb * NX;
-  for (int o = lane; o < MM; o += 64) {
-    const int i = o / NX, j = o % NX;
-    const double nx_i = vx[w][i], nx_j = vx[w][j];
-    const double dx_i = (double)dxb[i], dx_j = (double)dxb[j];
-    a.dQ[kb * MM + o] = (float)(0.5 * (nx_i * dx_j + nx_j * dx_i));
+  for (int h = 0; h < 2; ++h) {
+    half_rows(dx, 0.5 * x, x, 0.5 * dx, C, h);
+    if (out)
+#pragma unroll
+      for (int k = 0; k < NU; ++k) a.dQ[kb * MM + (14 * h + k) * NX + r] = (float)C[k];
   }
-  if (!hasNext) return;
-  // control b of block row b + 1: dA_b = lambda_{b+1} nu1x_b^T + mu_{b+1} dx_b^T,
-  // dB_b = lambda_{b+1} nu1u_b^T + mu_{b+1} du_b^T, dR_b = sym(nu1u_b du_b^T)
-  const float *lin = a.lam_in + (kb + 1) * NX;
-  const double *mun = lam + (kb + 1) * NX;
-  const float *dub = a.du_in + cb * NU;
-  for (int o = lane; o < MM; o += 64) {
-    const int i = o / NX, j = o % NX;
-    a.dA[cb * MM + o] = (float)((double)lin[i] * vx[w][j] + mun[i] * (double)dxb[j]);
+  if (!__any(next)) return;
+  // dA_b = lambda_{b+1} nu1x_b^T + mu_{b+1} dx_b^T, dB_b = lambda_{b+1} nu1u_b^T + mu_{b+1} du_b^T,
+  // dR_b = sym(nu1u_b du_b^T)
+  const double li = next ? (double)a.lam_in[(kb + 1) * NX + r] : 0.0;
+  const double du = next ? (double)a.du_in[cb * NU + c] : 0.0;
+  for (int h = 0; h < 2; ++h) {
+    half_rows(li, x, ln, dx, C, h);
+    if (outn)
+#pragma unroll
+      for (int k = 0; k < NU; ++k) a.dA[cb * MM + (14 * h + k) * NX + r] = (float)C[k];
   }
-  for (int o = lane; o < NX * NU; o += 64) {
-    const int i = o / NU, j = o % NU;
-    a.dB[cb * NX * NU + o] = (float)((double)lin[i] * vu[w][j] + mun[i] * (double)dub[j]);
+  half_rows(li, u, ln, du, C, 0);
+  {
+    double C1[NU];
+    half_rows(li, u, ln, du, C1, 1);  // each half writes its rows of B's columns
+    if (live && next && lane < NU)
+#pragma unroll
+      for (int k = 0; k < NU; ++k) a.dB[cb * NX * NU + (14 * L.half + k) * NU + lane] = (float)(L.half ? C1[k] : C[k]);
   }
-  for (int o = lane; o < NU * NU; o += 64) {
-    const int i = o / NU, j = o % NU;
-    const double ni = vu[w][i], nj = vu[w][j];
-    const double di = (double)dub[i], dj = (double)dub[j];
-    a.dR[cb * NU * NU + o] = (float)(0.5 * (ni * dj + nj * di));
-  }
+#pragma unroll
+  for (int k = 0; k < NU; ++k) C[k] = 0.0;
+  outer_row_add<NU>(C, du, 0.5 * u);
+  outer_row_add<NU>(C, u, 0.5 * du);
+  if (outu)
+#pragma unroll
+    for (int k = 0; k < NU; ++k) a.dR[cb * NU * NU + k * NU + lane] = (float)C[k];
 }
 
 }  // namespace wide

@@ -146,14 +146,14 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(3,
     double S[3][H];
     float P[3][H];
     {
-      const double *sb = a.S + kb * 3 * MM + (int64_t)r * NX + h * H;
-      const float *pb = a.P + kb * 3 * MM + (int64_t)r * NX + h * H;
+      const double *sb = a.S + kb * 3 * MM + h * H * NX + r;  // blocks by columns
+      const float *pb = a.P + kb * 3 * MM + h * H * NX + r;
 #pragma unroll
       for (int s = 0; s < 3; ++s)
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          const double sv = sb[s * MM + j];
-          const float pv = pb[s * MM + j];
+          const double sv = sb[s * MM + j * NX];
+          const float pv = pb[s * MM + j * NX];
           S[s][j] = mine ? sv : 0.0;
           P[s][j] = mine ? pv : 0.0f;
         }

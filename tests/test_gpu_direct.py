@@ -1,4 +1,4 @@
-"""GPU tests of the 14-state direct solve at the sizes where its split can go wrong: horizons
+"""GPU tests of the direct solves: of the 14-state one at the sizes where its split can go wrong: horizons
 around a whole chunk (4 knots), around the separators that fit LDS (32, so 128 knots), and
 around one, two and three levels of separators (512, 2048 knots), alone and in one ragged
 batch, and the adjoint with every loss gradient given and with none but dL/dlambda.
@@ -95,6 +95,48 @@ def test_adjoint_with_and_without_primal_loss_gradients(ctx, losses):
         k0, k1 = off[b], off[b + 1]
         c0, c1 = k0 - b, k1 - b - 1
         ref = kkt.adjoint_dense(p, f32(gl, k0, k1), f32(gx, k0, k1), f32(gu, c0, c1))
+        for k, a, z in (("dQ", k0, k1), ("dq", k0, k1), ("dR", c0, c1), ("dA", c0, c1), ("dB", c0, c1), ("dr", c0, c1), ("de", c0, c1)):
+            if z > a:
+                assert rel(g[k][a:z].cpu().numpy(), ref[k]) < 1e-5, (b, k)
+        assert rel(g["dx0"][b].cpu().numpy(), ref["dx0"]) < 1e-5, b
+
+
+# ---------------------------------------------------------------- 28 states
+# The two-arm path's chunks are of 4 rows on every level, two knots to a wave (an odd count
+# leaves half a wave without a knot); the last row of each problem is solved by itself.
+@pytest.fixture(scope="module")
+def wide():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_08079_amd.mpcpcg import Context
+    c = Context(28, 14, max_total_knots=1 << 10, max_batch=16)
+    c.mpcpcg_set_method("factor")
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("Ns", [[1], [2], [3], [4], [5], [16], [17], [64], [65], [257], [1, 4, 5, 3, 2, 16, 17, 66, 9]])
+def test_two_arm_at_the_edges_of_chunks_and_levels(wide, Ns):
+    probs = synth.batch(Ns, seed0=9950 + len(Ns) + Ns[0], nx=28, nu=14, defects=True)
+    packed, off = synth.pack(probs)
+    d = dev(packed)
+    fwd = wide.mpcpcg_solve_batched(d, off)
+    rng = np.random.default_rng(6)
+    gl, gx, gu = (rng.standard_normal(fwd[k].shape).astype(np.float32) for k in ("lam", "dx", "du"))
+    g = wide.mpcpcg_backward(d, off, fwd, *(torch.from_numpy(v).cuda() for v in (gl, gx, gu)))
+    torch.cuda.synchronize()
+    assert (status(fwd["stats"]) == 0).all() and (status(g["stats"]) == 0).all()
+    gl, gx, gu = (v.astype(np.float64) for v in (gl, gx, gu))
+    for b, p in enumerate(probs):
+        k0, k1 = off[b], off[b + 1]
+        c0, c1 = k0 - b, k1 - b - 1
+        ex = kkt.kkt_solve(p)
+        for k, a, z in (("lam", k0, k1), ("dx", k0, k1), ("du", c0, c1)):
+            if z > a:
+                assert rel(fwd[k][a:z].cpu().numpy(), ex[k]) < 1e-6, (b, k)
+        if k1 - k0 > 66:
+            continue  # (the dense adjoint of the oracle is cubic)
+        ref = kkt.adjoint_dense(p, gl[k0:k1], gx[k0:k1], gu[c0:c1])
         for k, a, z in (("dQ", k0, k1), ("dq", k0, k1), ("dR", c0, c1), ("dA", c0, c1), ("dB", c0, c1), ("dr", c0, c1), ("de", c0, c1)):
             if z > a:
                 assert rel(g[k][a:z].cpu().numpy(), ref[k]) < 1e-5, (b, k)
