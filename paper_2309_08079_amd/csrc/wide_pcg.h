@@ -2,20 +2,29 @@
 //
 // A problem of N knots is cut into parts of KW consecutive knots, one workgroup per part
 // and one wave per knot; the parts of a problem form a gang that meets at gang barriers,
-// as in the 14-state kernel.  Lanes r and r + 32 of a knot's wave both own row r (< 28)
-// of the knot's block row and each keeps half of its columns of S (FP64) and of Phi^-1
-// (FP32) in registers for the whole solve: 3 x 14 doubles and 3 x 14 floats per lane.  A
-// product takes the vector entries of its half from LDS (the same address for every lane
-// of a half: a broadcast read) and the two halves add their partial sums across the wave.
+// as in the 14-state kernel.  The four 16-lane DPP rows of a wave are the quarters of the
+// knot's block row: lane i < 14 of quarter (h, c) owns row 14 h + i of the first or second
+// half of the rows and the 14 columns of half c of each block, in registers for the whole
+// solve: 3 x 14 doubles of S and 3 x 14 floats of Phi^-1.  The vectors r and p are kept by
+// columns: that lane holds entry 14 c + i of the knot's own, the previous and the next knot,
+// so a product is 42 fused broadcast-FMAs from registers, and one swap between the two
+// quarters of a row half adds their partial sums.
 //
 // The loop is Algorithm 1 as printed, with its two inner products each met at a gang
-// barrier.  Values that cross a part boundary travel with those barriers as 16-byte tagged
-// words (the 14-state kernel's protocol): each part publishes its partial sum and the rows
-// of its first and last knot of the vector just formed (S p at the first barrier,
-// Phi^-1 r at the second); every part then updates its copies of r and p of the two
-// neighbouring knots with the same fused operations the neighbour applies to its own, so
-// the copies stay bit-identical and no other exchange is needed.  Partial sums are added
-// in a fixed order, so every part takes the same decisions.
+// barrier.  The rows of the vector just formed (S p at the first barrier, Phi^-1 r at the
+// second) go through LDS to the waves of the neighbouring knots, and across a part boundary
+// as 16-byte tagged words (the 14-state kernel's protocol) with the partial sums.  After the
+// barrier every wave updates r or p of its three knots with the same fused operations, so
+// the copies stay bit-identical to the owner's and no other exchange is needed.  Partial
+// sums are added in a fixed order, so every part takes the same decisions.
+//
+// What bounds it: rounds of resident workgroups (the rows of S and Phi^-1 fill the registers
+// at three waves per SIMD), and in each iteration the latency of its two barriers, ~ 0.65 us
+// each of the 2.2 us of a lone problem of 64 knots (0.87 us with no gang).  Measured on
+// MI355X, 32 problems of 64 to 256 knots (three rounds of ~ 113 iterations): 835 us.  With
+// the vectors' entries read from LDS as broadcasts, 42 + 42 per lane and iteration, and three
+// more workgroup barriers per iteration: 1276 (2.2 us with no gang); with sums and rows
+// awaited by one wave, two dependent round trips per poll: 990.
 //
 // Inputs are the workspace blocks the formation and preconditioner launches write (S, Phi^-1,
 // the right-hand side); the output is lambda (or mu in adjoint mode) in FP64 in lamw and
@@ -56,35 +65,35 @@ struct GangArgs {
 template <int NX, int KW>
 __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(3, 3)))
     wide_pcg_gang(const WArgs a, const GangArgs g) {
-  static_assert(NX % 2 == 0 && NX <= 32, "two lanes per row of an even NX <= 32");
+  static_assert(NX == pair::kN && KW > 2, "two halves of 14 rows; a wave for each channel beside the first");
   constexpr int H = NX / 2;
   constexpr int MM = NX * NX;
   constexpr int NT = KW * 64;
-  __shared__ __attribute__((aligned(16))) double vx[KW + 2][32];  // slot s + 1 = knot s of the part
-  __shared__ __attribute__((aligned(16))) float vf[KW + 2][32];
-  __shared__ double hr[2][32], hp[2][32], hg[2][32];  // neighbours' r, p, rhs [side][row]
-  __shared__ double hin[2][2][32];                    // received rows [channel][side][row]
-  __shared__ double red_w[2][KW];                     // [value][wave]
+  // rows of the part's knots (slot s + 1 = knot s) and of its two neighbours: S p (at the
+  // start the right-hand side, then r), Phi^-1 r (at the start lambda)
+  __shared__ double us[KW + 2][32], ts[KW + 2][32];
+  __shared__ double red_w[2][2][KW];                  // the knots' sums [parity of the barrier][value][wave]
   __shared__ double tot[2];
-  __shared__ int sh_task, sh_abort;
+  __shared__ int sh_task, sh_abort[2];                // [parity of the barrier]
 
   // Lane indices are re-derived through an opaque copy of threadIdx.x at the top of every
-  // PCG iteration (refresh below), so that the compiler recomputes the LDS addresses of the
-  // products instead of keeping them live across the loop, where the registers hold S and
-  // Phi^-1.
-  int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  int h = lane >> 5, row = lane & 31;
-  bool rowv = row < NX;
-  int r = rowv ? row : 0;
+  // PCG iteration, so that the compiler recomputes LDS and workspace addresses instead of
+  // keeping them live across the loop, where the registers hold S and Phi^-1.
+  int tid = threadIdx.x, wave, lane, c, r, e;
+  bool rowv, rows, ents;
   auto refresh = [&]() {
     asm volatile("" : "+v"(tid));
-    wave = tid >> 6;
+    wave = uni(tid >> 6);
     lane = tid & 63;
-    h = lane >> 5;
-    row = lane & 31;
-    rowv = row < NX;
-    r = rowv ? row : 0;
+    c = (lane >> 4) & 1;
+    rowv = (lane & 15) < H;
+    const int li = min(lane & 15, H - 1);
+    r = (lane >> 5) * H + li;   // this lane's row of the blocks
+    e = c * H + li;             // this lane's entry of the vectors
+    rows = rowv && c == 0;      // lanes that pass a product's rows on
+    ents = rowv && lane < 32;   // lanes that pass a vector's entries on
   };
+  refresh();
   WTag *tws = reinterpret_cast<WTag *>(g.tws);
   const __amdgpu_buffer_rsrc_t wsr = ws_rsrc(g.tws);
   auto ws_off = [&](const void *p) { return (uint32_t)((const char *)p - (const char *)g.tws); };
@@ -128,26 +137,24 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(3,
     const bool multi = G > 1;
     const int b = part * KW + wave;
     const bool act = b < N;
-    const bool mine = act && rowv;  // this lane holds a row of an existing knot
+    const bool mine = act && rowv;  // this lane holds part of an existing knot
     const int64_t kb = pd.k0 + (act ? b : 0);
     const int my_t = pd.t0 + part;
     Gang *gang = g.gang + tk.prob;
     int nsync = 0;
     bool aborted = false;
-    if (tid == 0) sh_abort = 0;
-    for (int t = tid; t < 2 * 32; t += NT) {
-      const int s = t >> 5, l = t & 31;
-      vx[s ? KW + 1 : 0][l] = 0.0;
-      vf[s ? KW + 1 : 0][l] = 0.0f;
-      hr[s][l] = 0.0; hp[s][l] = 0.0; hg[s][l] = 0.0;
+    if (tid < 2) sh_abort[tid] = 0;
+    for (int t = tid; t < (KW + 2) * 32; t += NT) {
+      (&us[0][0])[t] = 0.0;
+      (&ts[0][0])[t] = 0.0;
     }
 
     // rows of S and Phi^-1: this lane's half of the columns of blocks (b,b-1), (b,b), (b,b+1)
     double S[3][H];
     float P[3][H];
     {
-      const double *sb = a.S + kb * 3 * MM + h * H * NX + r;  // blocks by columns
-      const float *pb = a.P + kb * 3 * MM + h * H * NX + r;
+      const double *sb = a.S + kb * 3 * MM + c * H * NX + r;  // blocks by columns
+      const float *pb = a.P + kb * 3 * MM + c * H * NX + r;
 #pragma unroll
       for (int s = 0; s < 3; ++s)
 #pragma unroll
@@ -160,250 +167,203 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(3,
     }
     const bool adj = a.adjoint != 0;
     const bool warm = !adj && a.warm;
-    const double rhs = mine ? a.rhs[kb * NX + r] : 0.0;
-    double lam = (warm && mine) ? (double)a.lam[kb * NX + r] : 0.0;
+    double lam = (warm && mine) ? (double)a.lam[kb * NX + e] : 0.0;
 
-    // ---- products with the vector in vx / vf (slots wave, wave+1, wave+2 = b-1, b, b+1)
-    // (one block's vector entries at a time in registers: the loads of a block are not
-    // hoisted above the previous block's products)
-    auto s_prod = [&]() {
-      double acc = 0.0;
+    // ---- products with the vectors' entries of knots b-1, b, b+1: this lane's row r
+    auto s_prod = [&](const double (&x)[3]) {
+      double acc = 0.0, lo, hi;
 #pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        const double *x = &vx[wave + s][h * H];
-#pragma unroll
-        for (int j = 0; j < H; ++j) acc = __builtin_fma(S[s][j], x[j], acc);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const double other = __shfl_xor(acc, 32);
-      return h == 0 ? acc + other : other + acc;
+      for (int s = 0; s < 3; ++s) row_fma14_f64(acc, x[s], S[s]);
+      pair::dup(acc, lo, hi);
+      return lo + hi;
     };
-    auto p_prod = [&]() {
+    auto p_prod = [&](const double (&x)[3]) {
       float acc = 0.0f;
 #pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        const float *x = &vf[wave + s][h * H];
+      for (int s = 0; s < 3; ++s) row_fma14_f32(acc, (float)x[s], P[s]);
+      const uint32_t u = __builtin_bit_cast(uint32_t, acc);
+      const auto v = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+      return __builtin_bit_cast(float, (uint32_t)v[0]) + __builtin_bit_cast(float, (uint32_t)v[1]);
+    };
+    // the three knots' entries of rows that are in LDS
+    auto entries = [&](const double (&v)[KW + 2][32], double (&x)[3]) {
 #pragma unroll
-        for (int j = 0; j < H; ++j) acc = __builtin_fmaf(P[s][j], x[j], acc);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const float other = __shfl_xor(acc, 32);
-      return h == 0 ? acc + other : other + acc;
+      for (int s = 0; s < 3; ++s) x[s] = v[wave + s][e];
     };
-    // this wave's knot's share of an inner product, summed over its rows in a fixed order
-    // (the rows live in lanes 0..31)
+    // this wave's knot's share of an inner product, the row halves' sums added in order (the
+    // entries and the product's rows meet in the lanes with r == e)
     auto put_red = [&](int v, double x) {
-      const double s = sum_rows01((h == 0 && mine) ? x : 0.0);
-      if (lane == 0) red_w[v][wave] = s;
+      const uint64_t u = __builtin_bit_cast(uint64_t, group_sum_to_last(act && rowv && r == e ? x : 0.0));
+      const uint32_t lo0 = __builtin_amdgcn_readlane((uint32_t)u, 15), hi0 = __builtin_amdgcn_readlane((uint32_t)(u >> 32), 15);
+      const uint32_t lo1 = __builtin_amdgcn_readlane((uint32_t)u, 63), hi1 = __builtin_amdgcn_readlane((uint32_t)(u >> 32), 63);
+      if (lane == 0)
+        red_w[nsync & 1][v][wave] =
+            __builtin_bit_cast(double, ((uint64_t)hi0 << 32) | lo0) + __builtin_bit_cast(double, ((uint64_t)hi1 << 32) | lo1);
     };
-    // a boundary row of channel c (first knot: side 0, last knot: side 1) to the gang
-    auto put_row = [&](int c, double x) {
-      if (multi && h == 0 && rowv) {
+    // row i of the knot (lanes `on`) to the part and, of its first and last knot, to the gang
+    // (channel ch; first knot: side 0, last knot: side 1)
+    auto put_row = [&](int ch, double (&v)[KW + 2][32], bool on, int i, double x) {
+      if (on) v[wave + 1][i] = x;
+      if (multi && on) {
         const uint32_t tag = loop_tag(gen, nsync);
-        if (wave == 0) put_pair(ws_off(tws[my_t].rows[nsync & 1][c][0][row]), tag, x);
-        if (wave == KW - 1) put_pair(ws_off(tws[my_t].rows[nsync & 1][c][1][row]), tag, x);
+        if (wave == 0) put_pair(ws_off(tws[my_t].rows[nsync & 1][ch][0][i]), tag, x);
+        if (wave == KW - 1) put_pair(ws_off(tws[my_t].rows[nsync & 1][ch][1][i]), tag, x);
       }
     };
-    auto poll_spin = [&](int &polls, long long t_start) -> bool {
+    // (a wait's clock starts at its 64th poll: most end before)
+    auto poll_spin = [&](int &polls, long long &t_start) -> bool {
       __builtin_amdgcn_s_sleep(1);
       if ((++polls & 63) == 0) {
         if (__hip_atomic_load(&gang->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
-        if (wall_clock64() - t_start > g.spin_limit) {
+        const long long now = wall_clock64();
+        if (t_start == 0) t_start = now;
+        if (now - t_start > g.spin_limit) {
           __hip_atomic_store(&gang->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           return true;
         }
       }
       return false;
     };
-    // Gang barrier: NV partial sums (totals in tot[]) and NC channels of boundary rows
-    // (the neighbours' rows land in hin[c][side][row]; zeros where no neighbour exists).
-    auto sync = [&](int nv, int nc) {
-      __syncthreads();
+    // Barrier of the problem: the totals of nv inner products, and nc channels of rows, whose
+    // neighbours' rows land in v0s (and v1s).  A problem of one part needs one workgroup
+    // barrier, after which every wave adds the knots' sums itself.  In a gang wave 0 adds and
+    // publishes them and waits for the other parts' sums, 64 parts at a time, and wave 1 + ch
+    // for channel ch of the neighbours' rows (lane: side, row): one word per lane and value,
+    // all in flight at once, so that a poll is one round trip.  (Publishing every knot's sum
+    // instead, without the first workgroup barrier, measured 5% faster for 4 parts and 3 to 7%
+    // slower for 64 parts and for a full device.)
+    double total[2] = {0.0, 0.0};
+    auto sync = [&](int nv, int nc, double (&v0s)[KW + 2][32], double (&v1s)[KW + 2][32]) {
+      const int par = nsync & 1;
+      lds_barrier();
       if (!multi || aborted) {
-        if (tid == 0)
-          for (int v = 0; v < nv; ++v) {
-            double s = 0.0;
-            for (int w = 0; w < KW; ++w) s += red_w[v][w];
-            tot[v] = s;
-          }
-        for (int t = tid; t < 2 * 2 * 32; t += NT) (&hin[0][0][0])[t] = 0.0;
+        for (int v = 0; v < nv; ++v) {
+          double t = 0.0;
+#pragma unroll
+          for (int w = 0; w < KW; ++w) t += red_w[par][v][w];
+          total[v] = uni(t);
+        }
         ++nsync;
-        __syncthreads();
         return;
       }
-      const int par = nsync & 1;
       const uint32_t tag = loop_tag(gen, nsync);
+      // the whole workgroup waits for these waves: they issue ahead of co-resident ones
+      if (wave <= nc) __builtin_amdgcn_s_setprio(2);
       if (wave == 0 && lane < nv) {  // this part's sums, its waves in order
-        double ps = 0.0;
-        for (int w = 0; w < KW; ++w) ps += red_w[lane][w];
-        put_pair(ws_off(tws[my_t].red[par][lane]), tag, ps);
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) t += red_w[par][lane][w];
+        put_pair(ws_off(tws[my_t].red[par][lane]), tag, t);
       }
       // device scope: the last part's words land ~1 us after the first part arrives; through
       // one XCD's L2 a round takes ~0.4 us and polling at once is fastest
       if (!l2x) __builtin_amdgcn_s_sleep(24);
-      const long long t_start = wall_clock64();
+      long long t_start = 0;
       int polls = 0;
       bool ab = false;
-      // halo rows: thread t < nc * 2 * NX waits for (channel, side, row)
-      const bool hw = tid < nc * 2 * NX;
-      const int hc = tid / (2 * NX), hs = (tid / NX) & 1, hrow = tid % NX;
-      const int nb = hs == 0 ? part - 1 : part + 1;
-      const bool has = hw && nb >= 0 && nb < G;
-      const uint32_t hoff = ws_off(tws[has ? my_t + (hs == 0 ? -1 : 1) : my_t].rows[par][hc & 1][hs ^ 1][hrow]);
-      u32x4 hq = {0u, 0u, 0u, 0u};
-      double v0 = 0.0, v1 = 0.0;
-      for (int g0 = 0; g0 < (wave == 0 ? G : 1) && !ab; g0 += 64) {
-        const int gp = g0 + lane;
-        const bool want_red = wave == 0 && nv > 0 && gp < G;
-        const bool want_halo = g0 == 0 && has;
-        u32x4 rw0 = {0u, 0u, 0u, 0u}, rw1 = {0u, 0u, 0u, 0u};
+      if (wave == 0 && nv > 0) {
+        double v[2] = {0.0, 0.0};
+        for (int g0 = 0; g0 < G && !ab; g0 += 64) {
+          const bool want = g0 + lane < G;
+          const uint32_t o = ws_off(tws[pd.t0 + (want ? g0 + lane : 0)].red[par][0]);
+          u32x4 w0, w1;
+          while (true) {
+            w0 = get_pair(o);
+            w1 = w0;
+            if (nv > 1) w1 = get_pair(o + 16);
+            if (__ballot(!want || (pair_has(w0, tag) && pair_has(w1, tag))) == ~0ull) break;
+            if ((ab = poll_spin(polls, t_start))) break;
+          }
+          if (want) {
+            v[0] += pair_value(w0);
+            v[1] += pair_value(w1);
+          }
+        }
+        const double s0 = wave_sum(v[0]), s1 = nv > 1 ? wave_sum(v[1]) : 0.0;
+        if (lane == 0) {
+          tot[0] = s0;
+          tot[1] = s1;
+        }
+      } else if (wave > 0 && wave <= nc) {
+        const int side = lane >= NX, row = min(lane - side * NX, NX - 1);
+        const int nb = side ? part + 1 : part - 1;
+        const bool want = lane < 2 * NX && nb >= 0 && nb < G;
+        const uint32_t o = ws_off(tws[want ? pd.t0 + nb : my_t].rows[par][wave - 1][side ^ 1][row]);
+        u32x4 q;
         while (true) {
-          bool ok = true;
-          if (want_red) {
-            rw0 = get_pair(ws_off(tws[pd.t0 + gp].red[par][0]));
-            ok &= pair_has(rw0, tag);
-            if (nv > 1) {
-              rw1 = get_pair(ws_off(tws[pd.t0 + gp].red[par][1]));
-              ok &= pair_has(rw1, tag);
-            }
-          }
-          if (want_halo) {
-            hq = get_pair(hoff);
-            ok &= pair_has(hq, tag);
-          }
-          if (__ballot(ok) == ~0ull) break;
+          q = get_pair(o);
+          if (__ballot(!want || pair_has(q, tag)) == ~0ull) break;
           if ((ab = poll_spin(polls, t_start))) break;
         }
-        if (want_red && !ab) {
-          v0 += pair_value(rw0);
-          if (nv > 1) v1 += pair_value(rw1);
-        }
+        if (want && !ab) (wave == 1 ? v0s : v1s)[side ? KW + 1 : 0][row] = pair_value(q);
       }
-      if (hw) hin[hc][hs][hrow] = (has && !ab) ? pair_value(hq) : 0.0;
-      if (wave == 0) {
-        const double w0 = wave_sum(v0), w1 = nv > 1 ? wave_sum(v1) : 0.0;
-        if (lane == 0) {
-          tot[0] = w0;
-          tot[1] = w1;
-        }
-      }
-      if (ab) sh_abort = 1;
-      __syncthreads();
+      if (ab) sh_abort[par] = 1;
+      __builtin_amdgcn_s_setprio(0);
+      lds_barrier();
       ++nsync;
-      aborted = aborted || uni(sh_abort) != 0;
-    };
-    auto put_vx = [&](double x) {
-      if (h == 0 && rowv) vx[wave + 1][row] = x;
-    };
-    auto put_vf = [&](float x) {
-      if (h == 0 && rowv) vf[wave + 1][row] = x;
+      aborted = aborted || uni(sh_abort[par]) != 0;
+      total[0] = uni(tot[0]);
+      total[1] = uni(tot[1]);
     };
 
-    // ---- setup: the neighbours' right-hand-side rows (and warm-start rows)
-    put_row(0, rhs);
-    if (warm) put_row(1, lam);
-    sync(0, warm ? 2 : 1);
-    for (int t = tid; t < 2 * NX; t += NT) {
-      const int s = t / NX, l = t % NX;
-      hg[s][l] = hin[0][s][l];
-      hr[s][l] = hin[0][s][l];
-    }
-    double rv = rhs;
+    // ---- setup: right-hand side (and warm-start) of the three knots
+    double rs[3], ps[3], ms[3];
+    __syncthreads();  // us and ts are zero
+    put_row(0, us, ents, e, mine ? a.rhs[kb * NX + e] : 0.0);
+    if (warm) put_row(1, ts, ents, e, lam);
+    sync(0, warm ? 2 : 1, us, ts);
+    entries(us, rs);
     if (warm) {
-      // r = gamma - S lambda_0 (lambda_0 of the neighbours' boundary knots from the setup)
-      put_vx(lam);
-      for (int t = tid; t < 2 * NX; t += NT) {
-        const int s = t / NX, l = t % NX;
-        vx[s ? KW + 1 : 0][l] = hin[1][s][l];
-      }
-      __syncthreads();
-      rv = rhs - s_prod();
-      put_row(0, rv);
-      sync(0, 1);
-      for (int t = tid; t < 2 * NX; t += NT) {
-        const int s = t / NX, l = t % NX;
-        hr[s][l] = hin[0][s][l];
-      }
+      // r = gamma - S lambda_0; eta_ref = gamma^T Phi^-1 gamma needs Phi^-1 gamma as well
+      entries(ts, ms);
+      const double ref = rs[1] * (double)p_prod(rs);
+      __syncthreads();  // us and ts have been read
+      put_row(0, us, rows, r, (mine ? a.rhs[kb * NX + r] : 0.0) - s_prod(ms));
+      sync(0, 1, us, us);
+      entries(us, rs);
+      put_red(1, ref);
     }
-    double eta = 0.0, eta_ref = 0.0, eta_new = 0.0;
-    float rt;
-    {
-      __syncthreads();
-      put_vf((float)rv);
-      for (int t = tid; t < 2 * NX; t += NT) {
-        const int s = t / NX, l = t % NX;
-        vf[s ? KW + 1 : 0][l] = (float)hr[s][l];
-      }
-      __syncthreads();
-      rt = p_prod();
-      put_red(0, rv * (double)rt);
-      if (warm) {  // eta_ref = gamma^T Phi^-1 gamma needs Phi^-1 gamma as well
-        __syncthreads();
-        put_vf((float)rhs);
-        for (int t = tid; t < 2 * NX; t += NT) {
-          const int s = t / NX, l = t % NX;
-          vf[s ? KW + 1 : 0][l] = (float)hg[s][l];
-        }
-        __syncthreads();
-        const float gt = p_prod();
-        put_red(1, rhs * (double)gt);
-      }
-      put_row(0, (double)rt);
-      sync(warm ? 2 : 1, 1);
-      eta = uni(tot[0]);
-      eta_ref = warm ? uni(tot[1]) : eta;
-    }
-    double p = (double)rt;
-    for (int t = tid; t < 2 * NX; t += NT) {
-      const int s = t / NX, l = t % NX;
-      hp[s][l] = hin[0][s][l];
-    }
+    float rt = p_prod(rs);
+    put_red(0, rs[1] * (double)rt);
+    put_row(0, ts, rows, r, (double)rt);
+    sync(warm ? 2 : 1, 1, ts, ts);
+    double eta = total[0], eta_new = eta;
+    const double eta_ref = warm ? total[1] : eta;
+    entries(ts, ps);
     const double tau = a.stop_abs ? (double)a.eps : (double)a.eps * (double)a.eps * eta_ref;
     // two barriers per iteration: the cap keeps barrier indices within the tags' 24 bits
     const int max_iter = min(a.max_iter > 0 ? a.max_iter : N * NX, 1 << 22);
     int status = MPCPCG_NOT_CONVERGED, it = 0;
-    double res = rv;  // r of Algorithm 1 (this lane's row)
-    eta_new = eta;
     if (!(eta == eta) || !(eta_ref == eta_ref) || __builtin_isinf(eta) || __builtin_isinf(eta_ref)) {
       status = MPCPCG_BREAKDOWN;
     } else if (eta <= tau) {
       status = MPCPCG_OK;
     } else {
+      __syncthreads();  // the setup's sums and rows have been read
       for (it = 1; it <= max_iter && !aborted; ++it) {
         refresh();
         // Upsilon = S p, upsilon = p^T Upsilon
-        __syncthreads();
-        put_vx(p);
-        for (int t = tid; t < 2 * NX; t += NT) {
-          const int s = t / NX, l = t % NX;
-          vx[s ? KW + 1 : 0][l] = hp[s][l];
-        }
-        __syncthreads();
-        const double ups_row = s_prod();
-        put_red(0, p * ups_row);
-        put_row(0, ups_row);
-        sync(1, 1);
-        const double ups = uni(tot[0]);
+        const double ups_row = s_prod(ps);
+        put_row(0, us, rows, r, ups_row);
+        put_red(0, ps[1] * ups_row);
+        sync(1, 1, us, us);
+        entries(us, ms);
+        const double ups = total[0];
         if (!(ups > 0.0) || __builtin_isinf(ups)) {
           status = MPCPCG_BREAKDOWN;
           break;
         }
         const double alpha = eta / ups;
-        lam = __builtin_fma(alpha, p, lam);
-        res = __builtin_fma(-alpha, ups_row, res);
-        for (int t = tid; t < 2 * NX; t += NT) {
-          const int s = t / NX, l = t % NX;
-          hr[s][l] = __builtin_fma(-alpha, hin[0][s][l], hr[s][l]);
-          vf[s ? KW + 1 : 0][l] = (float)hr[s][l];
-        }
+        lam = __builtin_fma(alpha, ps[1], lam);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) rs[s] = __builtin_fma(-alpha, ms[s], rs[s]);
         // r~ = Phi^-1 r, eta' = r^T r~
-        put_vf((float)res);
-        __syncthreads();
-        rt = p_prod();
-        put_red(0, res * (double)rt);
-        put_row(0, (double)rt);
-        sync(1, 1);
-        eta_new = uni(tot[0]);
+        rt = p_prod(rs);
+        put_row(0, ts, rows, r, (double)rt);
+        put_red(0, rs[1] * (double)rt);
+        sync(1, 1, ts, ts);
+        entries(ts, ms);
+        eta_new = total[0];
         if (!(eta_new == eta_new) || __builtin_isinf(eta_new)) {
           status = MPCPCG_BREAKDOWN;
           break;
@@ -413,17 +373,14 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(3,
           break;
         }
         const double beta = eta_new / eta;
-        p = __builtin_fma(beta, p, (double)rt);
-        for (int t = tid; t < 2 * NX; t += NT) {
-          const int s = t / NX, l = t % NX;
-          hp[s][l] = __builtin_fma(beta, hp[s][l], hin[0][s][l]);
-        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) ps[s] = __builtin_fma(beta, ps[s], ms[s]);
         eta = eta_new;
       }
       if (it > max_iter) it = max_iter;
     }
     if (aborted) status = MPCPCG_TIMEOUT;
-    if (h == 0 && mine) a.lamw[kb * NX + r] = lam;
+    if (mine && lane < 32) a.lamw[kb * NX + e] = lam;
     if (tid == 0 && part == 0)
       put_stats(a.stats + pd.id, it, status,
                 eta_ref > 0.0 ? (float)__builtin_sqrt(eta_new > 0.0 ? eta_new / eta_ref : 0.0) : 0.0f);
