@@ -398,11 +398,14 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
     // the polling itself the bottleneck once hundreds of workgroups wait at once.  Stale
     // words from earlier solves never carry a live tag: the last part out of a gang zeroes
     // the tagged words of every part.
-    auto poll_spin = [&](int &polls, long long t_start) -> int {
+    // (a wait's clock starts at its 64th poll: most end before)
+    auto poll_spin = [&](int &polls, long long &t_start) -> int {
       __builtin_amdgcn_s_sleep(1);
       if ((++polls & 63) == 0) {
         if (__hip_atomic_load(&gang->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return 1;
-        if (wall_clock64() - t_start > a.spin_limit) {
+        const long long now = wall_clock64();
+        if (t_start == 0) t_start = now;
+        if (now - t_start > a.spin_limit) {
           __hip_atomic_store(&gang->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           return 1;
         }
@@ -429,14 +432,6 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         store_pair_l2(wsr, off, tag, v);
       else
         store_pair(wsr, off, tag, v);
-    };
-    auto get_pair = [&](uint32_t off) -> u32x4 {
-      u32x4 w;
-      if (l2x)
-        w = load_pair_l2(wsr, off);
-      else
-        w = load_pair(wsr, off);
-      return w;
     };
     // Loop barrier: ND double channels of halos, NR partial sums
     // (read from red_g[ph] when the problem has one part); totals land in tot[].  `after`
@@ -466,15 +461,16 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           const int side = wl >> 4, l = wl & 15;
           const int nb = side == 0 ? part - 1 : part + 1;
           const bool has = wl < 2 * kGroup && nb >= 0 && nb < G;
-          const TagWS *hsrc = &tws[has ? my_t + (side == 0 ? -1 : 1) : my_t].tg;
           const int srcside = side == 0 ? 1 : 0;  // left neighbour's last knot / right's first
+          const uint32_t ho = ws_off(&tws[has ? my_t + (side == 0 ? -1 : 1) : my_t].tg.hv[par][0][srcside][l]);
+          constexpr int kChan = sizeof(tws->tg.hv[0][0]);  // bytes from one channel to the next
           u32x4 hq[ND > 0 ? ND : 1];
           // lanes 0..31 read value 0 of 32 parts at a time, lanes 32..63 value 1 (when there
           // is one), so one packed reduction below gives both totals
           const int vi = wl >> 5;
           double v = 0.0;
           int ab = 0, polls = 0;
-          const long long t_start = wall_clock64();
+          long long t_start = 0;
           // Device scope: the last part's words land ~1 us after the first part arrives, so
           // an immediate poll almost always fails and only adds traffic at the coherence
           // point, which every other gang's polls share: waiting ~1,500 cycles first
@@ -485,21 +481,24 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
             const int g = g0 + (wl & 31);
             const bool mine = vi < NR && g < G;
             const bool halo = g0 == 0 && has;
-            const TagWS *rsrc = &tws[pd.t0 + (mine ? g : 0)].tg;
+            const uint32_t ro = ws_off(tws[mine ? pd.t0 + g : my_t].tg.red[par][vi]);
             u32x4 rw = {0u, 0u, 0u, 0u};
+            // every lane loads all its words (its own part's where it waits for none), so that
+            // they are in flight together and a poll is one round trip: 0.25 us less of 2.05 us
+            // per iteration at 128 knots than with three dependent ones
             while (true) {
-              bool ok = true;
-              if (mine) {
-                rw = get_pair(ws_off(rsrc->red[par][vi]));
-                ok &= pair_has(rw, want_tag);
-              }
-              if (halo) {
+              if (l2x) {
+                if (NR > 0) rw = load_pair_l2(wsr, ro);
 #pragma unroll
-                for (int c = 0; c < ND; ++c) {
-                  hq[c] = get_pair(ws_off(hsrc->hv[par][c][srcside][l]));
-                  ok &= pair_has(hq[c], want_tag);
-                }
+                for (int c = 0; c < ND; ++c) hq[c] = load_pair_l2(wsr, ho + c * kChan);
+              } else {
+                if (NR > 0) rw = load_pair(wsr, ro);
+#pragma unroll
+                for (int c = 0; c < ND; ++c) hq[c] = load_pair(wsr, ho + c * kChan);
               }
+              bool ok = !mine || pair_has(rw, want_tag);
+#pragma unroll
+              for (int c = 0; c < ND; ++c) ok &= !halo || pair_has(hq[c], want_tag);
               if (__ballot(ok) == ~0ull) break;
               if ((ab = poll_spin(polls, t_start))) break;
             }
@@ -552,7 +551,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         const uint64_t need = a.stall ? ~0ull : epoch;
         if (wave == 0) {
           if (wl == 0) store8_x(wsr, ws_off(&tws[my_t].flag), epoch, l2x);
-          const long long t_start = wall_clock64();
+          long long t_start = 0;
           int ab = 0, polls = 0;
           // only the two neighbours' rows are needed
           const int nb = wl == 0 ? part - 1 : part + 1;
@@ -603,7 +602,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       const uint64_t epoch = (gen << 32) | 2u;
       if (wave == 0) {
         if (wl == 0) store8_x(wsr, ws_off(&tws[my_t].flag), epoch, l2x);
-        const long long t_start = wall_clock64();
+        long long t_start = 0;
         int ab = 0, polls = 0;
         const int nb = wl == 0 ? part - 1 : part + 1;
         const bool want = wl < 2 && nb >= 0 && nb < G;
@@ -1048,7 +1047,10 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       // knot's Phi^-1 row, so no second exchange is needed inside an iteration.
       double p = 0.0, sv = 0.0, sm = 0.0, sp = 0.0;
       double gam_prev = 1.0, alpha_prev = 1.0, tau = 0.0;
-      const bool edge_wave = multi && (wave == 0 || wave == NW - 1);
+      // (a scalar branch: register copies that the compiler leaves at the end of a divergent
+      // one around the stores below have run for the stores' lanes only)
+      const int uwave = uni(wave);
+      const bool edge_wave = multi && (uwave == 0 || uwave == NW - 1);
       // the reciprocals of the previous iteration's gamma and alpha are formed before the
       // iteration's first workgroup barrier by a wave that does no ghost product (it waits
       // there anyway), so only one division remains after the gang barrier
