@@ -86,6 +86,7 @@ struct Schedule {
   Task *d_xtasks = nullptr;
   int32_t *d_xoff = nullptr;
   int xgrid = 0;
+  bool low[2] = {false, false};  // the two-waves-per-SIMD kernel [per-XCD lists]
   hipGraph_t graph[4][2] = {};
   hipGraphExec_t exec[4][2] = {};
   hipGraphNode_t node[4][2] = {};
@@ -195,6 +196,7 @@ struct mpcpcg_ctx {
   int max_batch = 0;
   int64_t max_tasks = 0;
   int kpw_override = 0;
+  int caps[kNumKpw][4][2] = {};  // capacity() [shape][mode][low] (0: not queried yet)
   int fwd_cap[kNumKpw] = {};  // resident forward workgroups per shape of kKpwChoices (0: not queried yet)
   int use_graph = 1;
   // per-XCD task lists: only on a device that reports eight XCDs (one partition spanning
@@ -294,7 +296,20 @@ KernelFn kernel_for(int mode) {
   }
 }
 
-KernelFn kernel_for(int kpw, int mode) {
+// `low` asks for the form with two waves per SIMD and Phi^-1 in registers, for launches whose
+// workgroups are all resident at that occupancy.  Measured on MI355X per iteration, three waves
+// per SIMD and Phi^-1 in LDS / two and in registers: one problem of 16, 128, 512 knots 0.97 /
+// 0.92, 1.82 / 1.76, 1.86 / 1.82 us, 64 of 128 knots 2.03 / 1.93; the rest of a solve (the
+// formation has no spills) 34 / 30, 39 / 33 and 69 / 61 us.
+// The shapes that such launches use have it: 16 knots, and 4 and 8 for one short problem.
+KernelFn kernel_for(int kpw, int mode, bool low = false) {
+  if (low) {
+    if (kpw == 4 && mode == mpc::kForward) return mpc::pcg_kernel<kNX, kNU, 4, mpc::kForward, 0, 2>;
+    if (kpw == 8 && mode == mpc::kForward) return mpc::pcg_kernel<kNX, kNU, 8, mpc::kForward, 0, 2>;
+    if (kpw == 16 && mode == mpc::kForward) return mpc::pcg_kernel<kNX, kNU, 16, mpc::kForward, 0, 2>;
+    if (kpw == 16 && mode == mpc::kAdjoint) return mpc::pcg_kernel<kNX, kNU, 16, mpc::kAdjoint, 0, 2>;
+    if (kpw == 16 && mode == kAdjointKept) return mpc::pcg_kernel<kNX, kNU, 16, mpc::kAdjoint, 3, 2>;
+  }
   switch (kpw) {
     case 4: return kernel_for<4>(mode);
     case 8: return kernel_for<8>(mode);
@@ -304,6 +319,7 @@ KernelFn kernel_for(int kpw, int mode) {
     default: return kernel_for<32>(mode);
   }
 }
+bool has_low(int kpw, int mode) { return kernel_for(kpw, mode, true) != kernel_for(kpw, mode); }
 
 bool valid_kpw(int k) {
   for (int c : kKpwChoices)
@@ -320,19 +336,25 @@ bool valid_kpw(int k) {
 // slower than the 16-knot one at the same knots per compute unit by the query, and a single
 // solve of 43 parts of 24 knots placed on one XCD (32 compute units) timed out waiting for
 // parts that never started.
-int resident_per_cu(int occupancy, int kpw) {
+int resident_per_cu(int occupancy, int kpw, bool low = false) {
   const int waves = kpw * mpc::kGroup / 64;
-  const int per_simd = kpw == 32 ? 2 : 3;  // the kernel's waves per SIMD (waves_per_eu)
+  const int per_simd = low || kpw == 32 ? 2 : 3;  // the kernel's waves per SIMD (waves_per_eu)
   const int by_simd = waves <= 4 ? per_simd * (4 / waves) : per_simd / ((waves + 3) / 4);
   return std::min(occupancy, by_simd);
 }
 
 // resident workgroups of this kernel on the whole device
-int capacity(mpcpcg_ctx *c, int kpw, int mode, int *out) {
-  int nb = 0;
-  HIPCHK(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, reinterpret_cast<const void *>(kernel_for(kpw, mode)), kpw * mpc::kGroup, 0));
-  *out = resident_per_cu(nb, kpw) * c->cus;
+int capacity(mpcpcg_ctx *c, int kpw, int mode, int *out, bool low = false) {
+  int ki = 0;
+  while (kKpwChoices[ki] != kpw) ++ki;
+  int &cap = c->caps[ki][mode][low];
+  if (cap == 0) {
+    int nb = 0;
+    HIPCHK(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                  &nb, reinterpret_cast<const void *>(kernel_for(kpw, mode, low)), kpw * mpc::kGroup, 0));
+    cap = resident_per_cu(nb, kpw, low) * c->cus;
+  }
+  *out = cap;
   return MPCPCG_OK;
 }
 
@@ -391,7 +413,12 @@ int launch_single(mpcpcg_ctx *c, KArgs &a, int N, int kpw, int mode, hipStream_t
   // that XCD's L2
   a.one_xcd = (c->xcd_ok && c->xcd_pin && g > 1 && 8 * g <= cap) ? 1 : 0;
   a.l2x = a.one_xcd;
-  hipLaunchKernelGGL(kernel_for(kpw, mode), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
+  bool low = has_low(kpw, mode);
+  if (low) {
+    if ((st = capacity(c, kpw, mode, &cap, true))) return st;
+    low = (a.one_xcd ? 8 * g : g) <= cap;
+  }
+  hipLaunchKernelGGL(kernel_for(kpw, mode, low), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
   HIPCHK(c, hipGetLastError());
   return MPCPCG_OK;
 }
@@ -490,11 +517,15 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
   int cap = 0;
   int st = capacity(c, kpw, mpc::kForward, &cap);
   if (st) return st;
-  for (int m : {(int)mpc::kAdjoint, kAdjointKept}) {
+  int cap_low = cap;
+  for (int m : {(int)mpc::kForward, (int)mpc::kAdjoint, kAdjointKept}) {
     int capb = 0;
     st = capacity(c, kpw, m, &capb);
     if (st) return st;
     cap = std::min(cap, capb);
+    st = capacity(c, kpw, m, &capb, true);
+    if (st) return st;
+    cap_low = std::min(cap_low, capb);
   }
   for (const auto &d : probs)
     if (d.nparts > cap)
@@ -511,6 +542,7 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
     return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
   }
   for (int m = 0; m < 4; ++m) s->grid[m] = std::min(s->ntasks, cap);
+  s->low[0] = s->ntasks <= cap_low;
   // Per-XCD lists: workgroups are dispatched to the eight XCDs in turn, so a grid of 8 m
   // workgroups puts m on each (at most cap / 8 of them resident).  When every gang fits in
   // cap / 8, each problem (in longest-first order) goes to the XCD with the least work so
@@ -550,6 +582,7 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
     int longest = 0;
     for (int x = 0; x < kXcds; ++x) longest = std::max(longest, xoff[x + 1] - xoff[x]);
     s->xgrid = kXcds * std::min(longest, cap / kXcds);
+    s->low[1] = longest <= cap_low / kXcds;
   }
   make_room(c, c->sched, true);
   *out = c->sched.put(key, std::move(s));
@@ -770,15 +803,16 @@ int launch_batched(mpcpcg_ctx *c, Schedule *s, KArgs &a, int mode, int want_pin,
   a.persistent = 1;
   const int grid = pin ? s->xgrid : s->grid[mode];
   const dim3 block(s->kpw * mpc::kGroup);
+  const KernelFn fn = kernel_for(s->kpw, mode, s->low[x]);
   if (!c->use_graph) {
-    hipLaunchKernelGGL(kernel_for(s->kpw, mode), dim3(grid), block, 0, stream, a);
+    hipLaunchKernelGGL(fn, dim3(grid), block, 0, stream, a);
     HIPCHK(c, hipGetLastError());
     return MPCPCG_OK;
   }
   void *params[] = {&s->args[mode][x]};
   hipKernelNodeParams kp;
   std::memset(&kp, 0, sizeof kp);
-  kp.func = reinterpret_cast<void *>(kernel_for(s->kpw, mode));
+  kp.func = reinterpret_cast<void *>(fn);
   kp.gridDim = dim3(grid);
   kp.blockDim = block;
   kp.sharedMemBytes = 0;
@@ -1158,7 +1192,7 @@ struct NaDevice {
   std::once_flag once;
   int rc = MPCPCG_OK;
   unsigned char *ptr = nullptr;
-  int cap[kNumKpw] = {};  // co-resident workgroups per shape of kKpwChoices
+  int cap[kNumKpw] = {}, cap_low[kNumKpw] = {};  // co-resident workgroups per shape of kKpwChoices
   int xcd_ok = 0;
   int64_t spin = 0;
 };
@@ -1225,6 +1259,13 @@ void na_setup(NaDevice &d, int dev) {
       return;
     }
     d.cap[i] = resident_per_cu(nb, k) * prop.multiProcessorCount;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &nb, reinterpret_cast<const void *>(kernel_for(k, mpc::kForward, true)), k * mpc::kGroup, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      d.rc = na_fail(MPCPCG_EHIP, "occupancy query failed on device %d", dev);
+      return;
+    }
+    d.cap_low[i] = resident_per_cu(nb, k, true) * prop.multiProcessorCount;
   }
 }
 
@@ -1914,7 +1955,8 @@ int mpcpcg_solve_noalloc(const mpcpcg_problem *p, const mpcpcg_opts *o, float *l
   // the placement rule of mpcpcg_solve: a gang that fits one XCD's share runs there
   a.one_xcd = (d.xcd_ok && g > 1 && 8 * g <= d.cap[ki]) ? 1 : 0;
   a.l2x = a.one_xcd;
-  hipLaunchKernelGGL(kernel_for(kpw, mpc::kForward), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
+  const bool low = has_low(kpw, mpc::kForward) && (a.one_xcd ? 8 * g : g) <= d.cap_low[ki];
+  hipLaunchKernelGGL(kernel_for(kpw, mpc::kForward, low), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return na_fail(MPCPCG_EHIP, "launch failed: %s", hipGetErrorString(e));
   return MPCPCG_OK;

@@ -233,11 +233,12 @@ __device__ __forceinline__ double uni(double v) {
 }
 
 
-// Register budget: the FP64 S row (84 VGPRs) stays resident for the whole solve and the
-// FP32 Phi^-1 row lives in LDS; the occupancy target sets how many knots stay resident.
-// A 32-knot workgroup (8 waves) fits only two waves per SIMD anyway, so it keeps the full
-// 256-VGPR budget; the other shapes target three (a 24-knot workgroup has 6 waves, two
-// per compute unit; a 48-knot one has 12 waves, one per compute unit).
+// Register budget: the FP64 S row (84 VGPRs) stays resident for the whole solve.  At three
+// waves per SIMD (168 VGPRs), which keeps the most knots resident, the FP32 Phi^-1 rows live
+// in LDS; at two (256) they are in registers as well, with the edge waves' ghost rows, and an
+// iteration's products read nothing but vectors.  A 32-knot workgroup (8 waves) fits only two
+// waves per SIMD anyway; the other shapes come in both forms (a 24-knot workgroup has 6 waves,
+// two per compute unit; a 48-knot one has 12 waves, one per compute unit).
 template <int KPW>
 constexpr int waves_per_eu() { return KPW == 32 ? 2 : 3; }
 // Rows of a control block as stored by columns (NU = 7 rows padded to 8: half a line).
@@ -255,13 +256,14 @@ __device__ __forceinline__ int64_t fws_index(int64_t k, int t, int c, int r) {
 // its factor record).  PHASE 3 (adjoint): S formed as in PHASE 0 from the inverses of Q and
 // R read from the forward's factor record, Phi^-1 read from it as well, then PCG and
 // epilogue.
-template <int NX, int NU, int KPW, int MODE, int PHASE = 0>
-__global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_eu(waves_per_eu<KPW>(), waves_per_eu<KPW>())))
+template <int NX, int NU, int KPW, int MODE, int PHASE = 0, int WPE = waves_per_eu<KPW>()>
+__global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
     pcg_kernel(const KArgs a) {
   static_assert(NX == 14 && NU <= NX, "the fused row kernels are written for 14-row blocks");
   constexpr int NT = KPW * kGroup;
   constexpr int NW = NT / 64;
   static_assert(NT % 64 == 0 && NW <= kMaxWaves, "whole waves, at most kMaxWaves");
+  constexpr bool kKeepP = WPE == 2;  // Phi^-1 rows in registers
 
   __shared__ double ex_d[2][KPW + 2][kGroup];  // vector exchange, slot s+1 is knot s
   __shared__ float ex_f[KPW + 2][kGroup];
@@ -937,7 +939,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       for (int j = 0; j < NX; ++j) asm volatile("" : "+v"(Sm[j]), "+v"(Sd[j]), "+v"(Sp[j]));
       // Phi^-1 rows move to LDS for the solve (the D^-1 exchange above used the same bytes)
       __syncthreads();
-      if (rowv) {
+      if (!kKeepP && rowv) {
         float *row = pl + (slot * NX + lane) * kPRow;
 #pragma unroll
         for (int j = 0; j < NX; ++j) {
@@ -977,6 +979,18 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         float m0[NX], m1[NX];
         load_m01(row, m0, m1);
         return precond_m01(row, m0, m1, xm, x0v, xp);
+      };
+      auto precond_regs = [&](const float (&m0)[NX], const float (&m1)[NX], const float (&m2)[NX], float xm, float x0v,
+                              float xp) {
+        float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f;
+        row_fma14_f32(acc0, xm, m0);
+        row_fma14_f32(acc1, x0v, m1);
+        row_fma14_f32(acc2, xp, m2);
+        return rowv ? (acc0 + acc1) + acc2 : 0.0f;
+      };
+      auto precond_own = [&](float xm, float x0v, float xp) {
+        if constexpr (kKeepP) return precond_regs(Pm, Pd, Pp, xm, x0v, xp);
+        else return precond_row(slot, xm, x0v, xp);
       };
       // one barrier per iteration; the cap keeps barrier indices within the 24 bits the tags give them
       const int max_iter = (int)min((int64_t)(a.max_iter > 0 ? a.max_iter : (int64_t)N * NX), (int64_t)1 << 23);
@@ -1026,7 +1040,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         row_fma14_f64(a1, lam, Sd);
         row_fma14_f64(a2, lp, Sp);
         r = rhs - ((a0 + a1) + a2);
-        const float gt = precond_row(slot, (float)rm, (float)rhs, (float)rp);
+        const float gt = precond_own((float)rm, (float)rhs, (float)rp);
         put_red(0, 0, rhs * (double)gt);
         __syncthreads();  // every halo read of the setup channels is done
         put_d2(r);
@@ -1046,36 +1060,53 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       // neighbours' w), and recomputes u of the adjacent knot itself from a copy of that
       // knot's Phi^-1 row, so no second exchange is needed inside an iteration.
       double p = 0.0, sv = 0.0, sm = 0.0, sp = 0.0;
-      double gam_prev = 1.0, alpha_prev = 1.0, tau = 0.0;
+      double gam_prev = __builtin_inf(), alpha_prev = 1.0, tau = 0.0;
       // (a scalar branch: register copies that the compiler leaves at the end of a divergent
       // one around the stores below have run for the stores' lanes only)
       const int uwave = uni(wave);
       const bool edge_wave = multi && (uwave == 0 || uwave == NW - 1);
+      // the ghost knots' rows (setup left them in LDS)
+      float Gm[NX], Gd[NX], Gp[NX];
+      if constexpr (kKeepP) {
+        const float *row = phi_row(slot == 0 ? KPW : KPW + 1);
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+          Gm[j] = row[j];
+          Gd[j] = row[NX + j];
+          Gp[j] = row[2 * NX + j];
+        }
+      }
       // the reciprocals of the previous iteration's gamma and alpha are formed before the
-      // iteration's first workgroup barrier by a wave that does no ghost product (it waits
+      // iteration's first workgroup barrier by waves that do no ghost product (they wait
       // there anyway), so only one division remains after the gang barrier
-      const int rcp_wave = NW > 2 ? 1 : 0;
+      const int rg_wave = NW > 2 ? 1 : 0, ra_wave = !kKeepP ? rg_wave : NW > 2 ? 2 : NW - 1;
       for (it = 0;; ++it) {
         if (aborted) break;
         // (1) u = Phi^-1 r on this knot, and on the ghost knot beyond each end
-        const float u = precond_row(slot, (float)rm, (float)r, (float)rp);
+        const float u = precond_own((float)rm, (float)r, (float)rp);
         ex_f[slot + 1][lane] = u;
         if (edge_wave) {
           // (the rest of the workgroup waits for the edge waves' second product)
           __builtin_amdgcn_s_setprio(1);
           const bool left = slot == 0;
-          const float ug = precond_row(left ? KPW : KPW + 1, (float)(left ? r2 : r), (float)(left ? rm : rp),
-                                       (float)(left ? r : r2));
+          const float xm = (float)(left ? r2 : r), xo = (float)(left ? rm : rp), xp = (float)(left ? r : r2);
+          float ug;
+          if constexpr (kKeepP) ug = precond_regs(Gm, Gd, Gp, xm, xo, xp);
+          else ug = precond_row(left ? KPW : KPW + 1, xm, xo, xp);
           if (slot == 0) ex_f[0][lane] = ug;
           if (slot == KPW - 1) ex_f[KPW + 1][lane] = ug;
           __builtin_amdgcn_s_setprio(0);
         }
-        if (wave == rcp_wave) {
-          const double rg = 1.0 / gam_prev, ra = 1.0 / alpha_prev;
-          if (wl == 0) {
-            rcp_sh[0] = rg;
-            rcp_sh[1] = ra;
+        if (uwave == rg_wave) {
+          const double q = 1.0 / gam_prev;
+          if (wl == 0) rcp_sh[0] = q;
+          if (ra_wave == rg_wave) {
+            const double q1 = 1.0 / alpha_prev;
+            if (wl == 0) rcp_sh[1] = q1;
           }
+        } else if (uwave == ra_wave) {
+          const double q = 1.0 / alpha_prev;
+          if (wl == 0) rcp_sh[1] = q;
         }
         __syncthreads();
         const double rg = uni(rcp_sh[0]), ra = uni(rcp_sh[1]);
@@ -1106,24 +1137,26 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         if (it == 0) {
           if (!warm) eta_ref = gam;  // lambda_0 = 0: r = gamma, so gam = gamma^T Phi^-1 gamma
           tau = a.stop_abs ? (double)a.eps : (double)a.eps * (double)a.eps * eta_ref;
-          if (!(eta_ref == eta_ref) || __builtin_isinf(eta_ref)) {
+          if (!__builtin_isfinite(eta_ref)) {
             status = MPCPCG_BREAKDOWN;
             break;
           }
+          if (gam <= tau) {
+            status = MPCPCG_OK;
+            break;
+          }
         }
-        if (!(gam == gam) || __builtin_isinf(gam)) {
-          status = MPCPCG_BREAKDOWN;
-          break;
-        }
-        if (it == 0 ? gam <= tau : gam < tau) {
-          status = MPCPCG_OK;
-          break;
-        }
-        if (it >= max_iter) break;
-        const double beta = it == 0 ? 0.0 : gam * rg;
-        const double pSp = it == 0 ? del : del - beta * gam * ra;
-        if (!(pSp > 0.0) || __builtin_isinf(pSp)) {
-          status = MPCPCG_BREAKDOWN;
+        const double beta = gam * rg;  // (0 at first: rg is the reciprocal of infinity)
+        const double pSp = del - beta * gam * ra;
+        // one test for every way out, the reason afterwards
+        const bool finite = __builtin_isfinite(gam), above = gam >= tau;
+        if (!(finite & above & (it < max_iter) & (pSp > 0.0) & (pSp < __builtin_inf()))) {
+          if (!finite)
+            status = MPCPCG_BREAKDOWN;
+          else if (!above)
+            status = MPCPCG_OK;
+          else if (it < max_iter)
+            status = MPCPCG_BREAKDOWN;
           break;
         }
         const double alpha = gam / pSp;
