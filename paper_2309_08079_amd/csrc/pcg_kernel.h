@@ -281,6 +281,8 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
   __shared__ __attribute__((aligned(16))) double red_g[2][KPW][2];  // [phase][knot slot][value]
   __shared__ double tot[2];
   __shared__ double rcp_sh[2];  // 1 / gamma_prev, 1 / alpha_prev of the PCG loop
+  // alpha, beta, gamma of the iteration, and whether the loop ends (1: done, 2: gave up)
+  __shared__ __attribute__((aligned(16))) double step_sh[4];
   __shared__ int sh_task;
   __shared__ int sh_abort;
 
@@ -436,10 +438,10 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         store_pair(wsr, off, tag, v);
     };
     // Loop barrier: ND double channels of halos, NR partial sums
-    // (read from red_g[ph] when the problem has one part); totals land in tot[].  `after`
-    // runs in every wave right after the closing workgroup barrier, before the abort flag is
-    // read, so that the LDS reads it issues share one round trip with that read.
-    auto sync_point = [&](auto nd_c, auto nr_c, int ph, auto &&after) {
+    // (read from red_g[ph] when the problem has one part).  Wave 0 calls `lead` with the
+    // totals and whether the wait was given up, before the closing workgroup barrier; `after`
+    // runs in every wave right after it, so that the LDS reads it issues share one round trip.
+    auto sync_point = [&](auto nd_c, auto nr_c, int ph, auto &&lead, auto &&after) {
       constexpr int ND = decltype(nd_c)::value, NR = decltype(nr_c)::value;
       __syncthreads();
       if (multi && aborted) {
@@ -447,7 +449,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         ++nsync;
         after();
       } else if (multi) {
-        if (wave == 0) {
+        if (uni(wave) == 0) {
           // the whole workgroup waits for this wave until the totals are out: it issues
           // ahead of the co-resident workgroups' waves meanwhile
           __builtin_amdgcn_s_setprio(2);
@@ -515,31 +517,33 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           }
           double w0, w1;
           half_sums(v, w0, w1);
-          if (wl == 0) {
-            tot[0] = w0;
-            tot[1] = w1;
-            sh_abort = ab;
-          }
+          lead(w0, w1, ab);
           __builtin_amdgcn_s_setprio(0);
         }
         __syncthreads();
         ++nsync;
         after();
-        aborted = aborted || uni(sh_abort) != 0;
       } else {
-        if (wave == 0) {
+        if (uni(wave) == 0) {
           double s0, s1;
           part_sums(ph, NR, s0, s1);
-          if (wl == 0) {
-            tot[0] = s0;
-            tot[1] = s1;
-          }
+          lead(s0, s1, 0);
         }
         __syncthreads();
         after();
       }
     };
-    auto nothing = [] {};
+    // outside the loop: the totals to every wave
+    auto totals = [&](double s0, double s1, int ab) {
+      if (wl == 0) {
+        tot[0] = s0;
+        tot[1] = s1;
+        sh_abort = ab;
+      }
+    };
+    auto outcome = [&] {
+      if (multi) aborted = aborted || uni(sh_abort) != 0;
+    };
     // Formation barrier (barrier 0): the D^-1 rows of the two boundary knots (NX doubles
     // per lane) go through plain stores, then a completion wait and a flag
     // (launch generation << 32) | 1.  It runs once per solve, so it keeps the simpler
@@ -1044,7 +1048,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         put_red(0, 0, rhs * (double)gt);
         __syncthreads();  // every halo read of the setup channels is done
         put_d2(r);
-        sync_point(IC<2>{}, IC<1>{}, 0, nothing);
+        sync_point(IC<2>{}, IC<1>{}, 0, totals, outcome);
         eta_ref = uni(tot[0]);
         rm = ex_d[0][slot][lane];
         rp = ex_d[0][slot + 2][lane];
@@ -1080,6 +1084,13 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       // iteration's first workgroup barrier by waves that do no ghost product (they wait
       // there anyway), so only one division remains after the gang barrier
       const int rg_wave = NW > 2 ? 1 : 0, ra_wave = !kKeepP ? rg_wave : NW > 2 ? 2 : NW - 1;
+      // LEAD: wave 0 turns the totals into the step for the whole workgroup.  With three waves
+      // per SIMD the loop is bound by issue, and one wave's arithmetic instead of every wave's
+      // measured 2.2 -> 2.1 us per iteration (256 problems of 128 knots, three rounds); in a
+      // gang at two waves 1.72 -> 1.67 (the wave runs at a higher priority).  In a problem of
+      // one part every wave takes the totals itself: 0.95 -> 0.87 us with 16 knots.
+      auto iterate = [&](auto lead_c) __attribute__((always_inline)) {
+      constexpr bool LEAD = decltype(lead_c)::value != 0;
       for (it = 0;; ++it) {
         if (aborted) break;
         // (1) u = Phi^-1 r on this knot, and on the ghost knot beyond each end
@@ -1109,7 +1120,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           if (wl == 0) rcp_sh[1] = q;
         }
         __syncthreads();
-        const double rg = uni(rcp_sh[0]), ra = uni(rcp_sh[1]);
+        const double rg = rcp_sh[0], ra = rcp_sh[1];  // (for wave 0)
         // (2) w = S u
         // (the own block first: it needs no LDS value, so it runs while u of the
         // neighbouring knots is read)
@@ -1122,44 +1133,71 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         // (3) gam = r^T u, delta = w^T u; w two knots deep to the neighbours
         put_red2(0, r * (double)u, w * (double)u);
         put_d2(w);
-        // after the barrier, one LDS round trip: the totals, w of the neighbouring knots
-        // (the halo copies at the part's ends) and w two knots out for the edge slots
-        double tg, td, wm, wp, wh2;
-        sync_point(IC<2>{}, IC<2>{}, 0, [&] {
-          tg = tot[0];
-          td = tot[1];
-          wm = ex_d[0][slot][lane];
-          wp = ex_d[0][slot + 2][lane];
-          wh2 = ex_d[1][slot == 0 ? 0 : KPW + 1][lane];
-        });
-        const double gam = uni(tg), del = uni(td);
-        eta_new = gam;
-        if (it == 0) {
-          if (!warm) eta_ref = gam;  // lambda_0 = 0: r = gamma, so gam = gamma^T Phi^-1 gamma
-          tau = a.stop_abs ? (double)a.eps : (double)a.eps * (double)a.eps * eta_ref;
-          if (!__builtin_isfinite(eta_ref)) {
-            status = MPCPCG_BREAKDOWN;
-            break;
+        // the step from the totals; returns whether the loop ends
+        auto decide = [&](double gam, double del, double &alpha, double &beta) __attribute__((always_inline)) -> bool {
+          bool end = false;
+          bool finite = __builtin_isfinite(gam);
+          eta_new = gam;
+          if (it == 0) {
+            if (!warm) eta_ref = gam;  // lambda_0 = 0: r = gamma, so gam = gamma^T Phi^-1 gamma
+            tau = a.stop_abs ? (double)a.eps : (double)a.eps * (double)a.eps * eta_ref;
+            finite = finite && __builtin_isfinite(eta_ref);
           }
-          if (gam <= tau) {
-            status = MPCPCG_OK;
-            break;
+          beta = gam * rg;  // (0 at first: rg is the reciprocal of infinity)
+          const double pSp = del - beta * gam * ra;
+          if (LEAD) alpha = gam / pSp;  // (beside the test: nothing else runs in this wave)
+          // one test for every way out, the reason afterwards
+          const bool above = it == 0 ? gam > tau : gam >= tau;
+          if (!(finite & above & (it < max_iter) & (pSp > 0.0) & (pSp < __builtin_inf()))) {
+            end = true;
+            if (!finite)
+              status = MPCPCG_BREAKDOWN;
+            else if (!above)
+              status = MPCPCG_OK;
+            else if (it < max_iter)
+              status = MPCPCG_BREAKDOWN;
           }
+          if (!LEAD) alpha = gam / pSp;
+          return end;
+        };
+        double alpha, beta, gam, wm, wp, wh2;
+        // after the barrier, one LDS round trip: the step or the totals, w of the neighbouring
+        // knots (the halo copies at the part's ends) and w two knots out for the edge slots
+        if constexpr (LEAD) {
+          int stop = 0;
+          sync_point(IC<2>{}, IC<2>{}, 0, [&](double s0, double s1, int ab) __attribute__((always_inline)) {
+            double al, be;
+            const int stop = (decide(s0, s1, al, be) ? 1 : 0) | (ab ? 2 : 0);
+            if (wl == 0) {
+              step_sh[0] = al;
+              step_sh[1] = be;
+              step_sh[2] = s0;
+              reinterpret_cast<int *>(&step_sh[3])[0] = stop;
+            }
+          }, [&] {
+            alpha = step_sh[0];
+            beta = step_sh[1];
+            gam = step_sh[2];
+            stop = reinterpret_cast<const int *>(&step_sh[3])[0];
+            wm = ex_d[0][slot][lane];
+            wp = ex_d[0][slot + 2][lane];
+            wh2 = ex_d[1][slot == 0 ? 0 : KPW + 1][lane];
+          });
+          stop = uni(stop);
+          aborted = aborted || (stop & 2) != 0;
+          if (stop & 1) break;
+        } else {
+          double tg, td;
+          sync_point(IC<2>{}, IC<2>{}, 0, totals, [&] {
+            tg = tot[0];
+            td = tot[1];
+            wm = ex_d[0][slot][lane];
+            wp = ex_d[0][slot + 2][lane];
+            wh2 = 0.0;
+          });
+          gam = uni(tg);
+          if (decide(gam, uni(td), alpha, beta)) break;
         }
-        const double beta = gam * rg;  // (0 at first: rg is the reciprocal of infinity)
-        const double pSp = del - beta * gam * ra;
-        // one test for every way out, the reason afterwards
-        const bool finite = __builtin_isfinite(gam), above = gam >= tau;
-        if (!(finite & above & (it < max_iter) & (pSp > 0.0) & (pSp < __builtin_inf()))) {
-          if (!finite)
-            status = MPCPCG_BREAKDOWN;
-          else if (!above)
-            status = MPCPCG_OK;
-          else if (it < max_iter)
-            status = MPCPCG_BREAKDOWN;
-          break;
-        }
-        const double alpha = gam / pSp;
         // (4) recurrences on this knot and on the halo copies (depth 1 everywhere, depth 2
         //     at the part's ends)
         p = __builtin_fma(beta, p, (double)u);
@@ -1177,6 +1215,11 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         gam_prev = gam;
         alpha_prev = alpha;
       }
+      };
+      if (!kKeepP || multi)
+        iterate(IC<1>{});
+      else
+        iterate(IC<!kKeepP>{});
       if (it > max_iter) it = max_iter;
       if (aborted) status = MPCPCG_TIMEOUT;
       if (!rowv || !act) lam = 0.0;
@@ -1187,7 +1230,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       // adjoint): x rows use Q_b^-1 and S_{b,b+1} = -Q_b^-1 A_b^T; u rows of control b-1
       // use R_{b-1}^-1 and W = R_{b-1}^-1 B_{b-1}^T (both written during formation).
       put_d(0, lam);
-      sync_point(IC<1>{}, IC<0>{}, 0, nothing);
+      sync_point(IC<1>{}, IC<0>{}, 0, totals, outcome);
       const double lp = ex_d[0][slot + 2][lane];
       double qmin = 0.0;   // q_b - lambda_b  (or gx_b - mu_b)
       if (act && rowv) {
@@ -1226,7 +1269,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
         // adjoint: lam holds mu, xrow = nu1x_b, urow = nu1u_{b-1}
         const double mu = lam, n1x = xrow, n1u = urow;
         put_d(0, n1x);
-          sync_point(IC<1>{}, IC<0>{}, 1, nothing);
+          sync_point(IC<1>{}, IC<0>{}, 1, totals, outcome);
         const double n1xm = ex_d[0][slot][lane];  // nu1x_{b-1}
         double dxb = 0.0, dxm = 0.0, lb = 0.0, dum = 0.0;
         if (act && rowv) {
