@@ -107,7 +107,7 @@ def ingest_counters(prof_dir):
         acc = {}
         for r in rows(name):
             # the forward (phase 0) and the adjoint that reads the forward's Phi^-1 (phase 3)
-            m = re.match(r"void mpc::pcg_kernel<14, 7, (\d+), (\d), [03]>", r["Kernel_Name"])
+            m = re.match(r"void mpc::pcg_kernel<14, 7, (\d+), (\d), [03], \d>", r["Kernel_Name"])
             if not m or m.group(2) not in MODE_OF_TEMPLATE:
                 continue
             acc.setdefault((MODE_OF_TEMPLATE[m.group(2)], m.group(1)), []).append(float(r["Counter_Value"]))
