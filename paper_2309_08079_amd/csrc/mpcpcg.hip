@@ -1021,10 +1021,7 @@ int wide_direct(mpcpcg_ctx *c, WideSchedule *w, const mpc::wide::WArgs &a, hipSt
   d.flag = c->w_flag;
   for (int l = 0; l < levels; ++l) {
     d.chunks = w->d_chunks[l]; d.in = lev[l]; d.out = lev[l + 1];
-    if (l == 0)
-      hipLaunchKernelGGL((mw::wide_eliminate<kWNX, 2>), dim3(w->nchunks[l]), dim3(2 * 64), 0, s, d);
-    else
-      hipLaunchKernelGGL((mw::wide_eliminate<kWNX, 4>), dim3(w->nchunks[l]), dim3(4 * 64), 0, s, d);
+    hipLaunchKernelGGL((mw::wide_eliminate<kWNX, 4>), dim3(w->nchunks[l]), dim3(4 * 64), 0, s, d);
   }
   const dim3 root_grid((w->nprobs + 1) / 2);
   if (levels == 0)

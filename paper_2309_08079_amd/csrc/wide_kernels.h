@@ -81,7 +81,7 @@ struct WArgs {
 //               for theta; one pair per knot with row-wise access at 2 waves per SIMD: 105);
 //   wide_theta  36 (with the products of theta and S before: 85); wide_precond 46 (130: one
 //               workgroup per knot, operands in LDS);
-//   wide_eliminate 109 for the knots, 25 for each of three levels above (four levels of odd-even
+//   wide_eliminate ~ 115 for the knots, 25 for each of three levels above (four levels of odd-even
 //               reduction, blocks re-read on each: ~ 430); its blocks read when needed and
 //               barriers that drained the stores: 164 and 55;
 //   wide_epilogue  43 forward and 34 adjoint (56 and 69 by one wave per knot).
@@ -325,7 +325,10 @@ __global__ void __launch_bounds__(256) wide_export(const WArgs a) {
 //   wide_eliminate  one workgroup per chunk: it eliminates rows 1 .. 3 one after the other.  A
 //       pair of 16-lane rows solves with D_k for W columns of T'_k^T or of F_k (and y_k), so
 //       every pair repeats the elimination of D_k itself and the columns are spread over the
-//       workgroup's 4 kWaves 16-lane rows;
+//       workgroup's 2 WAVES pairs.  Four waves (seven columns each, three workgroups per compute
+//       unit): a level of few chunks is one chain of three eliminations, 25 us, and the knots'
+//       level of the two-arm batch takes as long as with two waves and fourteen columns (less
+//       repeated work, but a workgroup more to a compute unit): forward and adjoint 643 -> 626 us;
 //   wide_root       the last separator of every problem, x_0 = D_0^-1 y_0, and its stats;
 //   wide_back       the inner rows of a level from the next level's solution.
 struct WChunk {
@@ -351,7 +354,7 @@ struct WDirect {
 };
 
 template <int NX, int WAVES>
-__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) wide_eliminate(const WDirect a) {
+__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_eliminate(const WDirect a) {
   constexpr int MM = NX * NX, W = NX / WAVES, LD = NX + 2;
   static_assert(NX == pair::kN && W % 7 == 0, "columns in blocks of seven");
   // by columns: D_1 .. D_3 (each takes the previous step's correction), and the couplings of
