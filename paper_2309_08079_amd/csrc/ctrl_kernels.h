@@ -58,14 +58,11 @@ struct CtrlArgs {
 
 __device__ __forceinline__ double alpha_of(int j) { return ldexp(1.0, -j); }
 
-// acc_i of the chain at joint i from positions q (stride 1), velocity v_i and torque u_i
-template <int NQ>
-__device__ __forceinline__ double chain_acc(const double *q, int i, double v, double u, double g, double d,
+// acc_i of the chain from the sines of the differences to the next and from the previous joint
+// (0 at the chain's ends), position q_i, velocity v_i and torque u_i
+__device__ __forceinline__ double chain_acc(double sr, double sl, double q, double v, double u, double g, double d,
                                             double kap) {
-  double spring = 0.0;
-  if (i + 1 < NQ) spring += sin(q[i + 1] - q[i]);
-  if (i > 0) spring -= sin(q[i] - q[i - 1]);
-  return u - g * sin(q[i]) - d * v + kap * spring;
+  return u - g * sin(q) - d * v + kap * (sr - sl);
 }
 
 // ---- Step 1: linearisation ------------------------------------------------------------
@@ -102,13 +99,11 @@ __global__ void __launch_bounds__(kThreads) linearize_kernel(const CtrlArgs a) {
       a.e[kc * NX + i] = (float)((double)xn[i] - f);
     } else {       // v+ = v + h acc
       const int p = i - NQ;
-      double qd[NQ];
-#pragma unroll
-      for (int j = 0; j < NQ; ++j) qd[j] = (double)x[j];
+      const double qp = (double)x[p], qr = (double)x[p + 1 < NQ ? p + 1 : p], ql = (double)x[p > 0 ? p - 1 : p];
       const double h = a.h, d = a.damp, kap = a.kap, g = a.grav[p];
-      const double cr = (p + 1 < NQ) ? cos(qd[p + 1 < NQ ? p + 1 : p] - qd[p]) : 0.0;
-      const double cl = (p > 0) ? cos(qd[p] - qd[p > 0 ? p - 1 : p]) : 0.0;
-      const double diag = -g * cos(qd[p]) - kap * (cr + cl);
+      const double cr = (p + 1 < NQ) ? cos(qr - qp) : 0.0;
+      const double cl = (p > 0) ? cos(qp - ql) : 0.0;
+      const double diag = -g * cos(qp) - kap * (cr + cl);
 #pragma unroll
       for (int j = 0; j < NQ; ++j) {
         double dq = (j == p) ? diag : (j == p + 1 ? kap * cr : (j == p - 1 ? kap * cl : 0.0));
@@ -118,7 +113,7 @@ __global__ void __launch_bounds__(kThreads) linearize_kernel(const CtrlArgs a) {
 #pragma unroll
       for (int j = 0; j < NU; ++j) brow[j] = (j == p) ? a.h : 0.0f;
       const double v = x[NQ + p];
-      const double acc = chain_acc<NQ>(qd, p, v, (double)u[p], g, d, kap);
+      const double acc = chain_acc(sin(qr - qp), sin(qp - ql), qp, v, (double)u[p], g, d, kap);
       a.e[kc * NX + i] = (float)((double)xn[i] - (v + h * acc));
     }
     if (i < NU) {  // r_k = R_k u_k
@@ -142,6 +137,14 @@ __global__ void __launch_bounds__(kThreads) merit_kernel(const CtrlArgs a) {
 #pragma unroll
   for (int j = 0; j < kAlphas; ++j) { cost[j] = 0.0; viol[j] = 0.0; }
 
+  // x - xref and dx of the chunk's knots: every row of a knot's Q needs all of them
+  __shared__ double ex[kMaxChunk * NX], ed[kMaxChunk * NX];
+  for (int t = threadIdx.x; t < nk * NX; t += kThreads) {
+    const int64_t at = (C.pk0 + C.lk0) * NX + t;
+    ex[t] = (double)a.X[at] - (double)a.xref[at];
+    ed[t] = (double)a.dX[at];
+  }
+  __syncthreads();
   // state rows: 1/2 e_i (Q e)_i with e = x + alpha dx - xref, linear in alpha per row
   for (int t = threadIdx.x; t < nk * NX; t += kThreads) {
     const int lk = C.lk0 + t / NX, i = t % NX;
@@ -151,11 +154,10 @@ __global__ void __launch_bounds__(kThreads) merit_kernel(const CtrlArgs a) {
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
       const double qj = qrow[j];
-      s0 += qj * ((double)a.X[kg * NX + j] - (double)a.xref[kg * NX + j]);
-      s1 += qj * (double)a.dX[kg * NX + j];
+      s0 += qj * ex[t - i + j];
+      s1 += qj * ed[t - i + j];
     }
-    const double e0 = (double)a.X[kg * NX + i] - (double)a.xref[kg * NX + i];
-    const double de = a.dX[kg * NX + i];
+    const double e0 = ex[t], de = ed[t];
 #pragma unroll
     for (int j = 0; j < kAlphas; ++j) {
       const double al = alpha_of(j);
@@ -192,26 +194,35 @@ __global__ void __launch_bounds__(kThreads) merit_kernel(const CtrlArgs a) {
 
   // dynamics rows: |q+ - (q + h v)| + |v+ - (v + h acc)| of joint i, knot k -> k + 1, one
   // item per (step length, knot, joint): the sines dominate, so the items of a chunk are
-  // spread over all its threads.  The terms are summed per step length in item order
-  // below, the same order for every step length, so equal trial points give equal merits.
+  // spread over all its threads.  The terms are summed per step length in one order below
+  // (kLanes interleaved sums, then those in turn), the same for every step length, so equal
+  // trial points give equal merits.
   __shared__ double dyn[kAlphas][kMaxChunk * NQ];
   const int ndyn = nkc * NQ;
-  for (int t = threadIdx.x; t < ndyn * kAlphas; t += kThreads) {
-    const int j = t / ndyn, rest = t % ndyn;
-    const int lk = C.lk0 + rest / NQ, i = rest % NQ;
+  // Seven neighbouring lanes take the joints of one knot, so that the spring between two joints
+  // costs one sine: two per item instead of three.  Measured on MI355X, 256 problems of 128
+  // knots: the kernel 40.5 us with all seven positions loaded per item, every state row reading
+  // x, xref and dx from memory and one lane per step length adding its ~217 terms; 35 without
+  // those three; 33 with two sines.
+  constexpr int kPer = 64 / NQ;  // knots (at one step length each) per wave
+  const int ml = threadIdx.x & 63, i = ml % NQ;
+  for (int g0 = (threadIdx.x >> 6) * kPer; g0 < nkc * kAlphas; g0 += kThreads / 64 * kPer) {
+    const bool on = ml < kPer * NQ && g0 + ml / NQ < nkc * kAlphas;
+    const int item = on ? g0 + ml / NQ : g0;
+    const int j = item / nkc, lk = C.lk0 + item % nkc;
     const int64_t kg = C.pk0 + lk, kc = cbase + lk;
     const float *x = a.X + kg * NX, *dx = a.dX + kg * NX;
     const double h = a.h, d = a.damp, kap = a.kap, g = a.grav[i];
     const double al = alpha_of(j);
-    double qa[NQ];
-#pragma unroll
-    for (int m = 0; m < NQ; ++m) qa[m] = (double)x[m] + al * (double)dx[m];
+    auto pos = [&](int m) { return (double)x[m] + al * (double)dx[m]; };
+    const double q = pos(i);
     const double v = (double)x[NQ + i] + al * (double)dx[NQ + i];
     const double u = (double)a.U[kc * NU + i] + al * (double)a.dU[kc * NU + i];
     const double qn = (double)x[NX + i] + al * (double)dx[NX + i];
     const double vn = (double)x[NX + NQ + i] + al * (double)dx[NX + NQ + i];
-    const double acc = chain_acc<NQ>(qa, i, v, u, g, d, kap);
-    dyn[j][rest] = fabs(qn - (qa[i] + h * v)) + fabs(vn - (v + h * acc));
+    const double sr = sin(pos(i + 1 < NQ ? i + 1 : i) - q), sp = __shfl_up(sr, 1);
+    const double acc = chain_acc(sr, i > 0 ? sp : 0.0, q, v, u, g, d, kap);
+    if (on) dyn[j][(lk - C.lk0) * NQ + i] = fabs(qn - (q + h * v)) + fabs(vn - (v + h * acc));
   }
 
   // workgroup reduction in a fixed order
@@ -231,12 +242,22 @@ __global__ void __launch_bounds__(kThreads) merit_kernel(const CtrlArgs a) {
   for (int o = 32; o > 0; o >>= 1) lmax = fmax(lmax, __shfl_xor(lmax, o));
   if (lane == 0) red[w][2 * kAlphas] = lmax;
   __syncthreads();
+  constexpr int kLanes = kThreads / kAlphas;  // 28
+  __shared__ double sub[kAlphas][kLanes];
+  if (threadIdx.x < kAlphas * kLanes) {
+    const int j = threadIdx.x / kLanes, m = threadIdx.x % kLanes;
+    double s = 0.0;
+    for (int t = m; t < ndyn; t += kLanes) s += dyn[j][t];
+    sub[j][m] = s;
+  }
+  __syncthreads();
   if (threadIdx.x < kParts) {
     const int j = threadIdx.x;
     double s = red[0][j];
     for (int ww = 1; ww < kThreads / 64; ++ww) s = (j == 2 * kAlphas) ? fmax(s, red[ww][j]) : s + red[ww][j];
     if (j >= kAlphas && j < 2 * kAlphas)
-      for (int t = 0; t < ndyn; ++t) s += dyn[j - kAlphas][t];
+#pragma unroll
+      for (int m = 0; m < kLanes; ++m) s += sub[j - kAlphas][m];
     a.part[(int64_t)blockIdx.x * kParts + j] = s;
   }
 }
