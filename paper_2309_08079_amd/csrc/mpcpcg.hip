@@ -302,6 +302,9 @@ KernelFn kernel_for(int mode) {
 // 0.92, 1.82 / 1.76, 1.86 / 1.82 us, 64 of 128 knots 2.03 / 1.93; the rest of a solve (the
 // formation has no spills) 34 / 30, 39 / 33 and 69 / 61 us.
 // The shapes that such launches use have it: 16 knots, and 4 and 8 for one short problem.
+// A launch takes it only if four like it would find room for their gangs at once (low_fits):
+// the workgroups of a gang wait for each other, a device runs up to four queues side by side
+// (HIP's default), and at two waves per SIMD a compute unit holds two workgroups, not three.
 KernelFn kernel_for(int kpw, int mode, bool low = false) {
   if (low) {
     if (kpw == 4 && mode == mpc::kForward) return mpc::pcg_kernel<kNX, kNU, 4, mpc::kForward, 0, 2>;
@@ -319,6 +322,9 @@ KernelFn kernel_for(int kpw, int mode, bool low = false) {
     default: return kernel_for<32>(mode);
   }
 }
+// `parts`: workgroups of the largest gang; `places`: workgroups resident where it runs (one XCD
+// or the device)
+bool low_fits(int parts, int places) { return parts == 1 || 4 * parts <= places; }
 bool has_low(int kpw, int mode) { return kernel_for(kpw, mode, true) != kernel_for(kpw, mode); }
 
 bool valid_kpw(int k) {
@@ -416,7 +422,7 @@ int launch_single(mpcpcg_ctx *c, KArgs &a, int N, int kpw, int mode, hipStream_t
   bool low = has_low(kpw, mode);
   if (low) {
     if ((st = capacity(c, kpw, mode, &cap, true))) return st;
-    low = (a.one_xcd ? 8 * g : g) <= cap;
+    low = low_fits(g, a.one_xcd ? cap / 8 : cap);
   }
   hipLaunchKernelGGL(kernel_for(kpw, mode, low), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
   HIPCHK(c, hipGetLastError());
@@ -542,7 +548,9 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
     return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
   }
   for (int m = 0; m < 4; ++m) s->grid[m] = std::min(s->ntasks, cap);
-  s->low[0] = s->ntasks <= cap_low;
+  int max_parts = 0;
+  for (const auto &d : sorted) max_parts = std::max(max_parts, d.nparts);
+  s->low[0] = s->ntasks <= cap_low && low_fits(max_parts, cap_low);
   // Per-XCD lists: workgroups are dispatched to the eight XCDs in turn, so a grid of 8 m
   // workgroups puts m on each (at most cap / 8 of them resident).  When every gang fits in
   // cap / 8, each problem (in longest-first order) goes to the XCD with the least work so
@@ -551,8 +559,6 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
   // XCD's L2.  A batch of fewer than eight problems leaves some lists empty; the grid gives
   // every XCD as many workgroups as the longest list has tasks, up to cap / 8.
   constexpr int kXcds = 8;
-  int max_parts = 0;
-  for (const auto &d : sorted) max_parts = std::max(max_parts, d.nparts);
   if (c->xcd_ok && cap % kXcds == 0 && max_parts <= cap / kXcds) {
     std::vector<std::vector<int>> lists(kXcds);
     std::vector<int64_t> load(kXcds, 0);
@@ -582,7 +588,7 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
     int longest = 0;
     for (int x = 0; x < kXcds; ++x) longest = std::max(longest, xoff[x + 1] - xoff[x]);
     s->xgrid = kXcds * std::min(longest, cap / kXcds);
-    s->low[1] = longest <= cap_low / kXcds;
+    s->low[1] = longest <= cap_low / kXcds && low_fits(max_parts, cap_low / kXcds);
   }
   make_room(c, c->sched, true);
   *out = c->sched.put(key, std::move(s));
@@ -1952,7 +1958,7 @@ int mpcpcg_solve_noalloc(const mpcpcg_problem *p, const mpcpcg_opts *o, float *l
   // the placement rule of mpcpcg_solve: a gang that fits one XCD's share runs there
   a.one_xcd = (d.xcd_ok && g > 1 && 8 * g <= d.cap[ki]) ? 1 : 0;
   a.l2x = a.one_xcd;
-  const bool low = has_low(kpw, mpc::kForward) && (a.one_xcd ? 8 * g : g) <= d.cap_low[ki];
+  const bool low = has_low(kpw, mpc::kForward) && low_fits(g, a.one_xcd ? d.cap_low[ki] / 8 : d.cap_low[ki]);
   hipLaunchKernelGGL(kernel_for(kpw, mpc::kForward, low), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return na_fail(MPCPCG_EHIP, "launch failed: %s", hipGetErrorString(e));
