@@ -140,13 +140,15 @@ __device__ __forceinline__ void elim_range(double (&a)[L], double c) {
 }
 
 // Gauss-Jordan elimination of the 14 pivots of half H from the rows of that half: columns
-// FROM.. of a and all of b; the other half's rows are left as they are.
+// FROM.. of a and all of b; the other half's rows are left as they are.  The pivots'
+// reciprocals are rounded as a division's (two Newton steps): 28 pivots a block and up to three
+// blocks a chunk and level follow one another, and one step costs up to five bits of each.
 template <int H, int W>
 __device__ __forceinline__ void eliminate_half(double (&a)[kN], double (&b)[W], int lane, int half, bool &pd) {
   constexpr int O = H * kH;
   const bool on = half == H;
   double piv = bc<0>(a[O]);
-  double d = rcp_f64(piv);
+  double d = rcp_f64<2>(piv);
   double mine = 1.0;
   static_for<0, kH>([&](auto kk) MPC_INLINE {
     constexpr int k = decltype(kk)::value;
@@ -160,8 +162,9 @@ __device__ __forceinline__ void eliminate_half(double (&a)[kN], double (&b)[W], 
       d = __builtin_amdgcn_rcp(piv);
     }
     elim_range<k, 0, W>(b, c);
-    if constexpr (k + 1 < kH) d = __builtin_fma(d, __builtin_fma(-piv, d, 1.0), d);
+    if constexpr (k + 1 < kH) d = newton_f64(piv, d);
     elim_range<k, (k + 1 < kH ? first + 1 : first), kN>(a, c);
+    if constexpr (k + 1 < kH) d = newton_f64(piv, d);
   });
   pd = pd && (!on || lane >= kH || mine > 0.0);
   if constexpr (H == 0)

@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
       R[j] = next ? (double)s0[ru * NU + j] : (j == ru ? 1.0 : 0.0);
       B[j] = (double)s0[NU * NU + r * NU + j];
     }
-    gj_inverse<NU>(R, lane, &pd);
+    gj_inverse<NU, 2>(R, lane, &pd);
     mm_nn<NU, NU>(B, R, U);
     pair::mm_nt_add<NU>(U, B, G);
     p1 -= mpc::row_dot<NU>(U, next && rv ? (double)rv[cb * NU + ru] : 0.0);
@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(kPairWaves * 64) wide_epilogue(const WArgs a) 
 #pragma unroll
     for (int j = 0; j < NU; ++j) R[j] = next ? (double)a.R[cb * NU * NU + c * NU + j] : (j == c ? 1.0 : 0.0);
     u = -((next && rv ? (double)rv[cb * NU + c] : 0.0) + pair::row_dot(M, ln));
-    gj_solve<NU>(R, u, lane);
+    gj_solve<NU, 2>(R, u, lane);
   }
   const bool outu = live && next && lane < NU && L.half == 0;
   if (!adj) {

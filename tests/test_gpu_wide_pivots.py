@@ -1,0 +1,47 @@
+"""GPU test of the 28-state pivots: their reciprocals are as accurate as a division.  The FP32
+outputs hide a few missing bits, so the test takes inputs that bring them out.
+
+One knot, Q diagonal, |q| 2^30 times Q x0: lambda = (Q^-1 q + x0) / Q^-1 and dx = Q^-1 (lambda
+- q), which is x0 again, so the relative error of lambda appears 2^30 times larger in dx.  In
+units of u = 2^-53 lambda carries the roundings of a product, a sum, a reciprocal (1 u when
+rounded to nearest, 2 u allowed here) and a product: 5 u |q|, and 5 u |q| / Q in dx; dx itself
+is rounded to FP32 (2^-24)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+NX, NU = 28, 14
+
+
+def context():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_08079_amd.mpcpcg import Context
+    return Context(NX, NU, max_total_knots=256, max_batch=256)
+
+
+def test_reciprocals_of_the_pivots():
+    from paper_2309_08079_amd.mpcpcg import stats_to_numpy, to_device
+    g = np.random.default_rng(28)
+    B = 128
+    u = 2.0 ** -53
+    Qd = g.uniform(0.25, 4.0, (B, NX)).astype(np.float32)
+    q = (g.uniform(0.5, 1.0, (B, NX)) * g.choice([-1.0, 1.0], (B, NX))).astype(np.float32)
+    x0 = (g.uniform(0.5, 1.0, (B, NX)) * 2.0 ** -30).astype(np.float32)
+    Q = np.zeros((B, NX, NX), dtype=np.float32)
+    Q[:, np.arange(NX), np.arange(NX)] = Qd
+    d = to_device(dict(Q=Q, q=q, x0=x0, R=np.zeros((0, NU, NU), np.float32), A=np.zeros((0, NX, NX), np.float32),
+                       B=np.zeros((0, NX, NU), np.float32), r=np.zeros((0, NU), np.float32),
+                       e=np.zeros((0, NX), np.float32)))
+    c = context()
+    c.mpcpcg_set_method("factor")
+    out = c.mpcpcg_solve_batched(d, np.arange(B + 1))
+    torch.cuda.synchronize()
+    assert (stats_to_numpy(out["stats"])["status"] == 0).all()
+    err = np.abs(out["dx"].cpu().numpy().astype(np.float64) - x0)
+    tol = 5 * u * np.abs(q.astype(np.float64)) / Qd + 2.0 ** -24 * np.abs(x0) * 1.01
+    worst = (err / tol).max()
+    c.close()
+    assert worst <= 1.0, worst
