@@ -232,8 +232,8 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
   }
 }
 
-// S_bb, the right-hand side and D_b^-1 of knot b from the shares (D_0^-1 = S_00^-1 = Q_0 up to
-// rounding, like every other knot).
+// S_bb, the right-hand side and D_b^-1 of knot b from the shares (D_0^-1 = S_00^-1 is Q_0
+// itself).
 template <int NX>
 __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_theta(const WArgs a) {
   constexpr int MM = NX * NX;
@@ -257,7 +257,10 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
 #pragma unroll
     for (int j = 0; j < NX; ++j) S1[j * NX] = D[j];
   }
-  pair::gj_solve<NX>(D, I, L.lane, L.half, pd);
+  if (__any(kd.b > 0)) pair::gj_solve<NX>(D, I, L.lane, L.half, pd);
+  if (kd.b == 0)
+#pragma unroll
+    for (int j = 0; j < NX; ++j) I[j] = (double)a.Q[kb * MM + r * NX + j];
   if (live && L.rowv)
 #pragma unroll
     for (int j = 0; j < NX; ++j) a.Dinv[kb * MM + j * NX + r] = I[j];

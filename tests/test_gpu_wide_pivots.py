@@ -1,15 +1,21 @@
-"""GPU test of the 28-state pivots: their reciprocals are as accurate as a division.  The FP32
-outputs hide a few missing bits, so the test takes inputs that bring them out.
+"""GPU tests of the 28-state pivots: their reciprocals are as accurate as a division, and the
+preconditioner's block of the first knot is that knot's Q itself.  The FP32 outputs hide a few
+missing bits, so both tests take inputs that bring them out.
 
 One knot, Q diagonal, |q| 2^30 times Q x0: lambda = (Q^-1 q + x0) / Q^-1 and dx = Q^-1 (lambda
 - q), which is x0 again, so the relative error of lambda appears 2^30 times larger in dx.  In
 units of u = 2^-53 lambda carries the roundings of a product, a sum, a reciprocal (1 u when
 rounded to nearest, 2 u allowed here) and a product: 5 u |q|, and 5 u |q| / Q in dx; dx itself
-is rounded to FP32 (2^-24)."""
+is rounded to FP32 (2^-24).
+
+Q_0 = (1 - d) 1 1^T + d I with d = 2^-22, exact in FP32, condition number 1.2e8: inverted twice
+it comes back with an error of ~1e8 roundings, some of FP32's last places."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
+
+from paper_2309_08079_amd import synth
 
 pytestmark = pytest.mark.gpu
 NX, NU = 28, 14
@@ -45,3 +51,16 @@ def test_reciprocals_of_the_pivots():
     worst = (err / tol).max()
     c.close()
     assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("N", [1, 2, 5])
+def test_first_block_of_the_preconditioner_is_the_first_cost(N):
+    from paper_2309_08079_amd.mpcpcg import to_device
+    p = synth.problem(N, nx=NX, nu=NU, seed=70 + N)
+    d = np.float32(2.0 ** -22)
+    p["Q"][0] = np.float32(1.0) - d
+    p["Q"][0][np.arange(NX), np.arange(NX)] = 1.0
+    c = context()
+    P = c.mpcpcg_form_schur(to_device(p))[1].cpu().numpy()
+    c.close()
+    assert np.array_equal(P[0, 1], p["Q"][0])
