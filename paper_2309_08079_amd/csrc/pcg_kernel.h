@@ -1147,7 +1147,8 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           const double pSp = del - beta * gam * ra;
           if (LEAD) alpha = gam / pSp;  // (beside the test: nothing else runs in this wave)
           // one test for every way out, the reason afterwards
-          const bool above = it == 0 ? gam > tau : gam >= tau;
+          // (a threshold that is not a number, infinity times 0, ends nothing here)
+          const bool above = it == 0 ? !(gam <= tau) : !(gam < tau);
           if (!(finite & above & (it < max_iter) & (pSp > 0.0) & (pSp < __builtin_inf()))) {
             end = true;
             if (!finite)
