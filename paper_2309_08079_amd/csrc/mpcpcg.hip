@@ -16,6 +16,7 @@
 
 #include "mpcpcg.h"
 #include "pcg_kernel.h"
+#include "residency.h"
 #include "ctrl_kernels.h"
 #include "tri_kernel.h"
 #include "wide_kernels.h"
@@ -296,15 +297,12 @@ KernelFn kernel_for(int mode) {
   }
 }
 
-// `low` asks for the form with two waves per SIMD and Phi^-1 in registers, for launches whose
-// workgroups are all resident at that occupancy.  Measured on MI355X per iteration, three waves
-// per SIMD and Phi^-1 in LDS / two and in registers: one problem of 16, 128, 512 knots 0.97 /
-// 0.92, 1.82 / 1.76, 1.86 / 1.82 us, 64 of 128 knots 2.03 / 1.93; the rest of a solve (the
-// formation has no spills) 34 / 30, 39 / 33 and 69 / 61 us.
-// The shapes that such launches use have it: 16 knots, and 4 and 8 for one short problem.
-// A launch takes it only if four like it would find room for their gangs at once (low_fits):
-// the workgroups of a gang wait for each other, a device runs up to four queues side by side
-// (HIP's default), and at two waves per SIMD a compute unit holds two workgroups, not three.
+// `low` asks for the form with two waves per SIMD and Phi^-1 in registers, for launches of
+// one-part problems whose workgroups are all resident at that occupancy (residency.h).  Measured
+// on MI355X, one problem of 16 knots, three waves per SIMD and Phi^-1 in LDS / two and in
+// registers: 0.97 / 0.92 us per iteration, 34 / 30 us for the rest of the solve (the formation
+// has no spills).  The shapes that such launches use have it: 16 knots, and 4 and 8 for one short
+// problem.
 KernelFn kernel_for(int kpw, int mode, bool low = false) {
   if (low) {
     if (kpw == 4 && mode == mpc::kForward) return mpc::pcg_kernel<kNX, kNU, 4, mpc::kForward, 0, 2>;
@@ -322,9 +320,6 @@ KernelFn kernel_for(int kpw, int mode, bool low = false) {
     default: return kernel_for<32>(mode);
   }
 }
-// `parts`: workgroups of the largest gang; `places`: workgroups resident where it runs (one XCD
-// or the device)
-bool low_fits(int parts, int places) { return parts == 1 || 4 * parts <= places; }
 bool has_low(int kpw, int mode) { return kernel_for(kpw, mode, true) != kernel_for(kpw, mode); }
 
 bool valid_kpw(int k) {
@@ -419,11 +414,7 @@ int launch_single(mpcpcg_ctx *c, KArgs &a, int N, int kpw, int mode, hipStream_t
   // that XCD's L2
   a.one_xcd = (c->xcd_ok && c->xcd_pin && g > 1 && 8 * g <= cap) ? 1 : 0;
   a.l2x = a.one_xcd;
-  bool low = has_low(kpw, mode);
-  if (low) {
-    if ((st = capacity(c, kpw, mode, &cap, true))) return st;
-    low = low_fits(g, a.one_xcd ? cap / 8 : cap);
-  }
+  const bool low = has_low(kpw, mode) && mpc::two_waves_form(g, g, 1);
   hipLaunchKernelGGL(kernel_for(kpw, mode, low), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
   HIPCHK(c, hipGetLastError());
   return MPCPCG_OK;
@@ -550,7 +541,7 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
   for (int m = 0; m < 4; ++m) s->grid[m] = std::min(s->ntasks, cap);
   int max_parts = 0;
   for (const auto &d : sorted) max_parts = std::max(max_parts, d.nparts);
-  s->low[0] = s->ntasks <= cap_low && low_fits(max_parts, cap_low);
+  s->low[0] = mpc::two_waves_form(max_parts, s->ntasks, cap_low);
   // Per-XCD lists: workgroups are dispatched to the eight XCDs in turn, so a grid of 8 m
   // workgroups puts m on each (at most cap / 8 of them resident).  When every gang fits in
   // cap / 8, each problem (in longest-first order) goes to the XCD with the least work so
@@ -588,7 +579,7 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
     int longest = 0;
     for (int x = 0; x < kXcds; ++x) longest = std::max(longest, xoff[x + 1] - xoff[x]);
     s->xgrid = kXcds * std::min(longest, cap / kXcds);
-    s->low[1] = longest <= cap_low / kXcds && low_fits(max_parts, cap_low / kXcds);
+    s->low[1] = mpc::two_waves_form(max_parts, longest, cap_low / kXcds);
   }
   make_room(c, c->sched, true);
   *out = c->sched.put(key, std::move(s));
@@ -1195,7 +1186,7 @@ struct NaDevice {
   std::once_flag once;
   int rc = MPCPCG_OK;
   unsigned char *ptr = nullptr;
-  int cap[kNumKpw] = {}, cap_low[kNumKpw] = {};  // co-resident workgroups per shape of kKpwChoices
+  int cap[kNumKpw] = {};  // co-resident workgroups per shape of kKpwChoices
   int xcd_ok = 0;
   int64_t spin = 0;
 };
@@ -1262,13 +1253,6 @@ void na_setup(NaDevice &d, int dev) {
       return;
     }
     d.cap[i] = resident_per_cu(nb, k) * prop.multiProcessorCount;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, reinterpret_cast<const void *>(kernel_for(k, mpc::kForward, true)), k * mpc::kGroup, 0) != hipSuccess) {
-      (void)hipGetLastError();
-      d.rc = na_fail(MPCPCG_EHIP, "occupancy query failed on device %d", dev);
-      return;
-    }
-    d.cap_low[i] = resident_per_cu(nb, k, true) * prop.multiProcessorCount;
   }
 }
 
@@ -1958,7 +1942,7 @@ int mpcpcg_solve_noalloc(const mpcpcg_problem *p, const mpcpcg_opts *o, float *l
   // the placement rule of mpcpcg_solve: a gang that fits one XCD's share runs there
   a.one_xcd = (d.xcd_ok && g > 1 && 8 * g <= d.cap[ki]) ? 1 : 0;
   a.l2x = a.one_xcd;
-  const bool low = has_low(kpw, mpc::kForward) && low_fits(g, a.one_xcd ? d.cap_low[ki] / 8 : d.cap_low[ki]);
+  const bool low = has_low(kpw, mpc::kForward) && mpc::two_waves_form(g, g, 1);
   hipLaunchKernelGGL(kernel_for(kpw, mpc::kForward, low), dim3(a.one_xcd ? 8 * g : g), dim3(kpw * mpc::kGroup), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return na_fail(MPCPCG_EHIP, "launch failed: %s", hipGetErrorString(e));
