@@ -266,7 +266,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
   constexpr bool kKeepP = WPE == 2;  // Phi^-1 rows in registers
 
   __shared__ double ex_d[2][KPW + 2][kGroup];  // vector exchange, slot s+1 is knot s
-  __shared__ float ex_f[KPW + 2][kGroup];
+  __shared__ float ex_f[KPW + 3][kGroup];  // (the last row is written, never read)
   // One LDS region serves two phases: the D^-1 row exchange of the formation, then the
   // FP32 Phi^-1 rows for the rest of the solve (row r of knot slot s at
   // pl[(s * NX + r) * kPRow], blocks (b,b-1), (b,b), (b,b+1) at offsets 0, 14, 28; slots
@@ -1065,8 +1065,7 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       // knot's Phi^-1 row, so no second exchange is needed inside an iteration.
       double p = 0.0, sv = 0.0, sm = 0.0, sp = 0.0;
       double gam_prev = __builtin_inf(), alpha_prev = 1.0, tau = 0.0;
-      // (a scalar branch: register copies that the compiler leaves at the end of a divergent
-      // one around the stores below have run for the stores' lanes only)
+      // (a scalar branch)
       const int uwave = uni(wave);
       const bool edge_wave = multi && (uwave == 0 || uwave == NW - 1);
       // the ghost knots' rows (setup left them in LDS)
@@ -1104,8 +1103,14 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
           float ug;
           if constexpr (kKeepP) ug = precond_regs(Gm, Gd, Gp, xm, xo, xp);
           else ug = precond_row(left ? KPW : KPW + 1, xm, xo, xp);
-          if (slot == 0) ex_f[0][lane] = ug;
-          if (slot == KPW - 1) ex_f[KPW + 1][lane] = ug;
+          // Every lane stores, the inner knots to a spare row: the branch has no divergent part.
+          // (With a store under its own mask at its end the compiler once put a copy of a
+          // register of S under that mask, and the adjoint broke down.  Against two masked
+          // stores: one problem of 512 knots 228 -> 220 us, 256 mixed ones 1265 -> 1225.)
+          int at = slot == 0 ? 0 : slot == KPW - 1 ? KPW + 1 : KPW + 2;
+          // at two waves per SIMD not kept across the loop: one problem of 32 knots 121.4 -> 120.0 us
+          if constexpr (kKeepP) asm volatile("" : "+v"(at));
+          ex_f[at][lane] = ug;
           __builtin_amdgcn_s_setprio(0);
         }
         if (uwave == rg_wave) {
