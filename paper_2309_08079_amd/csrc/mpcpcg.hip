@@ -135,11 +135,11 @@ struct CtrlGraph {
 struct WideSchedule {
   DevArrays mem;
   mpc::wide::KnotDesc *d_knots = nullptr;
-  mpc::wide::ProbDescW *d_probs = nullptr;
   int nknots = 0, nprobs = 0, maxN = 0;
-  // chunks of the direct solve, level by level until one row per problem is left
+  // chunks of the direct solve, level by level, a problem's until one row of it is left
   std::vector<int> nchunks;
   std::vector<mpc::wide::WChunk *> d_chunks;
+  mpc::wide::WRoot *d_roots = nullptr;
   // tasks of the gang PCG: (problem, part) longest problem first, KW knots per part
   ProbDesc *d_gprobs = nullptr;
   Task *d_gtasks = nullptr;
@@ -223,10 +223,9 @@ struct mpcpcg_ctx {
   // generic path (nx = 28)
   bool wide = false;
   double *w_S = nullptr, *w_Dinv = nullptr, *w_rhs = nullptr, *w_rhs_prev = nullptr, *w_Qinv = nullptr;
-  double *w_dir = nullptr;  // direct solve (on first use)
   double *w_lam = nullptr;  // lambda of the factorisation path
-  int *w_flag = nullptr;    // per-problem breakdown flags of the factorisation path
-  float *w_P = nullptr;
+  int *w_flag = nullptr;    // per-problem breakdown flags of the factorisation path (0 between solves)
+  float *w_P = nullptr;     // (behind w_Dinv, in one allocation)
   void *w_tws = nullptr;  // tagged words of the gang PCG, one per task
   Gang *w_gang = nullptr;
   int *w_queue = nullptr;
@@ -833,16 +832,27 @@ constexpr int kWKnots = mpc::wide::kGangKnots;  // knots per workgroup of the ga
 
 int64_t wide_max_tasks(const mpcpcg_ctx *c) { return c->max_knots / kWKnots + c->max_batch; }
 
+// Workspace of the direct solve: the preconditioner's blocks D^-1 and Phi^-1 (2.5 blocks of 28 x
+// 28 doubles a knot), which it does not form, hold z of every knot and the separators; -W^T and
+// H^T of an eliminated row take the place of that row's diagonal block and, of a knot, of
+// S_{b,b+1}.  A problem of n knots has f(n) = r + f(r) separators, r = ceil(n / 4), f(1) = 0: at
+// most 3 n / 5 of them (n = 5; by induction above), at 3 blocks and 4 vectors each 1.9 blocks a
+// knot.
+constexpr int64_t kWBlock = (int64_t)kWNX * kWNX;
+constexpr int64_t kWSlot = 3 * kWBlock + 4 * kWNX;  // doubles per separator
+int64_t wide_slots(int64_t knots) { return 3 * knots / 5; }
+static_assert(kWNX * 5 + 3 * kWSlot <= 5 * (2 * kWBlock + kWBlock / 2), "z and the separators fit the preconditioner's blocks");
+
 int wide_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, WideSchedule **out) {
   if (WideSchedule *hit = c->wsched.get(off)) { *out = hit; return MPCPCG_OK; }
   const int B = (int)off.size() - 1;
   std::vector<mpc::wide::KnotDesc> kd;
-  std::vector<mpc::wide::ProbDescW> pd(B);
+  std::vector<int> horizon(B);
   int maxN = 0;
   for (int b = 0; b < B; ++b) {
     const int N = (int)(off[b + 1] - off[b]);
     maxN = std::max(maxN, N);
-    pd[b] = mpc::wide::ProbDescW{off[b], N, b};
+    horizon[b] = N;
     for (int k = 0; k < N; ++k) kd.push_back(mpc::wide::KnotDesc{off[b], N, k, b, 0});
   }
   auto w = std::make_unique<WideSchedule>();
@@ -854,13 +864,13 @@ int wide_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, WideSchedule *
   {
     std::vector<int> order(B);
     for (int b = 0; b < B; ++b) order[b] = b;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return pd[x].N > pd[y].N; });
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return horizon[x] > horizon[y]; });
     std::vector<ProbDesc> gp(B);
     std::vector<Task> gt;
     for (int b : order) {
       ProbDesc d;
       d.k0 = off[b];
-      d.N = pd[b].N;
+      d.N = horizon[b];
       d.nparts = (d.N + kWKnots - 1) / kWKnots;
       d.t0 = (int32_t)gt.size();
       d.id = b;
@@ -891,7 +901,7 @@ int wide_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, WideSchedule *
       for (int b : order) {
         const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
         lists[x].push_back(b);
-        load[x] += pd[b].N;
+        load[x] += horizon[b];
       }
       std::vector<ProbDesc> xp(gp);
       std::vector<Task> xt;
@@ -915,14 +925,21 @@ int wide_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, WideSchedule *
   }
   {
     std::vector<mpc::wide::WChunk> rows(B);  // the problems' rows at the current level
-    for (int b = 0; b < B; ++b) rows[b] = mpc::wide::WChunk{off[b], pd[b].N, b, 0, 0};
+    std::vector<mpc::wide::WRoot> roots(B);
+    int64_t slots = 0;  // separators so far
+    for (int b = 0; b < B; ++b) {
+      rows[b] = mpc::wide::WChunk{off[b], horizon[b], b, 0, 0};
+      roots[b] = mpc::wide::WRoot{off[b], b, 1};
+    }
     for (int n = maxN; n > 1; n = (n + 3) / 4) {
       std::vector<mpc::wide::WChunk> ch;
       for (auto &p : rows) {
-        const int first = (int)ch.size();
-        for (int k = 0; k < p.N; k += 4) ch.push_back(mpc::wide::WChunk{p.k0, p.N, p.id, k, (int32_t)ch.size()});
+        if (p.N == 1) continue;
+        const int64_t first = slots;
+        for (int k = 0; k < p.N; k += 4) ch.push_back(mpc::wide::WChunk{p.k0, p.N, p.id, k, (int32_t)slots++});
         p.k0 = first;
         p.N = (p.N + 3) / 4;
+        roots[p.id] = mpc::wide::WRoot{first, p.id, 0};  // (once N is 1)
       }
       w->nchunks.push_back((int)ch.size());
       w->d_chunks.push_back(w->mem.upload(ch.data(), ch.size()));
@@ -931,10 +948,11 @@ int wide_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, WideSchedule *
         return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
       }
     }
+    if (slots > wide_slots(c->max_knots)) return fail(c, MPCPCG_EINVAL, "batch exceeds the factorisation workspace");
+    w->d_roots = w->mem.upload(roots.data(), roots.size());
   }
   w->d_knots = w->mem.upload(kd.data(), kd.size());
-  w->d_probs = w->mem.upload(pd.data(), pd.size());
-  if (!w->d_knots || !w->d_probs) {
+  if (!w->d_knots || !w->d_roots) {
     (void)hipGetLastError();
     return fail(c, MPCPCG_ENOMEM, "cannot allocate the schedule of a %d-problem batch", B);
   }
@@ -954,79 +972,37 @@ mpc::wide::WArgs wide_args(mpcpcg_ctx *c, const mpcpcg_problem *p, const mpcpcg_
   return a;
 }
 
-// Rows of level l of the 28-state direct solve: a quarter of the level before and one more per
-// problem at most (level 0: knots).
-int64_t wide_level_rows(const mpcpcg_ctx *c, int l) {
-  int64_t n = c->max_knots;
-  for (int i = 0; i < l; ++i) n = n / 4 + c->max_batch;
-  return n;
-}
-int wide_levels(int64_t nmax) {
-  int l = 0;
-  for (; nmax > 1; nmax = (nmax + 3) / 4) ++l;
-  return l;
-}
-
-// workspace of the direct solve: -W^T | H^T and z of every row that a level eliminates, the
-// systems of the levels above 0, one flag per problem (kept at 0 between solves)
-int ensure_wide_direct(mpcpcg_ctx *c) {
-  if (c->w_dir) return MPCPCG_OK;
-  const size_t MM = (size_t)kWNX * kWNX;
-  size_t n = 2;  // (a context of one knot has no levels)
-  const int levels = wide_levels(c->max_knots);
-  for (int l = 0; l <= levels; ++l) {
-    const size_t rows = (size_t)wide_level_rows(c, l);
-    if (l < levels) n += rows * (2 * MM + kWNX);
-    if (l > 0) n += rows * (3 * MM + 3 * kWNX);
-  }
-  const size_t fb = sizeof(int) * (size_t)c->max_batch;
-  if (hipMalloc(&c->w_dir, sizeof(double) * n) != hipSuccess) {
-    (void)hipGetLastError();
-    c->w_dir = nullptr;
-    return fail(c, MPCPCG_ENOMEM, "cannot allocate the factorisation workspace (%lld knots)", (long long)c->max_knots);
-  }
-  HIPCHK(c, hipMemset(c->w_flag, 0, fb));
-  HIPCHK(c, hipDeviceSynchronize());
-  return MPCPCG_OK;
-}
-
 int wide_direct(mpcpcg_ctx *c, WideSchedule *w, const mpc::wide::WArgs &a, hipStream_t s) {
   namespace mw = mpc::wide;
-  if (int st = ensure_wide_direct(c)) return st;
-  const int64_t MM = (int64_t)kWNX * kWNX;
+  const int64_t MM = kWBlock;
   const int levels = (int)w->nchunks.size();
-  double *p = c->w_dir;
+  double *p = c->w_Dinv;  // (w_P follows)
   auto take = [&](int64_t n) { double *q = p; p += n; return q; };
-  std::vector<mw::WLevel> lev(levels + 1);
-  for (int l = 0; l <= levels; ++l) {
-    mw::WLevel &v = lev[l];
-    std::memset(&v, 0, sizeof v);
-    const int64_t rows = wide_level_rows(c, l);
-    if (l == 0) {
-      v.d0 = a.Qinv; v.s0 = MM;
-      v.d1 = a.S + MM; v.s1 = 3 * MM;
-      v.l = a.S; v.sl = 3 * MM;
-      v.y0 = a.rhs; v.y1 = a.rhs_prev; v.x = a.lamw;
-    } else {
-      v.d0 = take(rows * MM); v.d1 = take(rows * MM); v.l = take(rows * MM);
-      v.s0 = v.s1 = v.sl = MM;
-      v.y0 = take(rows * kWNX); v.y1 = take(rows * kWNX); v.x = take(rows * kWNX);
-    }
-    if (l < levels) { v.ph = take(rows * 2 * MM); v.z = take(rows * kWNX); }
-  }
+  mw::WLevel knots, seps;
+  knots.d0 = a.Qinv; knots.s0 = MM;
+  knots.d1 = a.S + MM; knots.s1 = 3 * MM;
+  knots.l = a.S; knots.sl = 3 * MM;
+  knots.y0 = a.rhs; knots.y1 = a.rhs_prev; knots.x = a.lamw;
+  knots.ph = a.S + MM; knots.sp = 3 * MM;
+  knots.z = take(c->max_knots * kWNX);
+  const int64_t slots = wide_slots(c->max_knots);
+  seps.d0 = take(2 * MM * slots); seps.d1 = seps.d0 + MM;
+  seps.s0 = seps.s1 = 2 * MM;
+  seps.l = take(MM * slots); seps.sl = MM;
+  seps.ph = seps.d0; seps.sp = 2 * MM;
+  seps.y0 = take(kWNX * slots); seps.y1 = take(kWNX * slots);
+  seps.x = take(kWNX * slots); seps.z = take(kWNX * slots);
   mw::WDirect d;
   d.flag = c->w_flag;
+  d.out = seps;
   for (int l = 0; l < levels; ++l) {
-    d.chunks = w->d_chunks[l]; d.in = lev[l]; d.out = lev[l + 1];
+    d.chunks = w->d_chunks[l]; d.in = l ? seps : knots;
     hipLaunchKernelGGL((mw::wide_eliminate<kWNX, 4>), dim3(w->nchunks[l]), dim3(4 * 64), 0, s, d);
   }
-  const dim3 root_grid((w->nprobs + 1) / 2);
-  if (levels == 0)
-    hipLaunchKernelGGL((mw::wide_root<kWNX, true>), root_grid, dim3(64), 0, s, a, lev[0], w->d_probs, w->nprobs, c->w_flag);
-  else
-    hipLaunchKernelGGL((mw::wide_root<kWNX, false>), root_grid, dim3(64), 0, s, a, lev[levels], w->d_probs, w->nprobs, c->w_flag);
+  hipLaunchKernelGGL(mw::wide_root<kWNX>, dim3((w->nprobs + 1) / 2), dim3(64), 0, s, a, knots, seps, w->d_roots, w->nprobs,
+                     c->w_flag);
   for (int l = levels - 1; l >= 0; --l) {
-    d.chunks = w->d_chunks[l]; d.in = lev[l]; d.out = lev[l + 1];
+    d.chunks = w->d_chunks[l]; d.in = l ? seps : knots;
     hipLaunchKernelGGL(mw::wide_back<kWNX>, dim3(w->nchunks[l]), dim3(128), 0, s, d);
   }
   HIPCHK(c, hipGetLastError());
@@ -1040,9 +1016,7 @@ int wide_run(mpcpcg_ctx *c, const std::vector<int64_t> &off, mpc::wide::WArgs &a
   int st = wide_schedule(c, off, &w);
   if (st) return st;
   a.knots = w->d_knots;
-  a.probs = w->d_probs;
   a.nknots = w->nknots;
-  a.nprobs = w->nprobs;
   const bool fac = !form_only && use_factor(c, off, a.warm != 0);
   a.direct = fac ? 1 : 0;
   a.need_up = fac ? 0 : 1;
@@ -1292,8 +1266,8 @@ int mpcpcg_create(mpcpcg_ctx **out, int32_t nx, int32_t nu, int64_t max_total_kn
   if (wide) {
     const size_t MM = (size_t)nx * nx;
     if (hipMalloc(&c->w_S, sizeof(double) * K * 3 * MM) != hipSuccess ||
-        hipMalloc(&c->w_Dinv, sizeof(double) * K * MM) != hipSuccess ||
-        hipMalloc(&c->w_P, sizeof(float) * K * 3 * MM) != hipSuccess ||
+        // (D^-1, then Phi^-1: one piece for the direct solve)
+        hipMalloc(&c->w_Dinv, sizeof(double) * K * MM + sizeof(float) * K * 3 * MM) != hipSuccess ||
         hipMalloc(&c->w_rhs, sizeof(double) * K * nx) != hipSuccess ||
         hipMalloc(&c->w_rhs_prev, sizeof(double) * K * nx) != hipSuccess ||
         hipMalloc(&c->w_lam, sizeof(double) * K * nx) != hipSuccess ||
@@ -1305,7 +1279,9 @@ int mpcpcg_create(mpcpcg_ctx **out, int32_t nx, int32_t nu, int64_t max_total_kn
       mpcpcg_destroy(c.release());
       return MPCPCG_ENOMEM;
     }
-    if (hipMemset(c->w_tws, 0, sizeof(mpc::wide::WTag) * (size_t)wide_max_tasks(c.get())) != hipSuccess ||
+    c->w_P = reinterpret_cast<float *>(c->w_Dinv + K * MM);
+    if (hipMemset(c->w_flag, 0, sizeof(int) * (size_t)max_batch) != hipSuccess ||
+        hipMemset(c->w_tws, 0, sizeof(mpc::wide::WTag) * (size_t)wide_max_tasks(c.get())) != hipSuccess ||
         hipMemset(c->w_gang, 0, sizeof(Gang) * (size_t)max_batch) != hipSuccess ||
         hipMemset(c->w_queue, 0, 16 * sizeof(int)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
       mpcpcg_destroy(c.release());
@@ -1351,7 +1327,7 @@ int mpcpcg_destroy(mpcpcg_ctx *c) {
   if (c->ls_part) (void)hipFree(c->ls_part);
   if (c->cs_ws) (void)hipFree(c->cs_ws);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  for (void *p : {(void *)c->w_S, (void *)c->w_Dinv, (void *)c->w_P, (void *)c->w_rhs, (void *)c->w_rhs_prev, (void *)c->w_dir, (void *)c->w_lam, (void *)c->w_Qinv,
+  for (void *p : {(void *)c->w_S, (void *)c->w_Dinv, (void *)c->w_rhs, (void *)c->w_rhs_prev, (void *)c->w_lam, (void *)c->w_Qinv,
                   (void *)c->w_flag, c->w_tws, (void *)c->w_gang, (void *)c->w_queue})
     if (p) (void)hipFree(p);
   delete c;

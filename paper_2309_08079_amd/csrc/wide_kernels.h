@@ -31,12 +31,6 @@ struct KnotDesc {    // one per knot of the packed batch
   int32_t pad;
 };
 
-struct ProbDescW {
-  int64_t k0;
-  int32_t N;
-  int32_t id;
-};
-
 struct WArgs {
   const float *Q, *R, *A, *B, *q, *r, *x0, *e;
   const float *lam_in, *dx_in, *du_in, *gl, *gx, *gu;
@@ -45,8 +39,7 @@ struct WArgs {
   float *dQ, *dR, *dA, *dB, *dq, *dr, *dx0, *de, *dgamma;
   float *S_out, *P_out, *gam_out;
   const KnotDesc *knots;
-  const ProbDescW *probs;
-  int32_t nknots, nprobs;
+  int32_t nknots;
   // workspace (FP64 unless noted; blocks by columns, so that the lanes that own a block's rows
   // move whole lines)
   double *S;      // [K][3][NX][NX]
@@ -342,12 +335,21 @@ struct WChunk {
   int32_t sep;   // the separator's row at the next level
 };
 
-// The system at one level: diagonal block (two shares), coupling to the previous row,
-// right-hand side (two shares), solution; blocks by columns.
+// The last row of a problem: a separator, or the problem's only knot.
+struct WRoot {
+  int64_t row;
+  int32_t id;    // problem
+  int32_t knot;  // 1: a knot
+};
+
+// The rows of one level: diagonal block (two shares), coupling to the previous row, right-hand
+// side (two shares), solution; blocks by columns.  The separators of all levels above the knots
+// are numbered in one sequence.
 struct WLevel {
   double *d0, *d1, *l, *y0, *y1, *x;
   int64_t s0, s1, sl;  // doubles from one row's block to the next
   double *ph, *z;      // what this level's elimination leaves: -W^T | H^T by columns, z
+  int64_t sp;          // doubles from one row's ph to the next
 };
 
 struct WDirect {
@@ -429,7 +431,9 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
     }
     const double z = b[W];
     if (rowv) {
-      double *o = a.in.ph + (C.k0 + i) * 2 * MM + (isF ? MM : 0) + c0 * NX + r;
+      // (in the place of row i's own shares of the diagonal block, which the whole workgroup
+      // had moved to LDS before its first barrier and nobody else reads)
+      double *o = a.in.ph + (C.k0 + i) * a.in.sp + (isF ? MM : 0) + c0 * NX + r;
 #pragma unroll
       for (int c = 0; c < W; ++c) o[c * NX] = b[c];
       if (slot == 0) a.in.z[(C.k0 + i) * NX + r] = z;
@@ -461,21 +465,21 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
   if (rowv) {
     if (isF)
 #pragma unroll
-      for (int c = 0; c < W; ++c) a.out.d0[s * MM + (c0 + c) * NX + r] = Ds[c];
+      for (int c = 0; c < W; ++c) a.out.d0[s * a.out.s0 + (c0 + c) * NX + r] = Ds[c];
     if (slot == 0) a.out.y0[s * NX + r] = ys;
     if (C.b0 == 0) {  // a problem's first separator has no share from a previous chunk
       if (!isF)
 #pragma unroll
-        for (int c = 0; c < W; ++c) a.out.d1[s * MM + (c0 + c) * NX + r] = 0.0;
+        for (int c = 0; c < W; ++c) a.out.d1[s * a.out.s1 + (c0 + c) * NX + r] = 0.0;
       if (slot == 0) a.out.y1[s * NX + r] = 0.0;
     }
     if (C.b0 + 4 < N) {
 #pragma unroll
       for (int c = 0; c < W; ++c) {
         if (isF)
-          a.out.l[(s + 1) * MM + (c0 + c) * NX + r] = O[c];
+          a.out.l[(s + 1) * a.out.sl + (c0 + c) * NX + r] = O[c];
         else
-          a.out.d1[(s + 1) * MM + (c0 + c) * NX + r] = O[c];
+          a.out.d1[(s + 1) * a.out.s1 + (c0 + c) * NX + r] = O[c];
       }
       if (slot == 0) a.out.y1[(s + 1) * NX + r] = yc;
     }
@@ -483,16 +487,17 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
   if (!pd) a.flag[C.id] = 1;  // every writer stores the same value
 }
 
-// The last row of problem p: x = D^-1 y, the stats, and the breakdown flag cleared for the next
+// The last row of each problem: x = D^-1 y, the stats, and the breakdown flag cleared for the next
 // solve (wide_epilogue turns a non-finite multiplier into BREAKDOWN as well).
-template <int NX, bool KNOTS>
-__global__ void __launch_bounds__(64) wide_root(const WArgs a, const WLevel v, const ProbDescW *probs, int nprobs, int32_t *flag) {
+template <int NX>
+__global__ void __launch_bounds__(64) wide_root(const WArgs a, const WLevel knots, const WLevel seps, const WRoot *roots,
+                                                int nprobs, int32_t *flag) {
   const PairLane L(threadIdx.x);
   const int p = blockIdx.x * 2 + L.pr;
   const bool live = p < nprobs;
-  const int q = live ? p : nprobs - 1;
-  const ProbDescW P = probs[q];
-  const int64_t k = KNOTS ? P.k0 : q;  // level 0: the problem's only knot; above, separator p
+  const WRoot P = roots[live ? p : nprobs - 1];
+  const int64_t k = P.row;
+  const WLevel v = P.knot ? knots : seps;
   double D[NX], y[1];
   bool pd = true;
 #pragma unroll
@@ -526,7 +531,7 @@ __global__ void __launch_bounds__(128) wide_back(const WDirect a) {
   const double xl = a.out.x[s * NX + r];
   double P[NX], u = t == 0 ? xl : 0.0;
   const bool inner = t > 0 && i < C.N;
-  const double *ph = a.in.ph + (C.k0 + (inner ? i : 0)) * 2 * MM + r;
+  const double *ph = a.in.ph + (C.k0 + (inner ? i : C.b0)) * a.in.sp + r;
 #pragma unroll
   for (int j = 0; j < NX; ++j) P[j] = inner ? ph[MM + j * NX] : 0.0;
   if (inner) u = a.in.z[(C.k0 + i) * NX + r];
