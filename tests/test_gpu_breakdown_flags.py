@@ -1,0 +1,68 @@
+"""GPU tests of the direct solves' breakdown flags: in a ragged batch the problem whose Schur
+system is not positive definite reports BREAKDOWN, wherever its elimination meets the row, and no
+other problem does or changes a bit; the next solve of the repaired batch is clean.
+
+The bad row b: Q_b = -I between Q_{b-1} = 10 I and Q_{b+1} = I / 100, so that S_bb ~ -1 + 0.1 is
+the only diagonal block that is not positive definite.  Rows 1, 2, 3 of four are eliminated with
+their chunk of knots; rows 4, 8, 12 with the first level of separators, rows 16, 32, 128 above
+or by the last solve, row 0 as the root."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2309_08079_amd import synth
+
+pytestmark = pytest.mark.gpu
+CTX = {}
+
+
+def context(nx):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_08079_amd.mpcpcg import Context
+    if nx not in CTX:
+        CTX[nx] = Context(nx, nx // 2, max_total_knots=512, max_batch=8)
+        CTX[nx].mpcpcg_set_method("factor")
+    return CTX[nx]
+
+
+def spoil(p, b):
+    n = p["Q"].shape[1]
+    p = dict(p, Q=p["Q"].copy())
+    p["Q"][b] = -np.eye(n)
+    if b > 0:
+        p["Q"][b - 1] = 10 * np.eye(n)
+    if b + 1 < len(p["Q"]):
+        p["Q"][b + 1] = 0.01 * np.eye(n)
+    return p
+
+
+@pytest.mark.parametrize("nx", [14, 28])
+@pytest.mark.parametrize("N,b", [(1, 0), (3, 0), (40, 0), (40, 1), (40, 3), (40, 39), (40, 4), (40, 12), (40, 16), (140, 4),
+                                 (140, 16), (140, 32), (140, 128), (140, 139)])
+def test_one_bad_problem_of_a_ragged_batch(nx, N, b):
+    from paper_2309_08079_amd import mpcpcg as M
+    c = context(nx)
+    Ns = [17, 5, N, 1, 150]
+    good = synth.batch(Ns, seed0=600, nx=nx, nu=nx // 2)
+
+    def run(probs):
+        packed, off = synth.pack(probs)
+        d = M.to_device(packed)
+        out = c.mpcpcg_solve_batched(d, off)
+        g = c.mpcpcg_backward(d, off, out, 2 * out["lam"])
+        torch.cuda.synchronize()
+        return out["lam"].cpu().numpy(), M.stats_to_numpy(out["stats"])["status"], M.stats_to_numpy(g["stats"])["status"], off
+
+    lam, fs, bs, off = run(good)
+    assert (fs == M.OK).all() and (bs == M.OK).all()
+    bad = list(good)
+    bad[2] = spoil(good[2], b)
+    lamb, fsb, bsb, _ = run(bad)
+    want = [M.BREAKDOWN if i == 2 else M.OK for i in range(len(Ns))]
+    assert list(fsb) == want and list(bsb) == want
+    for i in (0, 1, 3, 4):
+        assert np.array_equal(lamb[off[i]:off[i + 1]], lam[off[i]:off[i + 1]]), i
+    lam2, fs2, bs2, _ = run(good)
+    assert (fs2 == M.OK).all() and (bs2 == M.OK).all() and np.array_equal(lam2, lam)
