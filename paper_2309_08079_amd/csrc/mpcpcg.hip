@@ -1019,15 +1019,21 @@ int wide_run(mpcpcg_ctx *c, const std::vector<int64_t> &off, mpc::wide::WArgs &a
   a.nknots = w->nknots;
   const bool fac = !form_only && use_factor(c, off, a.warm != 0);
   a.direct = fac ? 1 : 0;
-  a.need_up = fac ? 0 : 1;
+  a.need_up = fac || form_only ? 0 : 1;
   namespace mw = mpc::wide;
   const dim3 pair_grid((w->nknots + 2 * mw::kPairWaves - 1) / (2 * mw::kPairWaves)), pair_blk(mw::kPairWaves * 64);
-  hipLaunchKernelGGL((mw::wide_form<kWNX, kWNU>), pair_grid, pair_blk, 0, s, a);
-  if (!fac) {
-    hipLaunchKernelGGL(mw::wide_theta<kWNX>, pair_grid, pair_blk, 0, s, a);
-    hipLaunchKernelGGL(mw::wide_precond<kWNX>, pair_grid, pair_blk, 0, s, a);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, pair_grid, pair_blk, 0, s, a); };
+  if (!form_only) {
+    launch(mw::wide_form<kWNX, kWNU, false>);
+    if (!fac) {
+      launch(mw::wide_theta<kWNX, false>);
+      launch(mw::wide_precond<kWNX, false>);
+    }
+  } else {
+    launch(mw::wide_form<kWNX, kWNU, true>);
+    launch(mw::wide_theta<kWNX, true>);
+    launch(mw::wide_precond<kWNX, true>);
   }
-  if (form_only) hipLaunchKernelGGL(mw::wide_export<kWNX>, dim3(w->nknots), dim3(256), 0, s, a);
   HIPCHK(c, hipGetLastError());
   if (form_only) return MPCPCG_OK;
   if (fac) {

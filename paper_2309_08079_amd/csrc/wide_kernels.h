@@ -53,7 +53,7 @@ struct WArgs {
   int32_t warm;
   int32_t adjoint;
   int32_t stop_abs;   // 1: eta < eps; 0: sqrt(eta / eta_ref) < eps
-  int32_t need_up;    // 1: wide_form also writes S_{b,b+1} (the PCG and the export read it)
+  int32_t need_up;    // 1: wide_form also writes S_{b,b+1} (the PCG reads it)
   int32_t direct;     // 1: wide_epilogue checks the multipliers (the PCG does it as it goes)
   double *lamw;       // [K][NX] lambda
 };
@@ -102,7 +102,31 @@ struct PairLane {
         rowv((tid & 15) < 14) {}
 };
 
-template <int NX, int NU>
+// A block to the caller's row-major FP32 array: from the lanes' rows by way of a pair's LDS, whole
+// lines (rows: this thread's row of the block; the pair's lanes all call it or none)
+template <int NX>
+__device__ __forceinline__ void put_block(float *out, float *lds, const double (&rows)[NX], const PairLane &L) {
+  constexpr int MM = NX * NX;
+  const int me = threadIdx.x & 31;
+  wave_lds_order();
+  if (L.rowv)
+#pragma unroll
+    for (int j = 0; j < NX; ++j) lds[L.r * NX + j] = (float)rows[j];
+  wave_lds_order();
+#pragma unroll 4
+  for (int e = me; e < MM; e += 32) out[e] = lds[e];
+}
+template <int NX>
+__device__ __forceinline__ void zero_block(float *out) {
+  for (int e = threadIdx.x & 31; e < NX * NX; e += 32) out[e] = 0.0f;
+}
+
+// EXPORT (mpcpcg_form_schur): the three kernels of the preconditioner also write S, Phi^-1 and
+// gamma of one problem as the caller's arrays.  Measured on MI355X, us a call in a row (alone, its
+// inputs not in cache), 4, 64 and 512 knots: 42.0 (61.1), 42.2 (55.0), 45.5 (58.0); with a fourth
+// launch that read them back from the workspace 44.1 (63.1), 48.2 (60.4), 60.0 (70.2); one wave
+// per knot and a workgroup per knot for the preconditioner 52.0 (69.0), 54.0 (69.7), 70.0 (82.8).
+template <int NX, int NU, bool EXPORT>
 __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_form(const WArgs a) {
   static_assert(NX == pair::kN && NU == pair::kH, "blocks of 28 and 14 rows");
   constexpr int MM = NX * NX;
@@ -182,6 +206,10 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
 #pragma unroll
       for (int j = 0; j < NX; ++j) S[2 * MM + j * NX + r] = 0.0;
   }
+  if constexpr (EXPORT) {
+    if (live && b == 0) zero_block<NX>(a.S_out + kb * 3 * MM);
+    if (live && !next) zero_block<NX>(a.S_out + (kb * 3 + 2) * MM);
+  }
   if (!__any(next)) return;
   double (&T)[NX] = Qi, G[NX], p1;  // T replaces Q^-1 column by column
   wave_lds_order();
@@ -202,6 +230,15 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
       S0[j * NX] = -T[j];
       if (a.need_up) S2[j] = -T[j];
     }
+  }
+  if constexpr (EXPORT) {
+    double V[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) V[j] = -T[j];
+    if (live && next) put_block<NX>(a.S_out + (kb + 1) * 3 * MM, s1, V, L);  // (A_b has been used)
+    if (outn)
+#pragma unroll
+      for (int j = 0; j < NX; ++j) a.S_out[(kb * 3 + 2) * MM + j * NX + r] = (float)V[j];
   }
   {
     // the control: both halves hold R^-1, each its rows of B
@@ -227,9 +264,10 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
 
 // S_bb, the right-hand side and D_b^-1 of knot b from the shares (D_0^-1 = S_00^-1 is Q_0
 // itself).
-template <int NX>
+template <int NX, bool EXPORT>
 __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_theta(const WArgs a) {
   constexpr int MM = NX * NX;
+  __shared__ float stage[EXPORT ? kPairWaves * 2 : 1][EXPORT ? MM : 1];
   const PairLane L(threadIdx.x);
   const int t = (blockIdx.x * kPairWaves + (threadIdx.x >> 6)) * 2 + L.pr;
   const bool live = t < a.nknots;
@@ -250,6 +288,11 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
 #pragma unroll
     for (int j = 0; j < NX; ++j) S1[j * NX] = D[j];
   }
+  if constexpr (EXPORT)
+    if (live) {
+      put_block<NX>(a.S_out + (kb * 3 + 1) * MM, stage[threadIdx.x >> 5], D, L);
+      if (L.rowv) a.gam_out[kb * NX + r] = (float)y;
+    }
   if (__any(kd.b > 0)) pair::gj_solve<NX>(D, I, L.lane, L.half, pd);
   if (kd.b == 0)
 #pragma unroll
@@ -260,10 +303,12 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
 }
 
 // Phi^-1 blocks, one pair per knot b (needs D^-1 of b and b + 1): D_b^-1 itself, and
-// -D_{b+1}^-1 S_{b+1,b} D_b^-1, which is Phi^-1_{b+1,b} and, transposed, Phi^-1_{b,b+1}.
-template <int NX>
+// -D_{b+1}^-1 S_{b+1,b} D_b^-1, which is Phi^-1_{b+1,b} and, transposed, Phi^-1_{b,b+1}.  To the
+// workspace by columns, or (EXPORT) only to the caller's array.
+template <int NX, bool EXPORT>
 __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) wide_precond(const WArgs a) {
   constexpr int MM = NX * NX;
+  __shared__ float stage[EXPORT ? kPairWaves * 2 : 1][EXPORT ? MM : 1];
   const PairLane L(threadIdx.x);
   const int t = (blockIdx.x * kPairWaves + (threadIdx.x >> 6)) * 2 + L.pr;
   const bool live = t < a.nknots;
@@ -275,7 +320,13 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
   double D[NX], Y[NX];
 #pragma unroll
   for (int j = 0; j < NX; ++j) D[j] = a.Dinv[kb * MM + j * NX + r];
-  if (out) {
+  if constexpr (EXPORT) {
+    if (live) {
+      put_block<NX>(a.P_out + (kb * 3 + 1) * MM, stage[threadIdx.x >> 5], D, L);
+      if (kd.b == 0) zero_block<NX>(a.P_out + kb * 3 * MM);
+      if (!next) zero_block<NX>(a.P_out + (kb * 3 + 2) * MM);
+    }
+  } else if (out) {
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
       P[MM + j * NX] = (float)D[j];
@@ -291,7 +342,12 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
 #pragma unroll
   for (int j = 0; j < NX; ++j) Y[j] = -a.Dinv[kn * MM + j * NX + r];
   pair::mm_inplace<NX>(Y, D);
-  if (out && next) {
+  if constexpr (EXPORT) {
+    if (live && next) put_block<NX>(a.P_out + kn * 3 * MM, stage[threadIdx.x >> 5], D, L);
+    if (out && next)
+#pragma unroll
+      for (int j = 0; j < NX; ++j) a.P_out[(kb * 3 + 2) * MM + j * NX + r] = (float)D[j];
+  } else if (out && next) {
     float *Pn = a.P + kn * 3 * MM + r, *Pu = a.P + (kb * 3 + 2) * MM + r * NX;
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
@@ -299,19 +355,6 @@ __global__ void __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_p
       Pu[j] = (float)D[j];
     }
   }
-}
-
-// S, Phi^-1 and gamma of one problem as the caller's row-major FP32 arrays.
-template <int NX>
-__global__ void __launch_bounds__(256) wide_export(const WArgs a) {
-  constexpr int MM = NX * NX;
-  const int64_t kb = a.knots[blockIdx.x].k0 + a.knots[blockIdx.x].b;
-  for (int t = threadIdx.x; t < 3 * MM; t += 256) {
-    const int64_t in = (kb * 3 + t / MM) * MM + (t % NX) * NX + t % MM / NX;
-    a.S_out[kb * 3 * MM + t] = (float)a.S[in];
-    a.P_out[kb * 3 * MM + t] = a.P[in];
-  }
-  if (threadIdx.x < NX) a.gam_out[kb * NX + threadIdx.x] = (float)a.rhs[kb * NX + threadIdx.x];
 }
 
 // ---------------------------------------------------------------- direct solve
