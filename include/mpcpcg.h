@@ -226,7 +226,7 @@ int mpcpcg_cache_info(const mpcpcg_ctx *ctx, int32_t *entries, int64_t *device_b
  * inject_stall = 1 is a test hook: the first such wait of every launch of the (14, 7)
  * path waits for a signal that is never sent, so each multi-workgroup problem times out
  * (the factorisation path has no such wait: there the hook only makes every problem of more
- * than 16 knots report MPCPCG_TIMEOUT). */
+ * than 16 knots that was solved report MPCPCG_TIMEOUT instead of OK). */
 int mpcpcg_debug_set_wait(mpcpcg_ctx *ctx, int64_t limit_us, int32_t inject_stall);
 
 /* Solution method of mpcpcg_solve, mpcpcg_solve_batched and mpcpcg_backward.

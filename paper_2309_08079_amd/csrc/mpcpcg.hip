@@ -637,7 +637,6 @@ int direct_schedule(mpcpcg_ctx *c, const Sig &off, DirectSchedule **out) {
   if (int st = check_direct_horizon(c, nmax)) return st;
   auto s = std::make_unique<DirectSchedule>();
   s->nprobs = B;
-  s->nprobs = B;
   // longest problems first: their separator systems take the longest
   std::vector<int> order(B);
   for (int b = 0; b < B; ++b) order[b] = b;
@@ -723,7 +722,6 @@ int run_direct(mpcpcg_ctx *c, const KArgs &k, int mode, const Sig *off, int N, h
   a.dQ = k.dQ; a.dR = k.dR; a.dA = k.dA; a.dB = k.dB; a.dq = k.dq; a.dr = k.dr;
   a.dx0 = k.dx0; a.de = k.de; a.dgamma = k.dgamma;
   a.stats = k.stats;
-  a.stall = k.stall;
   DirectSchedule *s = nullptr;
   int levels;
   if (off) {
@@ -784,6 +782,7 @@ int run_direct(mpcpcg_ctx *c, const KArgs &k, int mode, const Sig *off, int N, h
     hipLaunchKernelGGL((mpc::direct_back<kNX, kNU, true>), back_grid(), dim3(mpc::kBackThreads), 0, stream, a);
   else
     hipLaunchKernelGGL((mpc::direct_back<kNX, kNU, false>), back_grid(), dim3(mpc::kBackThreads), 0, stream, a);
+  if (c->stall) hipLaunchKernelGGL(mpc::direct_stall_hook, dim3((a.nprobs + 63) / 64), dim3(64), 0, stream, a);
   HIPCHK(c, hipGetLastError());
   return MPCPCG_OK;
 }

@@ -85,7 +85,6 @@ struct DirectArgs {
   double *wh, *z;
   SepLevel in, out;
   int32_t *flag;     // [problems] 1 once a pivot was not > 0 (0 between solves)
-  int32_t stall;     // test hook (mpcpcg_debug_set_wait)
 };
 
 __device__ __forceinline__ Chunk chunk_of(const DirectArgs &a, int g) {
@@ -550,9 +549,7 @@ __global__ void __launch_bounds__(kCrThreads) separator_solve(const DirectArgs a
     a.flag[P.id] = 0;
     mpcpcg_stats st;
     st.iters = 0;
-    // this path waits for nothing across workgroups; under the test hook it reports what a
-    // problem of more than one 16-knot part reports elsewhere
-    st.status = a.stall && P.N > 16 ? MPCPCG_TIMEOUT : bad ? MPCPCG_BREAKDOWN : MPCPCG_OK;
+    st.status = bad ? MPCPCG_BREAKDOWN : MPCPCG_OK;
     st.final_ratio = 0.0f;
     st.reserved = 0;
     a.stats[P.id] = st;
@@ -715,6 +712,16 @@ __global__ void __launch_bounds__(kBackThreads) direct_back(const DirectArgs a) 
       a.dr[cb * NU + lane] = (float)uv;
     }
   }
+}
+
+// The test hook of mpcpcg_debug_set_wait, launched only while it is set: these kernels wait for
+// nothing across workgroups, so no time-out can be forced; a solved problem of more knots than
+// one part of the PCG's (16) reports TIMEOUT all the same, any other keeps its status.
+__global__ void __launch_bounds__(64) direct_stall_hook(const DirectArgs a) {
+  const int p = blockIdx.x * 64 + threadIdx.x;
+  if (p >= a.nprobs) return;
+  const SepProb P = sep_prob_of(a, p);
+  if (P.N > 16 && a.stats[P.id].status == MPCPCG_OK) a.stats[P.id].status = MPCPCG_TIMEOUT;
 }
 
 }  // namespace mpc

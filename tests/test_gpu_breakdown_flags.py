@@ -66,3 +66,22 @@ def test_one_bad_problem_of_a_ragged_batch(nx, N, b):
         assert np.array_equal(lamb[off[i]:off[i + 1]], lam[off[i]:off[i + 1]]), i
     lam2, fs2, bs2, _ = run(good)
     assert (fs2 == M.OK).all() and (bs2 == M.OK).all() and np.array_equal(lam2, lam)
+
+
+def test_the_wait_hook_hides_no_breakdown():
+    # the direct solve waits for nothing, so a problem that breaks down under the test hook of
+    # the waits says so; solved problems of more than 16 knots report the time-out
+    from paper_2309_08079_amd import mpcpcg as M
+    c = context(14)
+    probs = synth.batch([40, 40, 16, 17], seed0=700)
+    probs[1] = spoil(probs[1], 5)
+    packed, off = synth.pack(probs)
+    d, bad = M.to_device(packed), M.to_device(probs[1])
+    try:
+        c.mpcpcg_debug_set_wait(200, inject_stall=True)
+        got = [M.stats_to_numpy(c.mpcpcg_solve_batched(d, off)["stats"])["status"],
+               M.stats_to_numpy(c.mpcpcg_solve(bad)["stats"])["status"]]
+    finally:
+        c.mpcpcg_debug_set_wait(2_000_000, inject_stall=False)
+    assert list(got[0]) == [M.TIMEOUT, M.BREAKDOWN, M.OK, M.TIMEOUT] and list(got[1]) == [M.BREAKDOWN]
+    assert list(M.stats_to_numpy(c.mpcpcg_solve_batched(d, off)["stats"])["status"]) == [M.OK, M.BREAKDOWN, M.OK, M.OK]
