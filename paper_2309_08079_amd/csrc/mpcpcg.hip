@@ -585,13 +585,9 @@ int get_schedule(mpcpcg_ctx *c, const std::vector<int64_t> &off, int kpw, Schedu
   return MPCPCG_OK;
 }
 
-// Levels of separators: a level has at most a quarter of the rows of the one before it and
-// one more per problem; levels follow until the longest horizon has at most kCrBlocks.
-int64_t level_slots(const mpcpcg_ctx *c, int level) {  // level 0: knots
-  int64_t n = c->max_knots;
-  for (int l = 0; l < level; ++l) n = n / mpc::kChunk + c->max_batch;
-  return n;
-}
+// Levels of separators: a level takes four rows of a problem to one; levels follow until the
+// longest horizon has at most kCrBlocks rows, and a problem leaves them once one row of it is
+// left (level 1 has every problem).
 int separator_levels(int64_t nmax) {
   int l = 0;
   do {
@@ -600,16 +596,28 @@ int separator_levels(int64_t nmax) {
   } while (nmax > mpc::kCrBlocks);
   return l;
 }
+// Separators that a batch can need in all: on level l the problems with more than 4^(l - 1)
+// knots, n knots of one making at most (n - 1) / 4^l + 1.
+int64_t separator_slots(const mpcpcg_ctx *c) {
+  const int64_t K = c->max_knots;
+  const int levels = separator_levels(std::min<int64_t>(K, (int64_t)32 * c->cus));
+  int64_t total = 0, q = 1;
+  for (int l = 1; l <= levels; ++l) {
+    const int64_t B = std::min<int64_t>(c->max_batch, l == 1 ? K : K / (q + 1));
+    q *= mpc::kChunk;
+    total += (K - B) / q + B;
+  }
+  return total;
+}
 
 // Doubles per row of a level: blocks by columns padded to 16 rows (one 128-byte line each).
 constexpr size_t kBlkDoubles = (size_t)kNX * mpc::kGroup;
 
 int ensure_factor_ws(mpcpcg_ctx *c) {
   if (c->f_ws) return MPCPCG_OK;
-  // W, H and z of every row that some level eliminates; the systems of the levels above 0
-  const int levels = separator_levels(c->max_knots);
-  size_t n = (size_t)c->max_knots * (2 * kBlkDoubles + mpc::kGroup);
-  for (int l = 1; l <= levels; ++l) n += (size_t)level_slots(c, l) * (5 * kBlkDoubles + 4 * mpc::kGroup);
+  // W, H and z of every knot; the separators' rows (W and H in the place of their diagonal block)
+  const size_t n = (size_t)c->max_knots * (2 * kBlkDoubles + mpc::kGroup) +
+                   (size_t)separator_slots(c) * (3 * kBlkDoubles + 4 * mpc::kGroup);
   const size_t fb = sizeof(int) * (size_t)c->max_batch;
   if (hipMalloc(&c->f_ws, sizeof(double) * n) != hipSuccess || hipMalloc(&c->f_flag, fb) != hipSuccess) {
     (void)hipGetLastError();
@@ -644,16 +652,18 @@ int direct_schedule(mpcpcg_ctx *c, const Sig &off, DirectSchedule **out) {
   std::vector<mpc::SepProb> rows;  // the problems' rows at the current level
   for (int b : order) rows.push_back(mpc::SepProb{(int32_t)off[b], (int32_t)(off[b + 1] - off[b]), b, (int32_t)(off[b + 1] - off[b])});
   bool ok = true;
+  int64_t slots = 0;  // separators so far
   for (int l = 0; l < separator_levels(nmax); ++l) {
     std::vector<mpc::Chunk> chunks;
     for (auto &p : rows) {
-      const int32_t slot = (int32_t)chunks.size();
+      if (l > 0 && p.nsep == 1) continue;
+      const int32_t first = (int32_t)slots;
       for (int k = 0; k < p.nsep; k += mpc::kChunk)
-        chunks.push_back(mpc::Chunk{p.sep0, p.nsep, p.id, k, (int32_t)chunks.size()});
-      p.sep0 = slot;
+        chunks.push_back(mpc::Chunk{p.sep0, p.nsep, p.id, k, (int32_t)slots++});
+      p.sep0 = first;
       p.nsep = (p.nsep + mpc::kChunk - 1) / mpc::kChunk;
     }
-    if ((int64_t)chunks.size() > level_slots(c, l + 1)) return fail(c, MPCPCG_EINVAL, "batch exceeds the factorisation workspace");
+    if (slots > separator_slots(c)) return fail(c, MPCPCG_EINVAL, "batch exceeds the factorisation workspace");
     s->nchunks.push_back((int)chunks.size());
     s->d_chunks.push_back(s->mem.upload(chunks.data(), chunks.size()));
     ok = ok && s->d_chunks.back();
@@ -735,30 +745,31 @@ int run_direct(mpcpcg_ctx *c, const KArgs &k, int mode, const Sig *off, int N, h
   a.nprobs = s ? s->nprobs : 1;
   a.probs = s ? s->d_probs : nullptr;
   a.flag = c->f_flag;
-  // the workspace, level by level
   double *w = c->f_ws;
   auto take = [&](size_t n) { double *p = w; w += n; return p; };
-  std::vector<mpc::SepLevel> lev(levels + 1);
-  std::memset(lev.data(), 0, sizeof(mpc::SepLevel) * lev.size());
-  for (int l = 0; l <= levels; ++l) {
-    const size_t n = (size_t)level_slots(c, l);
-    mpc::SepLevel &v = lev[l];
-    if (l < levels) { v.wh = take(n * 2 * kBlkDoubles); v.z = take(n * mpc::kGroup); }
-    if (l > 0) {
-      v.dl = take(n * kBlkDoubles); v.dr = take(n * kBlkDoubles); v.l = take(n * kBlkDoubles);
-      v.yl = take(n * mpc::kGroup); v.yr = take(n * mpc::kGroup); v.x = take(n * mpc::kGroup);
-    }
-  }
-  // a launch over the chunks of level l
+  const size_t K = (size_t)c->max_knots, S = (size_t)separator_slots(c);
+  double *wh0 = take(K * 2 * kBlkDoubles), *z0 = take(K * mpc::kGroup);
+  a.sep.d = take(S * 2 * kBlkDoubles);
+  a.sep.l = take(S * kBlkDoubles);
+  a.sep.yl = take(S * mpc::kGroup);
+  a.sep.yr = take(S * mpc::kGroup);
+  a.sep.x = take(S * mpc::kGroup);
+  double *z1 = take(S * mpc::kGroup);
+  // a launch over the chunks of level l (over what is left of the problems after the last one)
   auto at = [&](int l) {
-    int64_t rows = N;
-    for (int i = 0; i < l; ++i) rows = (rows + mpc::kChunk - 1) / mpc::kChunk;
+    int64_t rows = N, first = 0, next = 0;  // of the one problem: this level's and the next one's first separator
+    for (int i = 0; i < l; ++i) {
+      rows = (rows + mpc::kChunk - 1) / mpc::kChunk;
+      first = next;
+      next += rows;
+    }
     a.N1 = (int)rows;
+    a.k0 = (int)first;
+    a.sep0 = (int)next;
     a.nchunks = s ? (l < levels ? s->nchunks[l] : 0) : (int)((rows + mpc::kChunk - 1) / mpc::kChunk);
     a.chunks = s && l < levels ? s->d_chunks[l] : nullptr;
-    a.wh = lev[l].wh; a.z = lev[l].z;
-    a.in = lev[l];
-    if (l < levels) a.out = lev[l + 1];
+    a.wh = l ? a.sep.d : wh0;
+    a.z = l ? z1 : z0;
   };
   auto elim_grid = [&] { return dim3((a.nchunks + mpc::kElimWaves - 1) / mpc::kElimWaves); };
   at(0);

@@ -44,11 +44,11 @@ constexpr int kChunk = 4;  // knots per chunk (one per knot group of a wave)
 
 // One chunk of a problem: of its knots (level 0) or of its separators (level 1, 2, ...).
 struct Chunk {
-  int64_t k0;    // first row of the problem at this level (packed knot, separator slot)
+  int64_t k0;    // first row of the problem at this level (packed knot, separator)
   int32_t N;     // knots, or separators, of the problem
   int32_t id;    // problem index b (x0 row, stats slot, control offset k0 - b)
   int32_t b0;    // first row of the chunk, its separator (a multiple of kChunk)
-  int32_t sep;   // the separator's slot at the next level
+  int32_t sep;   // the separator among all
 };
 
 // The separators of one problem that separator_solve takes.
@@ -57,14 +57,16 @@ struct SepProb {
   int32_t id, N;
 };
 
-// The separators' system at one level: blocks by columns padded to kGroup rows (lane = row: a
-// column is one line), vectors padded to kGroup.
-struct SepLevel {
-  double *dl, *dr;  // the diagonal block: its own chunk's share and the previous chunk's
+// The separators' systems, those of all levels numbered in one sequence: blocks by columns padded
+// to kGroup rows (lane = row: a column is one line), vectors padded to kGroup.
+struct SepRows {
+  // the diagonal block: its own chunk's share, then the previous chunk's, [row][2][NX][kGroup];
+  // -W^T and H^T in their place once the row is eliminated (a chunk's wave has moved both to
+  // LDS by then, and nobody else reads them)
+  double *d;
   double *l;        // the coupling to the previous separator
   double *yl, *yr;  // the right-hand side, two shares
   double *x;        // the solution
-  double *wh, *z;   // what the elimination of this level leaves for its back substitution
 };
 
 struct DirectArgs {
@@ -75,25 +77,26 @@ struct DirectArgs {
   float *dQ, *dR, *dA, *dB, *dq, *dr, *dx0, *de, *dgamma;
   mpcpcg_stats *stats;
   // schedule: the chunks of this launch's level, or (nullptr) those of one problem with N1
-  // rows at that level
+  // rows at that level, from row k0 to separators from sep0
   const Chunk *chunks;
   const SepProb *probs;
   int32_t nchunks, nprobs, N1;
   int32_t N;         // knots of the one problem
-  // workspace: -W^T and H^T by columns [rows][2][NX][kGroup] and z [rows][kGroup] of this
-  // level's rows, the level itself (unused by level 0) and the next
+  int32_t k0, sep0;
+  // what the elimination of this level's rows leaves: -W^T and H^T by columns
+  // [rows][2][NX][kGroup] and z [rows][kGroup]
   double *wh, *z;
-  SepLevel in, out;
+  SepRows sep;
   int32_t *flag;     // [problems] 1 once a pivot was not > 0 (0 between solves)
 };
 
 __device__ __forceinline__ Chunk chunk_of(const DirectArgs &a, int g) {
   if (a.chunks) return a.chunks[g];
-  return Chunk{0, a.N1, 0, g * kChunk, g};
+  return Chunk{a.k0, a.N1, 0, g * kChunk, a.sep0 + g};
 }
 __device__ __forceinline__ SepProb sep_prob_of(const DirectArgs &a, int p) {
   if (a.probs) return a.probs[p];
-  return SepProb{0, a.N1, 0, a.N};
+  return SepProb{a.k0, a.N1, 0, a.N};
 }
 
 // ---------------------------------------------------------------- elimination
@@ -128,7 +131,7 @@ struct ElimShared {
 };
 
 // Eliminates rows 1 .. 3 of the chunk whose blocks are in sh and whose separator's own
-// diagonal block is in out.dl; writes the shares of the next level.
+// diagonal block is in sep.d; writes the shares of the next level.
 template <int NX>
 __device__ __forceinline__ void eliminate_chunk(const DirectArgs &a, const Chunk &C, ElimShared<NX> &sh, int lane,
                                                 int t, bool &pd) {
@@ -141,7 +144,7 @@ __device__ __forceinline__ void eliminate_chunk(const DirectArgs &a, const Chunk
   double Ds[W];                                          // the group's columns of D_sep
   double ys = sh.y[0][r];
 #pragma unroll
-  for (int c = 0; c < W; ++c) Ds[c] = a.out.dl[((int64_t)C.sep * NX + col[c]) * kGroup + lane];
+  for (int c = 0; c < W; ++c) Ds[c] = a.sep.d[((int64_t)C.sep * 2 * NX + col[c]) * kGroup + lane];
 #pragma unroll 1
   for (int k = 1; k < kChunk; ++k) {
     double D[NX], X[NX], P[2 * W + 1], O[2 * W];
@@ -201,16 +204,16 @@ __device__ __forceinline__ void eliminate_chunk(const DirectArgs &a, const Chunk
 #pragma unroll
   for (int c = 0; c < W; ++c)
     if (W * t + c < NX) {
-      const int64_t o = (s * NX + W * t + c) * kGroup + lane;
-      a.out.dl[o] = Ds[c];
+      const int64_t o = (s * 2 * NX + W * t + c) * kGroup + lane;
+      a.sep.d[o] = Ds[c];
       if (next) {
-        a.out.dr[o + NX * kGroup] = rowv ? sh.D[kChunk - 1][r][W * t + c] : 0.0;
-        a.out.l[o + NX * kGroup] = rowv ? sh.F[W * t + c][r] : 0.0;
+        a.sep.d[o + 3 * NX * kGroup] = rowv ? sh.D[kChunk - 1][r][W * t + c] : 0.0;
+        a.sep.l[((s + 1) * NX + W * t + c) * kGroup + lane] = rowv ? sh.F[W * t + c][r] : 0.0;
       }
     }
   if (t == 0) {
-    a.out.yl[s * kGroup + lane] = rowv ? ys : 0.0;
-    if (next) a.out.yr[(s + 1) * kGroup + lane] = rowv ? sh.y[kChunk][r] : 0.0;
+    a.sep.yl[s * kGroup + lane] = rowv ? ys : 0.0;
+    if (next) a.sep.yr[(s + 1) * kGroup + lane] = rowv ? sh.y[kChunk][r] : 0.0;
   }
 }
 
@@ -289,7 +292,7 @@ __global__ void __launch_bounds__(kElimThreads) direct_eliminate(const DirectArg
     }
     if (t == 0)  // (a pad lane's row of Q^-1 is zero)
 #pragma unroll
-      for (int j = 0; j < NX; ++j) a.out.dl[((int64_t)C.sep * NX + j) * kGroup + lane] = Qi[j];
+      for (int j = 0; j < NX; ++j) a.sep.d[((int64_t)C.sep * 2 * NX + j) * kGroup + lane] = Qi[j];
     lds_order();
     if (rowv) {
 #pragma unroll
@@ -304,7 +307,7 @@ __global__ void __launch_bounds__(kElimThreads) direct_eliminate(const DirectArg
   if (!pd) a.flag[C.id] = 1;  // every writer stores the same value
 }
 
-// The same for a chunk of four separators of level a.in: S_{k+1,k} is the coupling L_{k+1}
+// The same for a chunk of four separators: S_{k+1,k} is the coupling L_{k+1}
 // and the diagonal blocks are the sums of their two shares.
 template <int NX>
 __global__ void __launch_bounds__(kElimThreads) sep_eliminate(const DirectArgs a) {
@@ -323,8 +326,8 @@ __global__ void __launch_bounds__(kElimThreads) sep_eliminate(const DirectArgs a
   {
     // rows past the horizon: identity diagonal, no coupling
     double D[NX], L[NX], G[NX];
-    const double *pl = a.in.l + kn * NX * kGroup + lane;
-    const double *pd_ = a.in.dl + k * NX * kGroup + lane, *pr = a.in.dr + k * NX * kGroup + lane;
+    const double *pl = a.sep.l + kn * NX * kGroup + lane;
+    const double *pd_ = a.sep.d + k * 2 * NX * kGroup + lane, *pr = pd_ + NX * kGroup;
     const bool two = act && b > 0;  // the first separator of a problem has one share
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
@@ -332,7 +335,7 @@ __global__ void __launch_bounds__(kElimThreads) sep_eliminate(const DirectArgs a
       G[j] = two ? pr[j * kGroup] : 0.0;
       L[j] = ctl ? pl[j * kGroup] : 0.0;
     }
-    double y = act ? a.in.yl[k * kGroup + lane] + (two ? a.in.yr[k * kGroup + lane] : 0.0) : 0.0;
+    double y = act ? a.sep.yl[k * kGroup + lane] + (two ? a.sep.yr[k * kGroup + lane] : 0.0) : 0.0;
 #pragma unroll
     for (int j = 0; j < NX; ++j) D[j] = act ? D[j] + G[j] : (j == lane ? 1.0 : 0.0);
     if (rowv) {
@@ -351,7 +354,7 @@ __global__ void __launch_bounds__(kElimThreads) sep_eliminate(const DirectArgs a
     }
     if (t == 0)
 #pragma unroll
-      for (int j = 0; j < NX; ++j) a.out.dl[((int64_t)C.sep * NX + j) * kGroup + lane] = rowv ? D[j] : 0.0;
+      for (int j = 0; j < NX; ++j) a.sep.d[((int64_t)C.sep * 2 * NX + j) * kGroup + lane] = rowv ? D[j] : 0.0;
     lds_order();
   }
   eliminate_chunk<NX>(a, C, sh, lane, t, pd);
@@ -523,11 +526,11 @@ __global__ void __launch_bounds__(kCrThreads) separator_solve(const DirectArgs a
       double D[NX], R[NX], L[NX];
 #pragma unroll
       for (int c = 0; c < NX; ++c) {
-        D[c] = a.in.dl[(o * NX + c) * kGroup + lane];
-        R[c] = i > 0 ? a.in.dr[(o * NX + c) * kGroup + lane] : 0.0;
-        L[c] = i > 0 ? a.in.l[(o * NX + c) * kGroup + lane] : 0.0;
+        D[c] = a.sep.d[(o * 2 * NX + c) * kGroup + lane];
+        R[c] = i > 0 ? a.sep.d[((o * 2 + 1) * NX + c) * kGroup + lane] : 0.0;
+        L[c] = i > 0 ? a.sep.l[(o * NX + c) * kGroup + lane] : 0.0;
       }
-      sh.y[i][lane] = a.in.yl[o * kGroup + lane] + (i > 0 ? a.in.yr[o * kGroup + lane] : 0.0);
+      sh.y[i][lane] = a.sep.yl[o * kGroup + lane] + (i > 0 ? a.sep.yr[o * kGroup + lane] : 0.0);
 #pragma unroll
       for (int c = 0; c < NX; ++c) {
         sh.dl[i][c * NX + lane] = D[c] + R[c];
@@ -542,7 +545,7 @@ __global__ void __launch_bounds__(kCrThreads) separator_solve(const DirectArgs a
   __syncthreads();
   for (s /= 2; s >= 1; s /= 2) op.level_back(s);
   for (int i = threadIdx.x; i < P.nsep * kGroup; i += kCrThreads)
-    a.in.x[(int64_t)P.sep0 * kGroup + i] = i % kGroup < NX ? sh.x[i / kGroup][i % kGroup] : 0.0;
+    a.sep.x[(int64_t)P.sep0 * kGroup + i] = i % kGroup < NX ? sh.x[i / kGroup][i % kGroup] : 0.0;
   const bool bad = __syncthreads_or(!pd) || a.flag[P.id] != 0;
   __syncthreads();  // every thread has read the flag
   if (threadIdx.x == 0) {
@@ -569,7 +572,7 @@ __device__ __forceinline__ void chunk_back(const DirectArgs &a, const Chunk &C, 
   const int N = C.N, b = C.b0 + t;
   const bool rowv = lane < NX;
   const int64_t s = C.sep;
-  const double xl = a.out.x[s * kGroup + lane];
+  const double xl = a.sep.x[s * kGroup + lane];
   double W[NX], H[NX], u;
   if (t > 0 && b < N) {
     const double *w = a.wh + (C.k0 + b) * 2 * NX * kGroup + lane;  // rows of -W^T and H^T
@@ -585,7 +588,7 @@ __device__ __forceinline__ void chunk_back(const DirectArgs &a, const Chunk &C, 
     u = t == 0 ? xl : 0.0;
   }
   u -= row_dot<NX>(H, xl);
-  if (t == 0) xs[kChunk][lane] = C.b0 + kChunk < N ? a.out.x[(s + 1) * kGroup + lane] : 0.0;
+  if (t == 0) xs[kChunk][lane] = C.b0 + kChunk < N ? a.sep.x[(s + 1) * kGroup + lane] : 0.0;
   lds_order();
 #pragma unroll
   for (int i = kChunk - 1; i >= 0; --i) {
@@ -595,7 +598,7 @@ __device__ __forceinline__ void chunk_back(const DirectArgs &a, const Chunk &C, 
   }
 }
 
-// The inner blocks of level a.in from the solution of the next level.
+// The inner blocks of a level of separators from the solution of the next level.
 template <int NX>
 __global__ void __launch_bounds__(kBackThreads) sep_back(const DirectArgs a) {
   __shared__ double shared[kBackWaves][kChunk + 1][kGroup];
@@ -604,7 +607,7 @@ __global__ void __launch_bounds__(kBackThreads) sep_back(const DirectArgs a) {
   if (g >= a.nchunks) return;  // whole waves leave; no workgroup barrier follows
   const Chunk C = chunk_of(a, g);
   chunk_back<NX>(a, C, shared[wave], lane, t);
-  if (C.b0 + t < C.N) a.in.x[(C.k0 + C.b0 + t) * kGroup + lane] = shared[wave][t][lane];
+  if (C.b0 + t < C.N) a.sep.x[(C.k0 + C.b0 + t) * kGroup + lane] = shared[wave][t][lane];
 }
 
 // lambda of every knot, then the knot's primal step or gradients.
