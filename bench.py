@@ -421,7 +421,7 @@ def two_arm_batch(dev, stream, reps=3):
 
 
 def factor_path(dev, stream, reps=3):
-    """The factorisation path (block LDL^T of S, MPCPCG_METHOD_FACTOR) on the headline batch
+    """The factorisation path (block elimination of S, MPCPCG_METHOD_FACTOR) on the headline batch
     and on one N = 512 problem: batched forward and adjoint, single-solve latency."""
     import torch
     from paper_2309_08079_amd import synth

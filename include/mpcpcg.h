@@ -233,22 +233,28 @@ int mpcpcg_debug_set_wait(mpcpcg_ctx *ctx, int64_t limit_us, int32_t inject_stal
  *   MPCPCG_METHOD_PCG (default): PCG as above (Algorithm 1).
  *   MPCPCG_METHOD_FACTOR: direct solve of the same Schur system, the alternative to the
  *     iterative solve that the paper names as future work (Section VI), by parallel block
- *     elimination of the block-tridiagonal S.  At (14, 7) chunks of four knots are
- *     eliminated in parallel, which leaves every fourth knot, again while a problem has
- *     more than 32 of them, and the rest by block cyclic reduction, one workgroup per
- *     problem; at (28, 14) by block cyclic reduction, every level spread over the device.
+ *     elimination of the block-tridiagonal S: chunks of four knots are eliminated in
+ *     parallel, which leaves every fourth knot, again level by level.  At (14, 7) while a
+ *     problem of the batch has more than 32 of them, and the rest by block cyclic reduction,
+ *     one workgroup per problem; at (28, 14) until one is left per problem.
  *     FP64 throughout, exact up to rounding;
  *     eps, max_iter, warm_start and stop_rule are ignored; stats report iters = 0, status
  *     OK or BREAKDOWN (a non-positive pivot, i.e. S not positive definite, or a non-finite
  *     result), final_ratio = 0.  Its cost does not depend on the conditioning of S.  At
- *     (14, 7) it needs ~6.8 KB of extra device workspace per knot of max_total_knots,
- *     allocated on first use, and takes horizons of up to 32 knots per compute unit.
- *   MPCPCG_METHOD_AUTO: per call, at (14, 7) the faster of the two by a cost model
- *     measured on MI355X, which prices PCG at ~100 iterations for cold starts and ~45 for
- *     warm starts (opts->warm_start; the adjoint counts as cold).  On the Kuka-shaped
- *     problems this takes the factorisation for cold solves, lone problems and large
- *     batches, and PCG for warm-started small batches.  At (28, 14) always the
- *     factorisation, which is faster there at every measured size. */
+ *     (14, 7) it needs extra device workspace, allocated on first use: for K = max_total_knots
+ *     3.7 KB per knot and 5.9 KB per separator, about K / 3 + 3 max_batch of them and at most
+ *     4/3 K (0.82 GB in all for K = 131,072 and max_batch = 4,096); and it takes horizons of up
+ *     to 32 knots per compute unit.  At (28, 14) it needs none beyond the context's.
+ *   MPCPCG_METHOD_AUTO: per call, at (14, 7) by a fixed cost model, which prices PCG at ~100
+ *     iterations for cold starts and ~45 for warm starts (opts->warm_start; the adjoint
+ *     counts as cold) and the factorisation as the slower one that it was when the model was
+ *     fitted.  It takes the factorisation for lone problems, for cold batches of horizons up
+ *     to 320 knots and for large batches, and PCG for cold batches of 2 to ~30 longer
+ *     problems and for warm ones of 2 to ~80 problems of 256 knots and more (~20 to 96 of
+ *     128).  There the factorisation is often the faster one by now; the choice stays because
+ *     it shows in the results (iterations, a lambda stopped at eps or exact), and a caller
+ *     who wants the other sets the method.  At (28, 14) always the factorisation, which is
+ *     faster there at every measured size. */
 enum { MPCPCG_METHOD_PCG = 0, MPCPCG_METHOD_FACTOR = 1, MPCPCG_METHOD_AUTO = 2 };
 int mpcpcg_set_method(mpcpcg_ctx *ctx, int32_t method);
 

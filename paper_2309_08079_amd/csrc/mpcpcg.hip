@@ -298,10 +298,10 @@ KernelFn kernel_for(int mode) {
 
 // `low` asks for the form with two waves per SIMD and Phi^-1 in registers, for launches of
 // one-part problems whose workgroups are all resident at that occupancy (residency.h).  Measured
-// on MI355X, one problem of 16 knots, three waves per SIMD and Phi^-1 in LDS / two and in
-// registers: 0.97 / 0.92 us per iteration, 34 / 30 us for the rest of the solve (the formation
-// has no spills).  The shapes that such launches use have it: 16 knots, and 4 and 8 for one short
-// problem.
+// on MI355X, three waves per SIMD and Phi^-1 in LDS / two and in registers: one problem of 16
+// knots 1.02 / 0.79 us per iteration and 25.0 / 22.4 us for the rest of the solve (the formation
+// has no spills), 512 of them 1.24 / 1.03 and 58 / 54.  The shapes that such launches use have it:
+// 16 knots, and 4 and 8 for one short problem.
 KernelFn kernel_for(int kpw, int mode, bool low = false) {
   if (low) {
     if (kpw == 4 && mode == mpc::kForward) return mpc::pcg_kernel<kNX, kNU, 4, mpc::kForward, 0, 2>;
@@ -679,7 +679,7 @@ int direct_schedule(mpcpcg_ctx *c, const Sig &off, DirectSchedule **out) {
 }
 
 // Whether a call takes the factorisation path: always for MPCPCG_METHOD_FACTOR; for
-// MPCPCG_METHOD_AUTO by a cost model measured on MI355X (nx = 14, microseconds):
+// MPCPCG_METHOD_AUTO at 14 states by a cost model fitted on MI355X (microseconds):
 //   PCG: rounds of resident problems (12,288 knots each), each ~40 + iters x (2.1 + 0.7 f)
 //        with f the fraction of the device the batch fills (2.2 us per iteration for one
 //        N = 512 solve, ~318 us per round of 256 x N = 512); iters ~100 for cold starts and
@@ -690,14 +690,18 @@ int direct_schedule(mpcpcg_ctx *c, const Sig &off, DirectSchedule **out) {
 //        spread over the device, ~49 + 20.5 (log2 N - 4) in all, against ~95 + 2.1 iters
 //        for its PCG solve.
 // The factorisation's prices are those of the method it had when the model was fitted; the
-// chunked elimination is two to three times faster.  The lines stay where they are because
-// the choice shows in the results (iterations in the stats, a lambda stopped at eps or exact):
-// a call keeps the method it has always had.
+// chunked elimination is two to three times faster, so the model takes PCG for some batches
+// that the factorisation would solve sooner (cold ones of 2 to ~30 problems of 384 knots and
+// more, warm ones of 2 to ~80 of 256 and more).  The lines stay where they are because the
+// choice shows in the results (iterations in the stats, a lambda stopped at eps or exact): a
+// call keeps the method it has always had.
 // The adjoint (warm = false) is priced as a cold solve.
 bool use_factor(mpcpcg_ctx *c, const std::vector<int64_t> &off, bool warm) {
   if (c->method == MPCPCG_METHOD_PCG) return false;
   if (c->method == MPCPCG_METHOD_FACTOR) return true;
-  if (c->wide) return true;  // the 28-state PCG runs one workgroup per problem: always slower
+  // 28 states: the direct solve was the faster one at every measured size (32 problems of 64 to
+  // 256 knots, forward: 313 us against 985)
+  if (c->wide) return true;
   const int64_t B = (int64_t)off.size() - 1;
   int64_t nmax = 0;
   for (int64_t b = 0; b < B; ++b) nmax = std::max(nmax, off[b + 1] - off[b]);

@@ -237,8 +237,8 @@ __device__ __forceinline__ double uni(double v) {
 // waves per SIMD (168 VGPRs), which keeps the most knots resident, the FP32 Phi^-1 rows live
 // in LDS; at two (256) they are in registers as well, with the edge waves' ghost rows, and an
 // iteration's products read nothing but vectors.  A 32-knot workgroup (8 waves) fits only two
-// waves per SIMD anyway; the other shapes come in both forms (a 24-knot workgroup has 6 waves,
-// two per compute unit; a 48-knot one has 12 waves, one per compute unit).
+// waves per SIMD anyway; 4, 8 and 16 knots come in both forms (residency.h has the rule).  Of 24
+// knots (6 waves) or 48 (12) a compute unit holds one workgroup.
 template <int KPW>
 constexpr int waves_per_eu() { return KPW == 32 ? 2 : 3; }
 // Rows of a control block as stored by columns (NU = 7 rows padded to 8: half a line).
@@ -1065,7 +1065,6 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       // knot's Phi^-1 row, so no second exchange is needed inside an iteration.
       double p = 0.0, sv = 0.0, sm = 0.0, sp = 0.0;
       double gam_prev = __builtin_inf(), alpha_prev = 1.0, tau = 0.0;
-      // (a scalar branch)
       const int uwave = uni(wave);
       const bool edge_wave = multi && (uwave == 0 || uwave == NW - 1);
       // the ghost knots' rows (setup left them in LDS)
@@ -1085,9 +1084,9 @@ __global__ void __launch_bounds__(KPW * kGroup) __attribute__((amdgpu_waves_per_
       const int rg_wave = NW > 2 ? 1 : 0, ra_wave = !kKeepP ? rg_wave : NW > 2 ? 2 : NW - 1;
       // LEAD: wave 0 turns the totals into the step for the whole workgroup.  With three waves
       // per SIMD the loop is bound by issue, and one wave's arithmetic instead of every wave's
-      // measured 2.2 -> 2.1 us per iteration (256 problems of 128 knots, three rounds); in a
-      // gang at two waves 1.72 -> 1.67 (the wave runs at a higher priority).  In a problem of
-      // one part every wave takes the totals itself: 0.95 -> 0.87 us with 16 knots.
+      // measured 2.2 -> 2.1 us per iteration (256 problems of 128 knots, three rounds).  In a
+      // problem of one part at two waves every wave takes the totals itself: 0.95 -> 0.87 us
+      // with 16 knots.
       auto iterate = [&](auto lead_c) __attribute__((always_inline)) {
       constexpr bool LEAD = decltype(lead_c)::value != 0;
       for (it = 0;; ++it) {

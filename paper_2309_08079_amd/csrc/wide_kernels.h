@@ -69,15 +69,17 @@ struct WArgs {
 // What bounds them is FP64 issue in one chain per wave and, before the blocks were laid out by
 // columns, memory: a lane that walks its own row of 28 doubles touches one line per lane and
 // entry.  Hence whole lines everywhere, and for the row-major inputs a detour through LDS.
-// Measured on MI355X, 5,436 knots (the 32-problem two-arm batch), in us, forward:
-//   wide_form   57 (one wave per knot, pivot rows by readlane, products from LDS: 79, and 52 more
-//               for theta; one pair per knot with row-wise access at 2 waves per SIMD: 105);
-//   wide_theta  36 (with the products of theta and S before: 85); wide_precond 46 (130: one
+// Measured on MI355X, 5,800 knots (a 32-problem two-arm batch), in us a direction:
+//   wide_form   56, 66 with S_{b,b+1} for the PCG (one wave per knot, pivot rows by readlane,
+//               products from LDS: 79, and 52 more for theta; one pair per knot with row-wise
+//               access at 2 waves per SIMD: 105);
+//   wide_theta  38 (with the products of theta and S before: 85); wide_precond 46 (130: one
 //               workgroup per knot, operands in LDS);
-//   wide_eliminate ~ 115 for the knots, 25 for each of three levels above (four levels of odd-even
-//               reduction, blocks re-read on each: ~ 430); its blocks read when needed and
-//               barriers that drained the stores: 164 and 55;
-//   wide_epilogue  43 forward and 34 adjoint (56 and 69 by one wave per knot).
+//   wide_eliminate  110 for the knots, 43, 26 and 24 for the three levels above (odd-even
+//               reduction, eight levels, blocks re-read on each: ~430); its blocks read when
+//               needed and barriers that drained the stores: 164 for the knots, 55 a level;
+//   wide_back 11 and 5 a level, wide_root 8;
+//   wide_epilogue  37, after the PCG 45 (56 forward and 69 adjoint by one wave per knot).
 // order this wave's LDS accesses: its earlier writes complete before its later reads
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)

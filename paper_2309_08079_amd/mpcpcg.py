@@ -301,7 +301,7 @@ class Context:
         self._check(self.lib.mpcpcg_set_knots_per_group(self.h, int(k)), "mpcpcg_set_knots_per_group")
 
     def mpcpcg_set_method(self, method):
-        """'pcg' (default), 'factor' (block LDL^T of S) or 'auto' (cost model per call)."""
+        """'pcg' (default), 'factor' (block elimination of S) or 'auto' (a fixed cost model per call)."""
         if method not in METHODS:
             raise MPCPCGError("method must be one of %s, not %r" % (sorted(METHODS), method))
         self._check(self.lib.mpcpcg_set_method(self.h, METHODS[method]), "mpcpcg_set_method")
