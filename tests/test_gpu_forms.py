@@ -1,9 +1,10 @@
-"""GPU test of the 14-state kernel's two-waves-per-SIMD form, which launches of one-part problems
+"""GPU tests of the 14-state kernel's two-waves-per-SIMD form, which launches of one-part problems
 take while all their workgroups are resident (two 16-knot workgroups per compute unit, 512 on
 the device, 64 per XCD list).  Both forms do the same operations in the same order, so the results
 must not depend on the size of the batch, bit for bit: forward, adjoint and adjoint from the kept factors,
 per XCD and from the global queue, on both sides of the line and beside a longer problem, which
-takes the launch to the other form."""
+takes the launch to the other form; and single solves on four streams, whose gangs fill the XCD
+they share."""
 import numpy as np
 import pytest
 
@@ -43,3 +44,34 @@ def test_one_part_problems_on_both_sides_of_the_line(pin):
         for x, y in zip(run(batch), first):
             assert torch.equal(x, y), len(batch)
     c.close()
+
+
+def test_single_solves_on_four_streams_find_their_places():
+    # 32 + 32 + 16 + 16 parts, the 96 places of the XCD that single solves share: every solve ends
+    # and has the bits it has alone
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2309_08079_amd.mpcpcg import Context, to_device
+    Ns = [512, 512, 256, 256]
+    ctx = [Context(14, 7, max_total_knots=n, max_batch=1) for n in Ns]
+    d = [to_device(synth.problem(n, seed=8400 + i)) for i, n in enumerate(Ns)]
+    alone = []
+    for c, p in zip(ctx, d):
+        o = c.mpcpcg_solve(p)
+        torch.cuda.synchronize()
+        alone.append({k: v.clone() for k, v in o.items()})
+    streams = [torch.cuda.Stream() for _ in Ns]
+    outs = [[] for _ in Ns]
+    torch.cuda.synchronize()
+    for _ in range(10):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                outs[i].append(ctx[i].mpcpcg_solve(d[i]))
+    torch.cuda.synchronize()
+    for i, want in enumerate(alone):
+        assert want["stats"][0, 1] == 0
+        for o in outs[i]:
+            for k in ("lam", "dx", "du", "stats"):
+                assert torch.equal(o[k], want[k]), (i, k)
+    for c in ctx:
+        c.close()
